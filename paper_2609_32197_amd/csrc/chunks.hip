@@ -13,25 +13,52 @@
 // A chunk's selected blocks are its heads' demanded blocks inside the shard,
 // counted from the demand bitsets.
 //
-// run_chunks executes a plan in order on one stream, one attention launch per
-// chunk. A chunk whose heads have no result yet writes (O, lse) directly; any
-// other chunk folds itself into them through the log-sum-exp inside the
-// attention kernel (query blocks with no kept block in the shard exit without
-// touching memory). Heads that no chunk covers end as the empty result.
+// run_chunks executes a plan on one stream. Everything the plan reads is in
+// place when the call's work starts (the call is stream-ordered), so the chunks
+// need not be launches of their own: merge_chunks joins a head's shards wherever
+// no block is counted twice, and a whole schedule of plan_chunks becomes one
+// launch over all heads and blocks. One launch per chunk leaves the GPU to the
+// longest row of each of a few heads: 40 heads x 147 rows, 591 blocks of 128,
+// 89 kept, four owners, 31 chunks took 6.78 ms, the one launch 4.04 ms. Chunks
+// that overlap run in plan order, one launch each: a chunk whose heads have no
+// result yet writes (O, lse) directly; any other chunk folds itself into them
+// through the log-sum-exp inside the attention kernel (query blocks with no
+// kept block in the shard exit without touching memory). Heads that no chunk
+// covers end as the empty result.
+#include <new>
+
 #include "sparsp_internal.h"
 
 namespace sparsp {
+namespace {
 
-hipError_t run_chunks(const Geom& g, const void* Q, const int32_t* sel, int keep,
-                      const int32_t* slot_of, const void* Kp, const void* Vp, int64_t capacity,
-                      float scale, const sparsp_chunk* plan, int n_chunks, float* O, float* lse,
-                      hipStream_t s) {
-    const int64_t rows = int64_t(g.nq) * g.block;  // accumulator rows per head
-    std::vector<bool> seen(g.H, false);             // heads whose rows hold a result
-    auto clear_head = [&](int h) {
-        return launch_fill_identity(O + int64_t(h) * rows * g.d, lse + int64_t(h) * rows, rows,
+struct Run {  // the arguments every launch of a plan shares
+    const Geom& g;
+    const void* Q;
+    const int32_t* sel;
+    int keep;
+    const int32_t* slot_of;
+    const void *Kp, *Vp;
+    int64_t capacity;
+    float scale;
+    float *O, *lse;
+    hipStream_t s;
+
+    hipError_t attend(const AttnPart& part) const {
+        return g.bf16 ? launch_attn_bf16(g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale, part, O,
+                                         false, lse, s)
+                      : launch_attn_f32(g, (const float*)Q, sel, keep, slot_of, (const float*)Kp,
+                                        (const float*)Vp, capacity, scale, part, O, lse, s);
+    }
+    hipError_t clear(int h_lo, int h_hi) const {  // the empty result for a run of heads
+        const int64_t rows = int64_t(g.nq) * g.block;
+        return launch_fill_identity(O + h_lo * rows * g.d, lse + h_lo * rows, (h_hi - h_lo) * rows,
                                     g.d, s);
-    };
+    }
+};
+
+hipError_t run_in_order(const Run& run, const sparsp_chunk* plan, int n_chunks) {
+    std::vector<bool> seen(run.g.H, false);  // heads whose rows hold a result
     for (int c = 0; c < n_chunks; ++c) {
         const sparsp_chunk& ch = plan[c];
         bool fresh = true, mixed = false;
@@ -42,20 +69,37 @@ hipError_t run_chunks(const Geom& g, const void* Q, const int32_t* sel, int keep
         hipError_t e = hipSuccess;
         if (!fresh && mixed)  // heads met for the first time start from the empty result
             for (int h = ch.head_begin; h < ch.head_end && e == hipSuccess; ++h)
-                if (!seen[h]) e = clear_head(h);
+                if (!seen[h]) e = run.clear(h, h + 1);
         if (e != hipSuccess) return e;
-        const AttnPart part{ch.kv_blk_begin, ch.kv_blk_end, ch.head_begin, ch.head_end,
-                            fresh ? 0 : 1};
-        e = g.bf16 ? launch_attn_bf16(g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale, part, O,
-                                      false, lse, s)
-                   : launch_attn_f32(g, (const float*)Q, sel, keep, slot_of, (const float*)Kp,
-                                     (const float*)Vp, capacity, scale, part, O, lse, s);
+        e = run.attend({ch.kv_blk_begin, ch.kv_blk_end, ch.head_begin, ch.head_end, fresh ? 0 : 1});
         if (e != hipSuccess) return e;
         for (int h = ch.head_begin; h < ch.head_end; ++h) seen[h] = true;
     }
-    for (int h = 0; h < g.H; ++h)  // heads no chunk covered: the empty result
+    for (int h = 0; h < run.g.H; ++h)  // heads no chunk covered: the empty result
         if (!seen[h])
-            if (hipError_t e = clear_head(h); e != hipSuccess) return e;
+            if (hipError_t e = run.clear(h, h + 1); e != hipSuccess) return e;
+    return hipSuccess;
+}
+
+}  // namespace
+
+hipError_t run_chunks(const Geom& g, const void* Q, const int32_t* sel, int keep,
+                      const int32_t* slot_of, const void* Kp, const void* Vp, int64_t capacity,
+                      float scale, const sparsp_chunk* plan, int n_chunks, float* O, float* lse,
+                      hipStream_t s) {
+    const Run run{g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale, O, lse, s};
+    try {
+        std::vector<AttnPart> launches;
+        std::vector<std::pair<int, int>> empty;
+        if (!merge_chunks(g.H, plan, n_chunks, &launches, &empty))
+            return run_in_order(run, plan, n_chunks);
+        for (const AttnPart& part : launches)
+            if (hipError_t e = run.attend(part); e != hipSuccess) return e;
+        for (const auto& heads : empty)
+            if (hipError_t e = run.clear(heads.first, heads.second); e != hipSuccess) return e;
+    } catch (const std::bad_alloc&) {  // no exception may leave the C entry
+        return hipErrorOutOfMemory;
+    }
     return hipSuccess;
 }
 

@@ -45,6 +45,41 @@ int plan_chunks(const Geom& g, const uint64_t* demand, int ranks, int rank, int 
     return int(plan.size());
 }
 
+bool merge_chunks(int H, const sparsp_chunk* plan, int n_chunks, std::vector<AttnPart>* launches,
+                  std::vector<std::pair<int, int>>* empty) {
+    typedef std::vector<std::pair<int, int>> Ranges;
+    std::vector<Ranges> of(H);
+    for (int c = 0; c < n_chunks; ++c) {
+        const sparsp_chunk& ch = plan[c];
+        if (ch.kv_blk_begin >= ch.kv_blk_end) continue;  // no block, nothing to add
+        for (int h = ch.head_begin; h < ch.head_end; ++h)
+            of[h].push_back({ch.kv_blk_begin, ch.kv_blk_end});
+    }
+    for (Ranges& r : of) {
+        std::sort(r.begin(), r.end());
+        size_t k = 0;
+        for (size_t i = 0; i < r.size(); ++i) {
+            if (k > 0 && r[i].first < r[k - 1].second) return false;
+            if (k > 0 && r[i].first == r[k - 1].second)
+                r[k - 1].second = r[i].second;
+            else
+                r[k++] = r[i];
+        }
+        r.resize(k);
+    }
+    launches->clear();
+    empty->clear();
+    for (int h0 = 0; h0 < H;) {
+        int h1 = h0 + 1;
+        while (h1 < H && of[h1] == of[h0]) ++h1;
+        if (of[h0].empty()) empty->push_back({h0, h1});
+        for (size_t i = 0; i < of[h0].size(); ++i)
+            launches->push_back(AttnPart{of[h0][i].first, of[h0][i].second, h0, h1, i > 0 ? 1 : 0});
+        h0 = h1;
+    }
+    return true;
+}
+
 void periodic_placement(int L, int block, int frame_tokens, int ranks, int32_t* perm,
                         int32_t* rank_begin) {
     const int n = (L + block - 1) / block;
