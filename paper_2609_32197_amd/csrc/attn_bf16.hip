@@ -73,6 +73,7 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx8 __attribute__((ext_vector_type(8)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
@@ -621,20 +622,57 @@ void attn_bf16_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
 // copy of block j+1 is issued once every wave has finished the scores of
 // block j, the V copy once the output product of block j is done; each copy
 // thus has half a block of compute to land.
+//
+// Products use v_mfma_f32_16x16x32_bf16. The part runs at its power limit here,
+// and this form does more work per joule than 32x32x16: with operands in
+// registers 2,031 against 1,716 TFLOP/s sustained, with this kernel's LDS reads
+// (1 KB per 32 KFLOP) 1,522 against 1,428. Layout (wave64): A lane l holds row
+// l%16, k values 8*(l/16) .. +7; B lane l column l%16, same k values; the four
+// results of lane l are column l%16, rows 4*(l/16) .. +3. A wave's 32 queries
+// are two column groups that share every A operand. The P^T operand of a 32-key
+// step is again the lane's own probabilities: tile 2t+u of the scores is fed the
+// keys 32t + 8(m/4) + 4u + m%4 as its rows m, so a lane's results of the two
+// tiles are 8 consecutive keys.
 template <int D, int BLK_>
 struct CfgRows {
     static constexpr int BLK = BLK_;
     static constexpr int NW = BLK / 32;          // one wave per 32 queries
     static constexpr int THREADS = 64 * NW;
-    static constexpr int MT = BLK / 32;          // 32-key tiles of the score product
-    static constexpr int PT = BLK / 16;          // 16-key steps of the output product
-    static constexpr int KT = D / 16;
-    static constexpr int DT = D / 32;
+    static constexpr int MT = BLK / 16;          // 16-key tiles of the score product
+    static constexpr int PT = BLK / 32;          // 32-key steps of the output product
+    static constexpr int KT = D / 32;            // k steps of the score product
+    static constexpr int DT = D / 16;            // d tiles of the output product
     static constexpr int TILE = BLK * D;
     static constexpr int CHUNKS = TILE / 8;
     static constexpr int DMA = CHUNKS / THREADS;
     static_assert(CHUNKS % THREADS == 0, "tile must split evenly");
+    static_assert(MT % 2 == 0 && DT % 2 == 0, "operands are read in two halves");
 };
+
+// XOR swizzle of a K row's 16-byte chunks for the 16 rows a quarter-wave reads
+// together, 8 i + j + const with i, j < 4: each lands on its own 16 bytes of 256.
+template <int D>
+__device__ __forceinline__ int swz_k16(int row) {
+    const int i = (row >> 3) & 3;
+    return D >= 128 ? ((row & 3) | (i << 2)) : (((row >> 1) & 1) | (i << 1));
+}
+template <int D>
+__device__ __forceinline__ int k16_src_offset(int p) {
+    constexpr int NCH = D / 8;
+    const int row = p / NCH, pc = p % NCH;
+    return (row * D + ((pc ^ swz_k16<D>(row)) * 8)) * 2;
+}
+
+// Max and sum over the four lanes l, l^16, l^32, l^48 of a query, the same in
+// all four: each swap pairs a lane's value with that of l^16, then of l^32.
+__device__ __forceinline__ float quad_max(float x) {
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return pair_max(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+}
+__device__ __forceinline__ float quad_sum(float x) {
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return pair_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+}
 
 // s_waitcnt vmcnt(n) for the n copies issued last, other counters untouched.
 template <int N>
@@ -661,7 +699,7 @@ void attn_rows_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
-    const int qi = lane & 31, g = lane >> 5;
+    const int qi = lane & 15, g = lane >> 4;
 
     const int G = n_heads * nq;
     int wg = blockIdx.x;
@@ -675,9 +713,6 @@ void attn_rows_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
         wg = tp.index;
     }
     const int h = h_lo + wg / nq, r = wg % nq;
-    const int qtok = (i0 + r) * BLK + 32 * wave + qi;
-    const bool qvalid = qtok < L;
-
     __shared__ int wave_cnt[C::NW];
     int nkeep = 0;
     {
@@ -723,7 +758,7 @@ void attn_rows_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
 #pragma unroll
     for (int u = 0; u < C::DMA; ++u) {
         const int p = (u * C::NW + wave) * 64 + lane;
-        kvoff[u] = chunk_src_offset<D>(p);
+        kvoff[u] = k16_src_offset<D>(p);
         vvoff[u] = chunk_src_offset<BLK>(p);
     }
     // (codes are wave-uniform; taking them into scalar registers keeps the
@@ -737,13 +772,18 @@ void attn_rows_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
         copy_tile<C::NW, C::DMA>(Vp + int64_t(code >> 1) * C::TILE, C::TILE * 2, lv, vvoff, wave);
     };
 
-    bf16x8 qf[C::KT];
-    {
-        const uint16_t* qp = Q + (int64_t(h) * L + (qvalid ? qtok : 0)) * D + 8 * g;
+    // Q^T operands: lane holds Q[q][32 kt + 8 g .. +7] of its query of each group.
+    bf16x8 qf[2][C::KT];
+    bool qvalid[2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+        const int qtok = (i0 + r) * BLK + 32 * wave + 16 * a + qi;
+        qvalid[a] = qtok < L;
+        const uint16_t* qp = Q + (int64_t(h) * L + (qvalid[a] ? qtok : 0)) * D + 8 * g;
 #pragma unroll
         for (int kt = 0; kt < C::KT; ++kt) {
-            uint4 v = qvalid ? *reinterpret_cast<const uint4*>(qp + 16 * kt) : make_uint4(0, 0, 0, 0);
-            qf[kt] = __builtin_bit_cast(bf16x8, v);
+            uint4 v = qvalid[a] ? *reinterpret_cast<const uint4*>(qp + 32 * kt) : make_uint4(0, 0, 0, 0);
+            qf[a][kt] = __builtin_bit_cast(bf16x8, v);
         }
     }
     // From here on nothing the compiler tracks is in flight: the Q loads are
@@ -754,13 +794,13 @@ void attn_rows_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
         copy_v(kept[0]);
     }
 
-    floatx16 oacc[C::DT];
+    floatx4 oacc[C::DT][2];
 #pragma unroll
-    for (int dt = 0; dt < C::DT; ++dt) oacc[dt] = floatx16{};
-    float m_run = -INFINITY, l_run = 0.f;
+    for (int dt = 0; dt < C::DT; ++dt) oacc[dt][0] = oacc[dt][1] = floatx4{};
+    float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
     // Set only where the max moves: lim = m_run + the rescale threshold,
     // neg_m = -m_run, or 0 while the lane has seen no finite score.
-    float lim = -INFINITY, neg_m = 0.f;
+    float lim[2] = {-INFINITY, -INFINITY}, neg_m[2] = {0.f, 0.f};
     const int last_cnt = L - (L / BLK) * BLK;
 
     // Entering block jj: K(jj) and V(jj) are in flight, K issued first.
@@ -771,36 +811,45 @@ void attn_rows_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
     for (int jj = 0; jj < nkeep; ++jj) {
         const int cur = kept[jj];
         // Scores: S^T for the wave's 32 queries over all 128 keys of the block;
-        // s[mt][rr] is key 32 mt + 16 (rr/8) + 8 g + rr%8.
-        // k step outermost, so the four accumulators advance together and no
-        // MFMA waits on the one before it; the K operands of step kt+1 are
-        // read while the four MFMAs of step kt run.
-        floatx16 s[C::MT];
+        // s[2t+u][a][r] is key 32 t + 8 g + 4 u + r of query 16 a + qi.
+        // k step outermost, four key tiles at a time, so the accumulators
+        // advance together and no MFMA waits on the one before it; the K
+        // operands of the next step are read while the eight MFMAs of this one
+        // run.
+        floatx4 s[C::MT][2];
 #pragma unroll
-        for (int mt = 0; mt < C::MT; ++mt) s[mt] = floatx16{};
-        bf16x8 kb[2][C::MT];
-        auto kread = [&](int kt, bf16x8 (&dst)[C::MT]) {
+        for (int mt = 0; mt < C::MT; ++mt) s[mt][0] = s[mt][1] = floatx4{};
+        constexpr int MH = C::MT / 2;       // key tiles per step
+        constexpr int KSTEPS = 2 * C::KT;   // step i: k step i/2, half i%2 of the tiles
+        bf16x8 kb[2][MH];
+        auto kread = [&](int i, bf16x8 (&dst)[MH]) {
 #pragma unroll
-            for (int mt = 0; mt < C::MT; ++mt) {
-                const int krow = 32 * mt + sigma(qi);
-                dst[mt] = *reinterpret_cast<const bf16x8*>(
-                    lk + krow * D + (((2 * kt + g) ^ swz<D>(krow)) * 8));
+            for (int x = 0; x < MH; ++x) {
+                const int mt = MH * (i & 1) + x;
+                const int krow = 32 * (mt >> 1) + 8 * (qi >> 2) + 4 * (mt & 1) + (qi & 3);
+                dst[x] = *reinterpret_cast<const bf16x8*>(
+                    lk + krow * D + (((4 * (i >> 1) + g) ^ swz_k16<D>(krow)) * 8));
             }
         };
         kread(0, kb[0]);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int kt = 0; kt < C::KT; ++kt) {
-            if (kt + 1 < C::KT) kread(kt + 1, kb[(kt + 1) & 1]);
+        for (int i = 0; i < KSTEPS; ++i) {
+            if (i + 1 < KSTEPS) kread(i + 1, kb[(i + 1) & 1]);
 #pragma unroll
-            for (int mt = 0; mt < C::MT; ++mt)
-                s[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kb[kt & 1][mt], qf[kt], s[mt], 0, 0, 0);
+            for (int x = 0; x < MH; ++x)
+#pragma unroll
+                for (int a = 0; a < 2; ++a) {
+                    const int mt = MH * (i & 1) + x;
+                    s[mt][a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kb[i & 1][x], qf[a][i >> 1],
+                                                                      s[mt][a], 0, 0, 0);
+                }
         }
-        // Keep that order: the reads of step kt+1 ahead of the MFMAs of step kt.
+        // Keep that order: the reads of step i+1 ahead of the MFMAs of step i.
 #pragma unroll
-        for (int kt = 0; kt < C::KT; ++kt) {
-            if (kt + 1 < C::KT) __builtin_amdgcn_sched_group_barrier(0x100, C::MT, 0);  // LDS reads
-            __builtin_amdgcn_sched_group_barrier(0x008, C::MT, 0);                      // MFMAs
+        for (int i = 0; i < KSTEPS; ++i) {
+            if (i + 1 < KSTEPS) __builtin_amdgcn_sched_group_barrier(0x100, MH, 0);  // LDS reads
+            __builtin_amdgcn_sched_group_barrier(0x008, 2 * MH, 0);                  // MFMAs
         }
         __builtin_amdgcn_sched_barrier(0);
         wait_vmem_all();   // V(jj) landed
@@ -815,132 +864,144 @@ void attn_rows_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
 #pragma unroll
             for (int mt = 0; mt < C::MT; ++mt)
 #pragma unroll
-                for (int rr = 0; rr < 16; ++rr) {
-                    const int key = 32 * mt + 16 * (rr >> 3) + 8 * g + (rr & 7);
-                    if (key >= last_cnt) s[mt][rr] = -INFINITY;
+                for (int rr = 0; rr < 4; ++rr) {
+                    const int key = 32 * (mt >> 1) + 8 * g + 4 * (mt & 1) + rr;
+                    if (key >= last_cnt) s[mt][0][rr] = s[mt][1][rr] = -INFINITY;
                 }
         }
-        float mx = -INFINITY;
+        float mx[2] = {-INFINITY, -INFINITY};
 #pragma unroll
-        for (int mt = 0; mt < C::MT; ++mt)
+        for (int a = 0; a < 2; ++a) {
 #pragma unroll
-            for (int rr = 0; rr < 16; rr += 2) mx = fmaxf(fmaxf(mx, s[mt][rr]), s[mt][rr + 1]);
-        mx = pair_max(mx) * c2;
-        const bool moved = __ballot(mx > lim) != 0;
+            for (int mt = 0; mt < C::MT; ++mt)
+#pragma unroll
+                for (int rr = 0; rr < 4; rr += 2)
+                    mx[a] = fmaxf(fmaxf(mx[a], s[mt][a][rr]), s[mt][a][rr + 1]);
+            mx[a] = quad_max(mx[a]) * c2;
+        }
+        const bool moved = __ballot(mx[0] > lim[0] || mx[1] > lim[1]) != 0;
         if (moved) {
-            const float m_new = fmaxf(m_run, mx);
-            const float alpha = (m_new == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m_run - m_new);
-            m_run = m_new;
-            l_run *= alpha;
-            lim = m_run + rescale_threshold(l_run);
-            neg_m = (m_run == -INFINITY) ? 0.f : -m_run;
 #pragma unroll
-            for (int dt = 0; dt < C::DT; ++dt) oacc[dt] *= alpha;
+            for (int a = 0; a < 2; ++a) {
+                const float m_new = fmaxf(m_run[a], mx[a]);
+                const float alpha =
+                    (m_new == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m_run[a] - m_new);
+                m_run[a] = m_new;
+                l_run[a] *= alpha;
+                lim[a] = m_run[a] + rescale_threshold(l_run[a]);
+                neg_m[a] = (m_run[a] == -INFINITY) ? 0.f : -m_run[a];
+#pragma unroll
+                for (int dt = 0; dt < C::DT; ++dt) oacc[dt][a] *= alpha;
+            }
         }
 
-        // 16-key steps; the V^T operands of step t+1 are read one step ahead.
-        // (the two partial sums start from the first two probabilities, not
-        // from 0 + p, which the compiler cannot drop)
-        float lsum[2];
-        bf16x8 vb[2][C::DT];
-        auto vread = [&](int t, bf16x8 (&dst)[C::DT]) {
+        // 32-key steps, each in two halves of the d tiles; the V^T operands of
+        // the next half are read one half ahead, and each half computes the next
+        // step's probabilities of one query group while its MFMAs run. (Groups
+        // that force two MFMAs per seven VALU instructions, or one per three or
+        // four, measured 0.4 to 1.1% slower than the compiler's own order.)
+        // (the two partial sums of a group start from its first two
+        // probabilities, not from 0 + p, which the compiler cannot drop)
+        float lsum[2][2];
+        constexpr int DH = C::DT / 2;
+        constexpr int VSTEPS = 2 * C::PT;
+        bf16x8 vb[2][DH];
+        auto vread = [&](int i, bf16x8 (&dst)[DH]) {
 #pragma unroll
-            for (int dt = 0; dt < C::DT; ++dt) {
-                const int vrow = 32 * dt + qi;
-                dst[dt] = *reinterpret_cast<const bf16x8*>(
-                    lv + vrow * BLK + (((2 * t + g) ^ swz<BLK>(vrow)) * 8));
+            for (int x = 0; x < DH; ++x) {
+                const int vrow = 16 * (DH * (i & 1) + x) + qi;
+                dst[x] = *reinterpret_cast<const bf16x8*>(
+                    lv + vrow * BLK + (((4 * (i >> 1) + g) ^ swz<BLK>(vrow)) * 8));
             }
         };
-        // Step t+1's probabilities are computed while step t's MFMAs run: the
-        // scheduling groups interleave each MFMA with about seven VALU
-        // instructions of the next step.
-        auto pstep = [&](int t) -> bf16x8 {
-            const int mt = t >> 1, hf = t & 1;
+        auto pstep = [&](int t, int a) -> bf16x8 {
             floatx8 p;
 #pragma unroll
             for (int v = 0; v < 8; ++v) {
-                p[v] = __builtin_amdgcn_exp2f(fmaf(s[mt][8 * hf + v], c2, neg_m));
+                p[v] = __builtin_amdgcn_exp2f(fmaf(s[2 * t + (v >> 2)][a][v & 3], c2, neg_m[a]));
                 if (t == 0 && v < 2)
-                    lsum[v] = p[v];
+                    lsum[a][v] = p[v];
                 else
-                    lsum[v & 1] += p[v];
+                    lsum[a][v & 1] += p[v];
             }
             return __builtin_convertvector(p, bf16x8);
         };
         vread(0, vb[0]);
-        bf16x8 pbn = pstep(0);
+        bf16x8 pb[2], pbn[2];
+        pbn[0] = pstep(0, 0);
+        pbn[1] = pstep(0, 1);
 #pragma unroll
-        for (int t = 0; t < C::PT; ++t) {
-            if (t + 1 < C::PT) vread(t + 1, vb[(t + 1) & 1]);
+        for (int i = 0; i < VSTEPS; ++i) {
+            const int t = i >> 1, hf = i & 1;
+            if (i + 1 < VSTEPS) vread(i + 1, vb[(i + 1) & 1]);
             __builtin_amdgcn_sched_barrier(0);
-            const bf16x8 pb = pbn;
-            if (t + 1 < C::PT) pbn = pstep(t + 1);
-#pragma unroll
-            for (int dt = 0; dt < C::DT; ++dt)
-                oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vb[t & 1][dt], pb, oacc[dt], 0, 0, 0);
-            if (t + 1 < C::PT) {
-#pragma unroll
-                for (int k = 0; k < C::DT; ++k) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);
-                }
+            if (hf == 0) {
+                pb[0] = pbn[0];
+                pb[1] = pbn[1];
             }
+            if (t + 1 < C::PT) pbn[hf] = pstep(t + 1, hf);
+#pragma unroll
+            for (int x = 0; x < DH; ++x)
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+                    oacc[DH * hf + x][a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        vb[hf][x], pb[a], oacc[DH * hf + x][a], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         }
         __builtin_amdgcn_s_setprio(0);
-        l_run += lsum[0] + lsum[1];
+#pragma unroll
+        for (int a = 0; a < 2; ++a) l_run[a] += lsum[a][0] + lsum[a][1];
 
         wait_vmem_all();   // K(jj+1) landed
         __syncthreads();   // K(jj+1) visible; every wave is done with V(jj)
         if (jj + 1 < nkeep) copy_v(kept[jj + 1]);
     }
 
-    const float l_tot = pair_sum(l_run);
-    const bool live = qvalid && l_tot > 0.f;
-    const float inv = live ? 1.0f / l_tot : 0.f;
-    const int64_t orow = int64_t(h) * nq * BLK + int64_t(r) * BLK + 32 * wave + qi;
-    float lse_out = live ? (m_run + __log2f(l_tot)) * kLn2 : -INFINITY;
-    if (tp.piece >= 0) {  // a piece of a split tail row: float32 partial into the workspace
-        const int64_t prow = int64_t(blockIdx.x - tail_first) * BLK + 32 * wave + qi;
 #pragma unroll
-        for (int dt = 0; dt < C::DT; ++dt)
+    for (int a = 0; a < 2; ++a) {
+        const float l_tot = quad_sum(l_run[a]);
+        const bool live = qvalid[a] && l_tot > 0.f;
+        const float inv = live ? 1.0f / l_tot : 0.f;
+        const int q = 32 * wave + 16 * a + qi;  // query of the block
+        const int64_t orow = int64_t(h) * nq * BLK + int64_t(r) * BLK + q;
+        float lse_out = live ? (m_run[a] + __log2f(l_tot)) * kLn2 : -INFINITY;
+        if (tp.piece >= 0) {  // a piece of a split tail row: float32 partial into the workspace
+            const int64_t prow = int64_t(blockIdx.x - tail_first) * BLK + q;
 #pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
+            for (int dt = 0; dt < C::DT; ++dt) {
                 float4 o;
-                o.x = live ? oacc[dt][4 * q4] * inv : 0.f;
-                o.y = live ? oacc[dt][4 * q4 + 1] * inv : 0.f;
-                o.z = live ? oacc[dt][4 * q4 + 2] * inv : 0.f;
-                o.w = live ? oacc[dt][4 * q4 + 3] * inv : 0.f;
-                *reinterpret_cast<float4*>(part_o + prow * D + 32 * dt + 8 * q4 + 4 * g) = o;
+                o.x = live ? oacc[dt][a][0] * inv : 0.f;
+                o.y = live ? oacc[dt][a][1] * inv : 0.f;
+                o.z = live ? oacc[dt][a][2] * inv : 0.f;
+                o.w = live ? oacc[dt][a][3] * inv : 0.f;
+                *reinterpret_cast<float4*>(part_o + prow * D + 16 * dt + 4 * g) = o;
             }
-        if (g == 0) part_lse[prow] = lse_out;
-        return;
-    }
-    float ka = 0.f, kb = 1.f;
-    bool store = true;
-    if (!OUT_BF16 && acc) {
-        store = live;
-        if (live) {
-            const float la2 = lse[orow] * kLog2e;
-            const float lb2 = m_run + __log2f(l_tot);
-            const float mm = fmaxf(la2, lb2);
-            const float wa = (la2 == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(la2 - mm);
-            const float wb = __builtin_amdgcn_exp2f(lb2 - mm);
-            const float t = wa + wb;
-            ka = wa / t;
-            kb = wb / t;
-            lse_out = (mm + __log2f(t)) * kLn2;
+            if (g == 0) part_lse[prow] = lse_out;
+            continue;
         }
-    }
+        float ka = 0.f, kb = 1.f;
+        bool store = true;
+        if (!OUT_BF16 && acc) {
+            store = live;
+            if (live) {
+                const float la2 = lse[orow] * kLog2e;
+                const float lb2 = m_run[a] + __log2f(l_tot);
+                const float mm = fmaxf(la2, lb2);
+                const float wa = (la2 == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(la2 - mm);
+                const float wb = __builtin_amdgcn_exp2f(lb2 - mm);
+                const float t = wa + wb;
+                ka = wa / t;
+                kb = wb / t;
+                lse_out = (mm + __log2f(t)) * kLn2;
+            }
+        }
+        if (!store) continue;
 #pragma unroll
-    for (int dt = 0; dt < C::DT; ++dt) {
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-            const int d0 = 32 * dt + 8 * q4 + 4 * g;
+        for (int dt = 0; dt < C::DT; ++dt) {
+            const int d0 = 16 * dt + 4 * g;
             float o4[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) o4[u] = live ? oacc[dt][4 * q4 + u] * inv : 0.f;
-            if (!store) continue;
+            for (int u = 0; u < 4; ++u) o4[u] = live ? oacc[dt][a][u] * inv : 0.f;
             if constexpr (OUT_BF16) {
                 uint16_t* op = static_cast<uint16_t*>(O) + orow * D + d0;
                 uint2 w;
@@ -959,8 +1020,8 @@ void attn_rows_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
                 *reinterpret_cast<float4*>(op) = make_float4(o4[0], o4[1], o4[2], o4[3]);
             }
         }
+        if (lse && g == 0) lse[orow] = lse_out;
     }
-    if (lse && g == 0 && store) lse[orow] = lse_out;
 }
 
 constexpr int kMaxTailSplit = 4;  // pieces per split tail row, at most

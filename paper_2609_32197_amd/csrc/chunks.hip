@@ -19,7 +19,7 @@
 // no block is counted twice, and a whole schedule of plan_chunks becomes one
 // launch over all heads and blocks. One launch per chunk leaves the GPU to the
 // longest row of each of a few heads: 40 heads x 147 rows, 591 blocks of 128,
-// 89 kept, four owners, 31 chunks took 6.78 ms, the one launch 4.04 ms. Chunks
+// 89 kept, four owners, 31 chunks took 6.78 ms, the one launch 3.86 ms. Chunks
 // that overlap run in plan order, one launch each: a chunk whose heads have no
 // result yet writes (O, lse) directly; any other chunk folds itself into them
 // through the log-sum-exp inside the attention kernel (query blocks with no
