@@ -8,9 +8,13 @@
 // Q's local blocks and all of K's blocks go through one launch. The step is
 // HBM-bound.
 //
-// score_kernel: per head, scores = pooled_q · pooled_k^T · d^-1/2 as a tiled
-// float32 product (64x64 output tile per workgroup, 4x4 per thread, d staged
-// through LDS in slices of 32). It is about 1 GFLOP at the largest workload.
+// score_kernel: per head, scores = pooled_q · pooled_k^T · d^-1/2 in float32 on
+// the matrix cores (v_mfma_f32_16x16x4_f32): a 64x64 output tile per workgroup,
+// 32x32 per wave, d staged through LDS in slices of 32. About 1 GFLOP and 30 MB
+// at the largest workload, so latency bounds it more than the 8 us of its
+// products: 40 heads x 147 x 591 blocks, d = 128 36.6 us with float32 FMAs on
+// transposed LDS tiles, 25.6 with slices of 64 (34 KB of LDS: a second round of
+// workgroups), 22.2 as it is; 48 x 139 x 278, d = 64 18.1 and 11.0 us.
 #include "sparsp_internal.h"
 
 namespace sparsp {
@@ -103,58 +107,90 @@ __global__ __launch_bounds__(kPoolThreads) void pool_kernel(
 
 constexpr int kTile = 64;   // output tile edge
 constexpr int kSlice = 32;  // d slice staged per step
+constexpr int kPitch = kSlice + 4;  // floats per LDS row: 16 rows start on 16 different banks of 16 bytes
 
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+// VEC: the pooled tiles are 16-byte aligned (their rows then are too, d being a
+// multiple of 4).
+template <bool VEC>
+__device__ __forceinline__ floatx4 load4(const float* p) {
+    if constexpr (VEC) return *reinterpret_cast<const floatx4*>(p);
+    return floatx4{p[0], p[1], p[2], p[3]};
+}
+
+template <bool VEC>
 __global__ __launch_bounds__(256) void score_kernel(const float* __restrict__ pq,
                                                      const float* __restrict__ pk,
                                                      float* __restrict__ scores, int nq, int n,
                                                      int d, float scale) {
-    // Tiles stored d-major so each thread reads 4 consecutive rows as a float4.
-    // One float4 of padding per row spreads the transposing stores over the banks.
-    __shared__ float4 As[kSlice][kTile / 4 + 1];
-    __shared__ float4 Bs[kSlice][kTile / 4 + 1];
+    __shared__ __attribute__((aligned(16))) float As[kTile * kPitch];
+    __shared__ __attribute__((aligned(16))) float Bs[kTile * kPitch];
     const int h = blockIdx.z;
     const int row0 = blockIdx.y * kTile;  // query blocks
     const int col0 = blockIdx.x * kTile;  // key blocks
-    const int tid = threadIdx.x;
-    const int tr = tid / 16, tc = tid % 16;  // 16x16 threads, 4x4 outputs each
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int qi = lane & 15, g = lane >> 4;
+    const int wr = 32 * (wave >> 1), wc = 32 * (wave & 1);  // this wave's 32x32 outputs
     const float* A = pq + int64_t(h) * nq * d;
     const float* B = pk + int64_t(h) * n * d;
 
-    float acc[4][4] = {};
+    // A slice is 64 rows of 8 float4 per operand, two of each per thread; the
+    // next slice is read while this one is multiplied.
+    floatx4 xa[2], xb[2];
+    const int r4 = tid >> 3, c4 = (tid & 7) * 4;
+    auto fetch = [&](int k0) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int ra = row0 + r4 + 32 * i, rb = col0 + r4 + 32 * i, k = k0 + c4;
+            xa[i] = (ra < nq && k < d) ? load4<VEC>(A + int64_t(ra) * d + k) : floatx4{};
+            xb[i] = (rb < n && k < d) ? load4<VEC>(B + int64_t(rb) * d + k) : floatx4{};
+        }
+    };
+    floatx4 acc[2][2] = {};
+    fetch(0);
     for (int k0 = 0; k0 < d; k0 += kSlice) {
-        // Load 64 rows x 32 columns of each operand: 2048 floats, 8 per thread.
-        for (int e = tid; e < kTile * kSlice; e += 256) {
-            const int r = e / kSlice, c = e % kSlice;
-            const int ra = row0 + r, rb = col0 + r, k = k0 + c;
-            const float a = (ra < nq && k < d) ? A[int64_t(ra) * d + k] : 0.f;
-            const float b = (rb < n && k < d) ? B[int64_t(rb) * d + k] : 0.f;
-            reinterpret_cast<float*>(&As[c][0])[r] = a;
-            reinterpret_cast<float*>(&Bs[c][0])[r] = b;
+        if (k0 > 0) __syncthreads();  // every wave is done with the slice before
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            *reinterpret_cast<floatx4*>(&As[(r4 + 32 * i) * kPitch + c4]) = xa[i];
+            *reinterpret_cast<floatx4*>(&Bs[(r4 + 32 * i) * kPitch + c4]) = xb[i];
         }
         __syncthreads();
-#pragma unroll 8
-        for (int c = 0; c < kSlice; ++c) {
-            const float4 a = As[c][tr];
-            const float4 b = Bs[c][tc];
-            const float av[4] = {a.x, a.y, a.z, a.w};
-            const float bv[4] = {b.x, b.y, b.z, b.w};
+        if (k0 + kSlice < d) fetch(k0 + kSlice);
+        // Lane group g supplies elements 16 c + 4 g + u of both operands in
+        // product u of chunk c.
 #pragma unroll
-            for (int x = 0; x < 4; ++x)
+        for (int c = 0; c < kSlice / 16; ++c) {
+            floatx4 a[2], b[2];
 #pragma unroll
-                for (int y = 0; y < 4; ++y) acc[x][y] = fmaf(av[x], bv[y], acc[x][y]);
-        }
-        __syncthreads();
-    }
+            for (int x = 0; x < 2; ++x) {
+                a[x] = *reinterpret_cast<const floatx4*>(&As[(wr + 16 * x + qi) * kPitch + 16 * c + 4 * g]);
+                b[x] = *reinterpret_cast<const floatx4*>(&Bs[(wc + 16 * x + qi) * kPitch + 16 * c + 4 * g]);
+            }
 #pragma unroll
-    for (int x = 0; x < 4; ++x) {
-        const int i = row0 + tr * 4 + x;
-        if (i >= nq) continue;
+            for (int u = 0; u < 4; ++u)
 #pragma unroll
-        for (int y = 0; y < 4; ++y) {
-            const int j = col0 + tc * 4 + y;
-            if (j < n) scores[(int64_t(h) * nq + i) * n + j] = acc[x][y] * scale;
+                for (int x = 0; x < 2; ++x)
+#pragma unroll
+                    for (int y = 0; y < 2; ++y)
+                        acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[x][u], b[y][u], acc[x][y],
+                                                                         0, 0, 0);
         }
     }
+    // The lane holds rows 4 g .. +3 of column qi of each 16x16 tile.
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = row0 + wr + 16 * x + 4 * g + r;
+            if (i >= nq) continue;
+#pragma unroll
+            for (int y = 0; y < 2; ++y) {
+                const int j = col0 + wc + 16 * y + qi;
+                if (j < n) scores[(int64_t(h) * nq + i) * n + j] = acc[x][y][r] * scale;
+            }
+        }
 }
 
 }  // namespace
@@ -173,7 +209,9 @@ hipError_t launch_pool_scores(const Geom& g, const void* Q, const void* K, float
     if (e != hipSuccess) return e;
     dim3 sgrid((g.n + kTile - 1) / kTile, (g.nq + kTile - 1) / kTile, g.H);
     const float scale = 1.0f / sqrtf(float(g.d));
-    score_kernel<<<sgrid, 256, 0, s>>>(pooled_q, pooled_k, scores, g.nq, g.n, g.d, scale);
+    const bool vec = ((reinterpret_cast<uintptr_t>(pooled_q) | reinterpret_cast<uintptr_t>(pooled_k)) & 15) == 0;
+    auto* score = vec ? score_kernel<true> : score_kernel<false>;
+    score<<<sgrid, 256, 0, s>>>(pooled_q, pooled_k, scores, g.nq, g.n, g.d, scale);
     return hipGetLastError();
 }
 
