@@ -266,7 +266,7 @@ int sparsp_block_sparse_attn_balanced_noalloc(const sparsp_geom* g, const void* 
  *     count in unspecified order);
  *   - the queues are interleaved round-robin: entry k of queue x is at
  *     position x + 8k while every queue is longer than k.
- * Device pointers; one workgroup on `stream`.
+ * Device pointers; one small kernel on `stream`.
  */
 int sparsp_row_order(const sparsp_geom* g, const int32_t* counts, int32_t* order, void* stream);
 

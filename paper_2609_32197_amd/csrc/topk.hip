@@ -9,7 +9,11 @@
 // Selection is exact and order-free. Scores become order-preserving 32-bit
 // keys (-0.0 folded onto +0.0). A 32-step bitwise search finds T, the k-th
 // largest candidate key (k = keep - |F|): at each bit it keeps the bit set if
-// at least k candidates still reach the threshold.
+// at least k candidates still reach the threshold, and it stops as soon as
+// exactly k do, which on scores of one scale is after about half the bits. The
+// search is instruction bound, S compares and counts per bit: S is the row's own
+// number of mask words up to 16. 5,880 rows of 591 blocks: 36.8 us with the next
+// power of two and all 32 bits, 20.5 us; 6,672 rows of 278: 20.4 and 10.9 us.
 // Candidates above T are taken; among those equal to T the lowest indices are
 // taken until k is reached, ranked in index order with ballots and
 // mbcnt. No floating point is involved, so the result is a pure function of
@@ -45,7 +49,7 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ sco
     const int i = i0 + r;  // global index of this query block: the forced diagonal
 
     const float* srow = scores + int64_t(row) * n;
-    uint32_t key[S];
+    uint32_t key[S], pick[S];  // pick: 0 for what is no candidate (a key of 0 is a NaN's)
     bool cand[S], forced[S];
 #pragma unroll
     for (int s = 0; s < S; ++s) {
@@ -55,6 +59,7 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ sco
         forced[s] = f;
         cand[s] = valid && !f;
         key[s] = valid ? order_key(srow[j]) : 0u;
+        pick[s] = cand[s] ? key[s] : 0u;
     }
     const bool diag_in_g = (gs.w[i >> 6] >> (i & 63)) & 1;
     const int n_forced = gs.count + (diag_in_g ? 0 : 1);
@@ -67,8 +72,10 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ sco
             const uint32_t t = T | (1u << b);
             int cnt = 0;
 #pragma unroll
-            for (int s = 0; s < S; ++s) cnt += popc64(__ballot(cand[s] && key[s] >= t));
+            for (int s = 0; s < S; ++s) cnt += popc64(__ballot(pick[s] >= t));  // t >= 1
             if (cnt >= k) T = t;
+            // Exactly k reach t: they are the choice, whatever bits would follow.
+            if (cnt == k) break;
         }
         int gt = 0;
 #pragma unroll
@@ -109,13 +116,31 @@ hipError_t launch_s(const Geom& g, const float* scores, int keep, const GlobalSe
 // differ in its last bits from lane to lane (each lane adds in its own
 // order), so lane 0's result is broadcast. Every decision below therefore is
 // uniform across the wave.
-__device__ __forceinline__ float wave_sum(float x) {
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+//
+// Butterfly step `off` without the LDS round trip of a shuffle: lane swaps for 32
+// and 16, and row rotations for 8, 4, 2, 1 (after the step of 2 off the values
+// repeat every 2 off lanes, so the lane off further on holds what the lane
+// across does). Both operands of a sum meet as in the shuffle form, bit for bit.
+template <typename F>
+__device__ __forceinline__ float wave_fold(float x, F f) {
+    auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = f(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = f(__uint_as_float(b[0]), __uint_as_float(b[1]));
+#define SPARSP_ROW_ROR(n) \
+    x = f(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + n, 0xf, 0xf, false)))
+    SPARSP_ROW_ROR(8);
+    SPARSP_ROW_ROR(4);
+    SPARSP_ROW_ROR(2);
+    SPARSP_ROW_ROR(1);
+#undef SPARSP_ROW_ROR
     return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
 }
+__device__ __forceinline__ float wave_sum(float x) {
+    return wave_fold(x, [](float a, float b) { return a + b; });
+}
 __device__ __forceinline__ float wave_max(float x) {
-    for (int off = 32; off > 0; off >>= 1) x = fmaxf(x, __shfl_xor(x, off, 64));
-    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
+    return wave_fold(x, [](float a, float b) { return fmaxf(a, b); });
 }
 
 // CDF-mode selection (Section 8.1), one wave per (head, local row), blocks held
@@ -130,7 +155,9 @@ __device__ __forceinline__ float wave_max(float x) {
 // indices are left out while the budget allows. tau = 1 keeps every block
 // (every block's mass is positive, even where float32 exp underflows). The
 // diagonal and global blocks are kept in any case. sel rows list the kept
-// blocks ascending, then -1 up to n. Scores must be finite.
+// blocks ascending, then -1 up to n. Scores must be finite. Each bit costs a
+// wave-wide sum: 5,880 rows of 591 blocks took 44.9 us with shuffles through LDS
+// and S the next power of two, 30.5 us as it is.
 template <int S>
 __global__ __launch_bounds__(256) void cdf_kernel(const float* __restrict__ scores, int H, int nq,
                                                   int n, int W, int i0, float tau, GlobalSet gs,
@@ -225,21 +252,23 @@ hipError_t launch_cdf_s(const Geom& g, const float* scores, float tau, const Glo
 }
 
 // Row order for rows of unequal kept counts (CDF selection), for a launch
-// whose workgroup w runs on XCD w mod 8. One workgroup:
+// whose workgroup w runs on XCD w mod 8. Eight workgroups, one per queue; each
+// repeats steps 1 and 2, which is cheaper than handing their result on:
 //   1. totals per head; heads ranked by total (descending, then by index);
 //   2. heads dealt to the eight XCD queues largest first, each to the least
 //      loaded queue that still has room (H/8 heads per queue, the first H mod 8
 //      queues one more), so every head's rows share one XCD's L2 and the
 //      queues carry nearly equal work;
-//   3. each queue's rows sorted by count, largest first (counting sort; rows
-//      of equal count in unspecified order);
-//   4. the queues interleaved: entry k of queue x goes to the position that a
+//   3. workgroup x sorts queue x's rows by count, largest first (counting sort;
+//      rows of equal count in unspecified order);
+//   4. the queues are interleaved: entry k of queue x goes to the position that a
 //      round-robin walk over the queues gives it, i.e. x + 8k while all
 //      queues are that long.
 // A count outside [0, n] is clamped into it. Up to kCountCache rows the
-// counts are read from memory once and kept in LDS, where one thread per head
+// counts are read from memory once and kept in LDS, where one wave per head
 // sums its total; past that, all rows add into the totals with LDS atomics.
-// Each queue's pass walks only the rows of its own heads.
+// 40 x 147 rows: 45.1 us as one workgroup that dealt by shuffles and sorted the
+// queues one after another, 17.7 us.
 constexpr int kXcds = 8;
 constexpr int kCountCache = 14336;  // rows whose counts are kept in LDS (16 bits each)
 static_assert(kMaxBlocks < 65536, "counts must fit 16 bits");
@@ -286,18 +315,19 @@ __global__ __launch_bounds__(1024) void row_order_kernel(const int32_t* __restri
     const bool cached = rows <= kCountCache;
     auto cnt_at = [&](int row) { return cached ? int(cnt_s[row]) : cnt_of(row); };
 
-    // 1. totals per head, heads ranked by total. With the counts in LDS a
-    // thread sums its head's rows there; otherwise all rows are added in
+    // 1. totals per head, heads ranked by total. With the counts in LDS a wave
+    // sums a head's rows there; otherwise all rows are added in
     // parallel (LDS atomics).
     for (int h = tid; h < H; h += 1024) tot[h] = 0;
     if (cached)
         for (int r = tid; r < rows; r += 1024) cnt_s[r] = uint16_t(cnt_of(r));
     __syncthreads();
     if (cached) {
-        for (int h = tid; h < H; h += 1024) {
-            unsigned long long t = 0;
-            for (int r = 0; r < nq; ++r) t += cnt_s[h * nq + r];
-            tot[h] = t;
+        for (int h = tid >> 6; h < H; h += 16) {  // one wave per head; the sum fits 31 bits
+            int t = 0;
+            for (int r = tid & 63; r < nq; r += 64) t += cnt_s[h * nq + r];
+            for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+            if ((tid & 63) == 0) tot[h] = (unsigned long long)t;
         }
     } else {
         for (int r = tid; r < rows; r += 1024) atomicAdd(&tot[r / nq], (unsigned long long)cnt_of(r));
@@ -316,34 +346,39 @@ __global__ __launch_bounds__(1024) void row_order_kernel(const int32_t* __restri
     __syncthreads();
     // 2. heads dealt to the queues in rank order, each to the least loaded
     // queue with room (the lowest such queue on a tie); each queue's heads are
-    // listed together. One wave: lane x < 8 holds queue x's load and room,
-    // and a shuffle argmin over lanes 0..7 picks the queue for each head.
+    // listed together. One wave: lane x < 8 holds queue x's load and room. The
+    // smallest (load, queue) is found as the minimum of load * 8 + x over the
+    // eight lanes (a load is at most 1024 * 4096 * 4096, so the key fits; a full
+    // queue's is the largest), by three steps of lane permutes.
     if (tid < 64) {
-        const int lane = tid;
+        const int lane = tid & 7;  // eight copies of the eight queues
         unsigned long long load = 0;
-        int room = lane < kXcds ? H / kXcds + (lane < H % kXcds ? 1 : 0) : 0;
-        int fill = lane < kXcds ? q_first[lane] : 0;
+        int room = H / kXcds + (lane < H % kXcds ? 1 : 0);
+        int fill = q_first[lane];
+        unsigned long long t = H > 0 ? tot[head_at[0]] : 0;
         for (int k = 0; k < H; ++k) {
             const int h = head_at[k];
-            const unsigned long long t = tot[h];
-            unsigned long long key = (lane < kXcds && room > 0) ? load : ~0ull;
-            int arg = lane;
-#pragma unroll
-            for (int off = 1; off < kXcds; off <<= 1) {
-                const uint32_t lo = __shfl_xor(uint32_t(key), off, 64);
-                const uint32_t hi = __shfl_xor(uint32_t(key >> 32), off, 64);
-                const int oa = __shfl_xor(arg, off, 64);
-                const unsigned long long ok = (uint64_t(hi) << 32) | lo;
-                if (ok < key || (ok == key && oa < arg)) {
-                    key = ok;
-                    arg = oa;
-                }
-            }
-            if (lane < kXcds && lane == arg) {
-                q_heads[fill++] = h;
+            const unsigned long long t_next = k + 1 < H ? tot[head_at[k + 1]] : 0;
+            const unsigned long long mine = room > 0 ? load * 8 + lane : ~0ull;
+            unsigned long long key = mine;
+#define SPARSP_MIN_STEP(ctrl)                                                                    \
+    {                                                                                            \
+        const uint32_t lo = __builtin_amdgcn_update_dpp(0, int(uint32_t(key)), ctrl, 0xf, 0xf, false); \
+        const uint32_t hi = __builtin_amdgcn_update_dpp(0, int(key >> 32), ctrl, 0xf, 0xf, false); \
+        const unsigned long long o = (uint64_t(hi) << 32) | lo;                                  \
+        key = o < key ? o : key;                                                                 \
+    }
+            SPARSP_MIN_STEP(0xB1)   // lane ^ 1
+            SPARSP_MIN_STEP(0x4E)   // lane ^ 2
+            SPARSP_MIN_STEP(0x141)  // 7 - lane: the other four
+#undef SPARSP_MIN_STEP
+            if (key == mine) {
+                if (tid < kXcds) q_heads[fill] = h;
+                ++fill;
                 load += t;
                 --room;
             }
+            t = t_next;
         }
     }
     __syncthreads();
@@ -351,41 +386,39 @@ __global__ __launch_bounds__(1024) void row_order_kernel(const int32_t* __restri
 #pragma unroll
     for (int x = 0; x < kXcds; ++x) ql[x] = (q_first[x + 1] - q_first[x]) * nq;
 
-    // 3. per queue: counting sort of its rows by count, largest first, and
+    // 3. counting sort of this workgroup's queue by count, largest first, and
     // placement at the queue's round-robin positions
     const int per = (n + 1 + 1023) / 1024;
-    for (int x = 0; x < kXcds; ++x) {
-        if (ql[x] == 0) continue;
-        const int* qh = q_heads + q_first[x];
-        for (int c = tid; c <= n; c += 1024) start[c] = 0;
-        __syncthreads();
-        for (int i = tid; i < ql[x]; i += 1024) atomicAdd(&start[cnt_at(qh[i / nq] * nq + i % nq)], 1);
-        __syncthreads();
-        // exclusive scan over the count values n, n-1, ..., 0
-        int local = 0;
-        for (int k = 0; k < per; ++k) {
-            const int idx = tid * per + k;
-            if (idx <= n) local += start[n - idx];
+    const int x = blockIdx.x;
+    if (ql[x] == 0) return;  // the whole workgroup
+    const int* qh = q_heads + q_first[x];
+    for (int c = tid; c <= n; c += 1024) start[c] = 0;
+    __syncthreads();
+    for (int i = tid; i < ql[x]; i += 1024) atomicAdd(&start[cnt_at(qh[i / nq] * nq + i % nq)], 1);
+    __syncthreads();
+    // exclusive scan over the count values n, n-1, ..., 0
+    int local = 0;
+    for (int k = 0; k < per; ++k) {
+        const int idx = tid * per + k;
+        if (idx <= n) local += start[n - idx];
+    }
+    int run = block_exclusive_scan(local, wave_sums);
+    for (int k = 0; k < per; ++k) {
+        const int idx = tid * per + k;
+        if (idx <= n) {
+            const int c = start[n - idx];
+            start[n - idx] = run;
+            run += c;
         }
-        int run = block_exclusive_scan(local, wave_sums);
-        for (int k = 0; k < per; ++k) {
-            const int idx = tid * per + k;
-            if (idx <= n) {
-                const int c = start[n - idx];
-                start[n - idx] = run;
-                run += c;
-            }
-        }
-        __syncthreads();
-        for (int i = tid; i < ql[x]; i += 1024) {
-            const int r = qh[i / nq] * nq + i % nq;
-            const int k = atomicAdd(&start[cnt_at(r)], 1);  // place in queue x
-            int pos = 0;  // round-robin position of entry k of queue x
+    }
+    __syncthreads();
+    for (int i = tid; i < ql[x]; i += 1024) {
+        const int r = qh[i / nq] * nq + i % nq;
+        const int k = atomicAdd(&start[cnt_at(r)], 1);  // place in queue x
+        int pos = 0;  // round-robin position of entry k of queue x
 #pragma unroll
-            for (int y = 0; y < kXcds; ++y) pos += min(k, ql[y]) + (y < x && ql[y] > k ? 1 : 0);
-            order[pos] = r;
-        }
-        __syncthreads();
+        for (int y = 0; y < kXcds; ++y) pos += min(k, ql[y]) + (y < x && ql[y] > k ? 1 : 0);
+        order[pos] = r;
     }
 }
 
@@ -394,31 +427,31 @@ __global__ __launch_bounds__(1024) void row_order_kernel(const int32_t* __restri
 hipError_t launch_cdf(const Geom& g, const float* scores, float tau, const GlobalSet& gs,
                       uint64_t* mask, int32_t* sel, int32_t* counts, hipStream_t st) {
     (void)hipGetLastError();
-    if (g.W <= 1) return launch_cdf_s<1>(g, scores, tau, gs, mask, sel, counts, st);
-    if (g.W <= 2) return launch_cdf_s<2>(g, scores, tau, gs, mask, sel, counts, st);
-    if (g.W <= 4) return launch_cdf_s<4>(g, scores, tau, gs, mask, sel, counts, st);
-    if (g.W <= 8) return launch_cdf_s<8>(g, scores, tau, gs, mask, sel, counts, st);
-    if (g.W <= 16) return launch_cdf_s<16>(g, scores, tau, gs, mask, sel, counts, st);
-    if (g.W <= 32) return launch_cdf_s<32>(g, scores, tau, gs, mask, sel, counts, st);
+#define SPARSP_W(S) if (g.W <= S) return launch_cdf_s<S>(g, scores, tau, gs, mask, sel, counts, st)
+    SPARSP_W(1); SPARSP_W(2); SPARSP_W(3); SPARSP_W(4); SPARSP_W(5); SPARSP_W(6);
+    SPARSP_W(7); SPARSP_W(8); SPARSP_W(9); SPARSP_W(10); SPARSP_W(11); SPARSP_W(12);
+    SPARSP_W(13); SPARSP_W(14); SPARSP_W(15); SPARSP_W(16); SPARSP_W(24); SPARSP_W(32);
+    SPARSP_W(48);
+#undef SPARSP_W
     return launch_cdf_s<64>(g, scores, tau, gs, mask, sel, counts, st);
 }
 
 hipError_t launch_topk(const Geom& g, const float* scores, int keep, const GlobalSet& gs,
                        uint64_t* mask, int32_t* sel, hipStream_t st) {
     (void)hipGetLastError();
-    if (g.W <= 1) return launch_s<1>(g, scores, keep, gs, mask, sel, st);
-    if (g.W <= 2) return launch_s<2>(g, scores, keep, gs, mask, sel, st);
-    if (g.W <= 4) return launch_s<4>(g, scores, keep, gs, mask, sel, st);
-    if (g.W <= 8) return launch_s<8>(g, scores, keep, gs, mask, sel, st);
-    if (g.W <= 16) return launch_s<16>(g, scores, keep, gs, mask, sel, st);
-    if (g.W <= 32) return launch_s<32>(g, scores, keep, gs, mask, sel, st);
+#define SPARSP_W(S) if (g.W <= S) return launch_s<S>(g, scores, keep, gs, mask, sel, st)
+    SPARSP_W(1); SPARSP_W(2); SPARSP_W(3); SPARSP_W(4); SPARSP_W(5); SPARSP_W(6);
+    SPARSP_W(7); SPARSP_W(8); SPARSP_W(9); SPARSP_W(10); SPARSP_W(11); SPARSP_W(12);
+    SPARSP_W(13); SPARSP_W(14); SPARSP_W(15); SPARSP_W(16); SPARSP_W(24); SPARSP_W(32);
+    SPARSP_W(48);
+#undef SPARSP_W
     return launch_s<64>(g, scores, keep, gs, mask, sel, st);
 }
 
 hipError_t launch_row_order(const int32_t* counts, int H, int nq, int n, int32_t* order,
                             hipStream_t st) {
     (void)hipGetLastError();
-    row_order_kernel<<<1, 1024, 0, st>>>(counts, H, nq, n, order);
+    row_order_kernel<<<kXcds, 1024, 0, st>>>(counts, H, nq, n, order);
     return hipGetLastError();
 }
 
