@@ -78,6 +78,7 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kRescaleThreshold = 8.0f;  // log2 units
+constexpr int kCus = 256;                  // of an MI355X
 
 // The rescale threshold for a lane that has accumulated mass l (units of its
 // running max): moving the max pays off once a block's top probability would
@@ -681,7 +682,9 @@ __device__ __forceinline__ void wait_vmem_keep() {
     __builtin_amdgcn_s_waitcnt(0x0F70 | N);
 }
 
-template <int D, int BLK, bool OUT_BF16>
+// ORDERED: an explicit row order is given (an instance of its own, so that the
+// others carry no test of it in their loop).
+template <int D, int BLK, bool OUT_BF16, bool ORDERED>
 __global__ __launch_bounds__(64 * (BLK / 32)) __attribute__((amdgpu_waves_per_eu(2)))
 void attn_rows_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict__ sel,
                     const int32_t* __restrict__ slot_of, const uint16_t* __restrict__ Kp,
@@ -701,10 +704,17 @@ void attn_rows_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
     const int lane = tid & 63, wave = tid >> 6;
     const int qi = lane & 15, g = lane >> 4;
 
+    // Longest-first launches end with their longest rows when nothing speeds those
+    // up: a row of several hundred blocks takes the whole launch on half a CU.
+    // The first round's rows therefore keep a priority above the later rows they
+    // share a CU with (40 x 147 rows of 1 to 278 blocks, CDF tau 0.9: 1.271 ms
+    // without, 1.208 with; 128 or 256 rows instead of the whole round 1.212 and
+    // 1.218).
+    const bool first_round = ORDERED && blockIdx.x < 2 * kCus;
     const int G = n_heads * nq;
     int wg = blockIdx.x;
     const TailPiece tp = tail_piece(wg, tail_first, tail_k);
-    if (order) {  // an explicit row order (e.g. longest first); no XCD remap
+    if constexpr (ORDERED) {  // e.g. longest first; no XCD remap
         wg = order[blockIdx.x];
         if (wg < 0 || wg >= G) return;
     } else if (remap) {
@@ -808,6 +818,7 @@ void attn_rows_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
         wait_vmem_keep<C::DMA>();  // K(0) landed (V(0) may still be in flight)
         __syncthreads();
     }
+    if (first_round) __builtin_amdgcn_s_setprio(2);
     for (int jj = 0; jj < nkeep; ++jj) {
         const int cur = kept[jj];
         // Scores: S^T for the wave's 32 queries over all 128 keys of the block;
@@ -859,7 +870,10 @@ void attn_rows_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
         // Softmax and output product at raised priority: where the other wave
         // on the SIMD is in its score MFMAs, this wave's VALU work issues first
         // and the matrix pipe stays fed by both.
-        __builtin_amdgcn_s_setprio(1);
+        if (first_round)
+            __builtin_amdgcn_s_setprio(3);
+        else
+            __builtin_amdgcn_s_setprio(1);
         if (cur & 1) {
 #pragma unroll
             for (int mt = 0; mt < C::MT; ++mt)
@@ -948,7 +962,10 @@ void attn_rows_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
                         vb[hf][x], pb[a], oacc[DH * hf + x][a], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_s_setprio(0);
+        if (first_round)
+            __builtin_amdgcn_s_setprio(2);
+        else
+            __builtin_amdgcn_s_setprio(0);
 #pragma unroll
         for (int a = 0; a < 2; ++a) l_run[a] += lsum[a][0] + lsum[a][1];
 
@@ -1182,22 +1199,20 @@ hipError_t launch_rows(const Geom& g, const void* Q, const int32_t* sel, int kee
     constexpr int THREADS = CfgRows<D, BLK>::THREADS;
     TailPlan tp;
     void* partials = nullptr;
-    if (hipError_t e = balanced_plan(attn_rows_kernel<D, BLK, true>, THREADS, dyn, g, part, sel,
+    if (hipError_t e = balanced_plan(attn_rows_kernel<D, BLK, true, false>, THREADS, dyn, g, part, sel,
                                      keep, G, int64_t(BLK) * (D + 1) * 4, s, &tp, &partials);
         e != hipSuccess)
         return e;
     const TailSpace ts = tp.k > 1 ? tail_space(partials, tp, G, D, BLK) : TailSpace{nullptr, nullptr};
     const int grid = tp.first + (G - tp.first) * tp.k;
-    if (out_bf16)
-        attn_rows_kernel<D, BLK, true><<<grid, THREADS, dyn, s>>>(
-            (const uint16_t*)Q, sel, slot_of, (const uint16_t*)Kp, (const uint16_t*)Vp, O, lse,
-            g.L, g.n, g.i0, g.nq, keep, cap, c2, part.kv_lo, part.kv_hi, part.h_lo, n_heads,
-            part.acc, 1, part.order, tp.first, tp.k, ts.part_o, ts.part_lse, tp.row_sort);
-    else
-        attn_rows_kernel<D, BLK, false><<<grid, THREADS, dyn, s>>>(
-            (const uint16_t*)Q, sel, slot_of, (const uint16_t*)Kp, (const uint16_t*)Vp, O, lse,
-            g.L, g.n, g.i0, g.nq, keep, cap, c2, part.kv_lo, part.kv_hi, part.h_lo, n_heads,
-            part.acc, 1, part.order, tp.first, tp.k, ts.part_o, ts.part_lse, tp.row_sort);
+    auto* kern = part.order ? (out_bf16 ? attn_rows_kernel<D, BLK, true, true>
+                                        : attn_rows_kernel<D, BLK, false, true>)
+                            : (out_bf16 ? attn_rows_kernel<D, BLK, true, false>
+                                        : attn_rows_kernel<D, BLK, false, false>);
+    kern<<<grid, THREADS, dyn, s>>>(
+        (const uint16_t*)Q, sel, slot_of, (const uint16_t*)Kp, (const uint16_t*)Vp, O, lse, g.L, g.n,
+        g.i0, g.nq, keep, cap, c2, part.kv_lo, part.kv_hi, part.h_lo, n_heads, part.acc, 1,
+        part.order, tp.first, tp.k, ts.part_o, ts.part_lse, tp.row_sort);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || tp.k < 2) return e;
     return out_bf16 ? launch_tail_merge<D, BLK, true>(g, part, tp, G, ts.part_o, ts.part_lse, O, lse, s)
@@ -1267,9 +1282,9 @@ int64_t attn_tail_workspace_bytes(const Geom& g, int keep) {
     const size_t dyn = size_t(keep) * sizeof(int32_t);
     int slots = 0;
     if (g.d == 128 && g.block == 128)
-        slots = resident_slots(attn_rows_kernel<128, 128, true>, CfgRows<128, 128>::THREADS, dyn);
+        slots = resident_slots(attn_rows_kernel<128, 128, true, false>, CfgRows<128, 128>::THREADS, dyn);
     else if (g.d == 64 && g.block == 128)
-        slots = resident_slots(attn_rows_kernel<64, 128, true>, CfgRows<64, 128>::THREADS, dyn);
+        slots = resident_slots(attn_rows_kernel<64, 128, true, false>, CfgRows<64, 128>::THREADS, dyn);
     else if (g.d == 64 && g.block == 64)
         slots = resident_slots(attn_bf16_kernel<64, 64, true>, Cfg<64, 64>::THREADS, dyn);
     else if (g.d == 128 && g.block == 64)
