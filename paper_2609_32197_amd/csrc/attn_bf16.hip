@@ -2,8 +2,8 @@
 // the packed K/V buffers (Eq. 1 over the kept blocks; softmax renormalised
 // over the kept keys, computed online in float32).
 //
-// Two kernels, one workgroup per (head, local query block) in both; the
-// block size picks the kernel.
+// Three kernels, one workgroup per (head, local query block) in all; the shape
+// and the number of rows pick the kernel.
 //
 // attn_rows_kernel (128-token blocks): four waves, wave w owns queries
 // 32 w .. +31 against all 128 keys of every kept block; single K and V tile
@@ -22,7 +22,10 @@
 // of block jj+1 is issued right after the barrier that opens block jj and has
 // the whole of block jj's compute to land. One barrier per block.
 //
-// Data movement (both). The kept blocks' K tile ([BLK, D]) and transposed V
+// attn_wave_kernel (64-token blocks at d = 64, many rows): one wave per row,
+// all 64 queries against all keys, tiles of its own, no barrier.
+//
+// Data movement (all). The kept blocks' K tile ([BLK, D]) and transposed V
 // tile ([D, BLK]) are copied HBM -> LDS with direct-to-LDS buffer loads
 // (buffer_load_dwordx4 ... lds); each wave waits for its own copies before the
 // barrier that publishes them. The split-key kernel reads all MFMA operands
@@ -35,7 +38,8 @@
 // query block): neighbouring query blocks select overlapping KV blocks, which
 // then hit in that XCD's L2.
 //
-// Products use v_mfma_f32_32x32x16_bf16 with the score tile computed
+// Products use v_mfma_f32_32x32x16_bf16 (the rows kernel 16x16x32, laid out as
+// stated there) with the score tile computed
 // transposed, S^T = K Q^T (A = K from LDS, B = Q^T from registers):
 //   * each lane holds one query column (q = lane % 32) and 16 keys per 32x32
 //     tile, so the row max and row sum are in-lane except for one exchange
@@ -1041,6 +1045,300 @@ void attn_rows_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
     }
 }
 
+// Kernel for 64-token blocks at d = 64 in large launches: one wave per row, a
+// workgroup of its own. The wave owns all 64 queries against all keys of every
+// kept block, stages K and V^T tiles (8 KB apiece) for itself and waits for its
+// own copies by count: there is no barrier and no merge. K of the next block is
+// copied while the softmax and output product of this one run, V while the next
+// scores run. Every operand read feeds two MFMAs, half the LDS traffic of the
+// split-key kernel, and the work per block spreads over four times its scores.
+// Eight rows are in flight per CU, so a launch needs many rows of like length
+// (the rule stands at use_wave_kernel).
+template <int D>
+struct CfgWave {
+    static constexpr int BLK = 64;
+    static constexpr int KT = D / 16;            // k steps of the score product
+    static constexpr int DT = D / 32;            // d tiles of the output product
+    static constexpr int TILE = BLK * D;
+    static constexpr int DMA = TILE / 8 / 64;    // copies per lane per tile
+    static_assert(D == 64, "one copy pattern serves the K and the V^T tile");
+};
+
+template <int D, bool OUT_BF16>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
+void attn_wave_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict__ sel,
+                      const int32_t* __restrict__ slot_of, const uint16_t* __restrict__ Kp,
+                      const uint16_t* __restrict__ Vp, void* __restrict__ O,
+                      float* __restrict__ lse, int L, int n, int i0, int nq, int keep,
+                      int64_t capacity, float c2 /* scale * log2(e) */, int G, int tail_first,
+                      int tail_k, float* __restrict__ part_o,
+                      float* __restrict__ part_lse, const int32_t* __restrict__ row_sort,
+                      const int32_t* __restrict__ order) {
+    using C = CfgWave<D>;
+    constexpr int BLK = C::BLK;
+    __shared__ __attribute__((aligned(16))) uint16_t lk[C::TILE];
+    __shared__ __attribute__((aligned(16))) uint16_t lv[C::TILE];
+    extern __shared__ int32_t codes[];
+
+    const int lane = threadIdx.x;
+    const int qi = lane & 31, g = lane >> 5;
+
+    const TailPiece tp = tail_piece(blockIdx.x, tail_first, tail_k);
+    int row;
+    if (order) {  // an explicit row order; no XCD remap
+        row = order[blockIdx.x];
+        if (row < 0 || row >= G) return;
+    } else {
+        row = sorted_row(xcd_row(tp.index, G), nq, row_sort);
+    }
+    const int h = row / nq, r = row % nq;
+
+    // The kept list: usable entries compacted in list order, four per lane and
+    // round so that a round's loads overlap.
+    int nkeep = 0;
+    {
+        const int32_t* srow = sel + int64_t(row) * keep;
+        const int32_t* hslot = slot_of + int64_t(h) * n;
+        const bool ragged = (L % BLK) != 0;
+        for (int base = 0; base < keep; base += 256) {
+            int code[4], j[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int jj = base + u * 64 + lane;
+                j[u] = jj < keep ? srow[jj] : -1;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int sl = (j[u] >= 0 && j[u] < n) ? hslot[j[u]] : -1;
+                code[u] = (sl >= 0 && sl < capacity && sl < (1 << 30))
+                              ? 2 * sl + ((ragged && j[u] == n - 1) ? 1 : 0)
+                              : -1;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint64_t bal = __ballot(code[u] >= 0);
+                const int below = __builtin_amdgcn_mbcnt_hi(
+                    uint32_t(bal >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(bal), 0));
+                if (code[u] >= 0) codes[nkeep + below] = code[u];
+                nkeep += __popcll(bal);
+            }
+        }
+        __syncthreads();  // (one wave: orders the list's writes before its reads)
+    }
+    const int32_t* kept = codes;  // this workgroup's kept list
+    if (tp.piece >= 0) {          // its share of a split tail row
+        const int e0 = tp.piece * nkeep / tail_k, e1 = (tp.piece + 1) * nkeep / tail_k;
+        kept = codes + e0;
+        nkeep = e1 - e0;
+    }
+
+    int voff[C::DMA];
+#pragma unroll
+    for (int u = 0; u < C::DMA; ++u) voff[u] = chunk_src_offset<D>(u * 64 + lane);
+    auto copy_k = [&](int code) {
+        copy_tile<1, C::DMA>(Kp + int64_t(code >> 1) * C::TILE, C::TILE * 2, lk, voff, 0);
+    };
+    auto copy_v = [&](int code) {
+        copy_tile<1, C::DMA>(Vp + int64_t(code >> 1) * C::TILE, C::TILE * 2, lv, voff, 0);
+    };
+
+    // Q^T operands: lane holds Q[q][16 kt + 8 g .. +7] of its query of each group.
+    bf16x8 qf[2][C::KT];
+    bool qvalid[2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+        const int qtok = (i0 + r) * BLK + 32 * a + qi;
+        qvalid[a] = qtok < L;
+        const uint16_t* qp = Q + (int64_t(h) * L + (qvalid[a] ? qtok : 0)) * D + 8 * g;
+#pragma unroll
+        for (int kt = 0; kt < C::KT; ++kt) {
+            uint4 v = qvalid[a] ? *reinterpret_cast<const uint4*>(qp + 16 * kt) : make_uint4(0, 0, 0, 0);
+            qf[a][kt] = __builtin_bit_cast(bf16x8, v);
+        }
+    }
+
+    floatx16 oacc[C::DT][2];
+#pragma unroll
+    for (int dt = 0; dt < C::DT; ++dt) oacc[dt][0] = oacc[dt][1] = floatx16{};
+    float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
+    // Set only where the max moves: lim = m_run + the rescale threshold,
+    // neg_m = -m_run, or 0 while the lane has seen no finite score.
+    float lim[2] = {-INFINITY, -INFINITY}, neg_m[2] = {0.f, 0.f};
+    const int last_cnt = L - (L / BLK) * BLK;
+
+    // From here on only the copies are in flight (see copy_tile).
+    wait_vmem_all();
+    int code = 0;
+    if (nkeep > 0) {
+        code = __builtin_amdgcn_readfirstlane(kept[0]);
+        copy_k(code);
+    }
+    for (int jj = 0; jj < nkeep; ++jj) {
+        const int cur = code;
+        copy_v(cur);
+        // (the last block's K is read again rather than none, so that the count
+        // of copies in flight is the same in every iteration)
+        const int next = kept[jj + 1 < nkeep ? jj + 1 : jj];
+        wait_vmem_keep<C::DMA>();  // K landed; V may still be in flight
+        __builtin_amdgcn_sched_barrier(0);
+        // Scores: s[mt][a][rr] is key 32 mt + 16 (rr/8) + 8 g + rr%8 of query
+        // 32 a + qi.
+        floatx16 s[2][2];
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) s[mt][0] = s[mt][1] = floatx16{};
+        bf16x8 kb[2][2];
+        auto kread = [&](int kt, bf16x8 (&dst)[2]) {
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt) {
+                const int krow = 32 * mt + sigma(qi);
+                dst[mt] = *reinterpret_cast<const bf16x8*>(
+                    lk + krow * D + (((2 * kt + g) ^ swz<D>(krow)) * 8));
+            }
+        };
+        kread(0, kb[0]);
+#pragma unroll
+        for (int kt = 0; kt < C::KT; ++kt) {
+            if (kt + 1 < C::KT) kread(kt + 1, kb[(kt + 1) & 1]);
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+                    s[mt][a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kb[kt & 1][mt], qf[a][kt],
+                                                                      s[mt][a], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        code = __builtin_amdgcn_readfirstlane(next);
+        copy_k(code);
+        __builtin_amdgcn_sched_barrier(0);
+
+        __builtin_amdgcn_s_setprio(1);
+        if (cur & 1) {  // partial last block: keys past L do not exist
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                for (int rr = 0; rr < 16; ++rr) {
+                    const int key = 32 * mt + 16 * (rr >> 3) + 8 * g + (rr & 7);
+                    if (key >= last_cnt) s[mt][0][rr] = s[mt][1][rr] = -INFINITY;
+                }
+        }
+        float mx[2] = {-INFINITY, -INFINITY};
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                for (int rr = 0; rr < 16; rr += 2)
+                    mx[a] = fmaxf(fmaxf(mx[a], s[mt][a][rr]), s[mt][a][rr + 1]);
+            mx[a] = pair_max(mx[a]) * c2;
+        }
+        const bool moved = __ballot(mx[0] > lim[0] || mx[1] > lim[1]) != 0;
+        if (moved) {
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+                const float m_new = fmaxf(m_run[a], mx[a]);
+                const float alpha =
+                    (m_new == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m_run[a] - m_new);
+                m_run[a] = m_new;
+                l_run[a] *= alpha;
+                lim[a] = m_run[a] + rescale_threshold(l_run[a]);
+                neg_m[a] = (m_run[a] == -INFINITY) ? 0.f : -m_run[a];
+#pragma unroll
+                for (int dt = 0; dt < C::DT; ++dt) oacc[dt][a] *= alpha;
+            }
+        }
+        wait_vmem_keep<C::DMA>();  // V landed; the next K may still be in flight
+        __builtin_amdgcn_sched_barrier(0);
+        // Output product by 16-key steps; the probabilities of step t+1 are
+        // computed while the MFMAs of step t run.
+        float lsum[2][2];
+        bf16x8 vb[2][C::DT];
+        auto vread = [&](int t, bf16x8 (&dst)[C::DT]) {
+#pragma unroll
+            for (int dt = 0; dt < C::DT; ++dt) {
+                const int vrow = 32 * dt + qi;
+                dst[dt] = *reinterpret_cast<const bf16x8*>(
+                    lv + vrow * BLK + (((2 * t + g) ^ swz<BLK>(vrow)) * 8));
+            }
+        };
+        auto pstep = [&](int t, int a) -> bf16x8 {
+            floatx8 p;
+#pragma unroll
+            for (int v = 0; v < 8; ++v) {
+                p[v] = __builtin_amdgcn_exp2f(fmaf(s[t >> 1][a][8 * (t & 1) + v], c2, neg_m[a]));
+                if (t == 0 && v < 2)
+                    lsum[a][v] = p[v];
+                else
+                    lsum[a][v & 1] += p[v];
+            }
+            return __builtin_convertvector(p, bf16x8);
+        };
+        vread(0, vb[0]);
+        bf16x8 pbn[2];
+        pbn[0] = pstep(0, 0);
+        pbn[1] = pstep(0, 1);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            if (t + 1 < 4) vread(t + 1, vb[(t + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+            const bf16x8 pb[2] = {pbn[0], pbn[1]};
+            if (t + 1 < 4) {
+                pbn[0] = pstep(t + 1, 0);
+                pbn[1] = pstep(t + 1, 1);
+            }
+#pragma unroll
+            for (int dt = 0; dt < C::DT; ++dt)
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+                    oacc[dt][a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vb[t & 1][dt], pb[a],
+                                                                         oacc[dt][a], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        __builtin_amdgcn_s_setprio(0);
+#pragma unroll
+        for (int a = 0; a < 2; ++a) l_run[a] += lsum[a][0] + lsum[a][1];
+    }
+    wait_vmem_all();  // no copy may land after the wave has gone
+
+    const int64_t orow0 = int64_t(row) * BLK;
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+        const float l_tot = pair_sum(l_run[a]);
+        const bool live = qvalid[a] && l_tot > 0.f;
+        const float inv = live ? 1.0f / l_tot : 0.f;
+        const int q = 32 * a + qi;
+        const float lse_out = live ? (m_run[a] + __log2f(l_tot)) * kLn2 : -INFINITY;
+        const int64_t prow = int64_t(blockIdx.x - tail_first) * BLK + q;  // row of a piece's partials
+#pragma unroll
+        for (int dt = 0; dt < C::DT; ++dt) {
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                float o4[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) o4[u] = live ? oacc[dt][a][4 * q4 + u] * inv : 0.f;
+                const int d0 = 32 * dt + 8 * q4 + 4 * g;
+                if (tp.piece >= 0) {  // a piece of a split tail row: float32 partial
+                    *reinterpret_cast<float4*>(part_o + prow * D + d0) =
+                        make_float4(o4[0], o4[1], o4[2], o4[3]);
+                } else if constexpr (OUT_BF16) {
+                    uint2 w;
+                    w.x = f32_to_bf16_bits(o4[0]) | (f32_to_bf16_bits(o4[1]) << 16);
+                    w.y = f32_to_bf16_bits(o4[2]) | (f32_to_bf16_bits(o4[3]) << 16);
+                    *reinterpret_cast<uint2*>(static_cast<uint16_t*>(O) + (orow0 + q) * D + d0) = w;
+                } else {
+                    *reinterpret_cast<float4*>(static_cast<float*>(O) + (orow0 + q) * D + d0) =
+                        make_float4(o4[0], o4[1], o4[2], o4[3]);
+                }
+            }
+        }
+        if (g == 0) {
+            if (tp.piece >= 0)
+                part_lse[prow] = lse_out;
+            else if (lse)
+                lse[orow0 + q] = lse_out;
+        }
+    }
+}
+
 constexpr int kMaxTailSplit = 4;  // pieces per split tail row, at most
 
 // Merge of the pieces of the split tail rows. Piece p of tail row t sits in
@@ -1256,6 +1554,56 @@ hipError_t launch_shape(const Geom& g, const void* Q, const int32_t* sel, int ke
                     : launch_tail_merge<D, BLK, false>(g, part, tp, G, ts.part_o, ts.part_lse, O, lse, s);
 }
 
+// Where the one-wave-per-row kernel serves 64 x 64 blocks instead of the split-key
+// kernel, which has four waves on a row. The launch must
+//   - fill the chip with single waves: 2,048 rows are in flight. Attention alone,
+//     split-key / one wave (us): 1,000 rows of 12 kept blocks 25.8 / 27.0, 1,300
+//     of 60 107 / 123, 1,812 of 60 158 / 143, 2,500 of 60 187 / 181, 6,672 of 14
+//     163 / 151, of 139 1,144 / 1,109;
+//   - have rows of like length, as far as the host can tell (a row of several
+//     times the mean would end the launch alone, four times as late): whole rows
+//     over all blocks, with a top-k width (keep < n; a CDF list is n wide and
+//     padded). An explicit row order or a workspace does not enter, so that they
+//     leave a row's arithmetic as it is;
+//   - leave room for eight kept lists beside the tiles of a CU's rows (160 KB).
+// Past 900,000 rows the split-key kernel's smaller tail split keeps the workspace
+// inside the library's fixed array.
+constexpr int kWaveRowsMin = 1800, kWaveRowsMax = 900000, kWaveKeepMax = 896;
+bool use_wave_kernel(const Geom& g, int keep, int G) {
+    return g.d == 64 && g.block == 64 && G >= kWaveRowsMin && G <= kWaveRowsMax &&
+           keep < g.n && keep <= kWaveKeepMax;
+}
+bool whole_rows(const Geom& g, const AttnPart& p) {
+    return !p.acc && p.kv_lo == 0 && p.kv_hi == g.n && p.h_lo == 0 && p.h_hi == g.H;
+}
+
+template <int D>
+hipError_t launch_wave(const Geom& g, const void* Q, const int32_t* sel, int keep,
+                       const int32_t* slot_of, const void* Kp, const void* Vp, int64_t cap,
+                       float scale, const AttnPart& part, void* O, bool out_bf16, float* lse,
+                       hipStream_t s) {
+    constexpr int BLK = 64;
+    const int G = g.H * g.nq;
+    const float c2 = scale * kLog2e;
+    const size_t dyn = size_t(keep) * sizeof(int32_t);
+    TailPlan tp;
+    void* partials = nullptr;
+    if (hipError_t e = balanced_plan(attn_wave_kernel<D, true>, 64, dyn, g, part, sel, keep, G,
+                                     int64_t(BLK) * (D + 1) * 4, s, &tp, &partials);
+        e != hipSuccess)
+        return e;
+    const TailSpace ts = tp.k > 1 ? tail_space(partials, tp, G, D, BLK) : TailSpace{nullptr, nullptr};
+    const int grid = tp.first + (G - tp.first) * tp.k;
+    auto* kern = out_bf16 ? attn_wave_kernel<D, true> : attn_wave_kernel<D, false>;
+    kern<<<grid, 64, dyn, s>>>((const uint16_t*)Q, sel, slot_of, (const uint16_t*)Kp,
+                               (const uint16_t*)Vp, O, lse, g.L, g.n, g.i0, g.nq, keep, cap, c2, G,
+                               tp.first, tp.k, ts.part_o, ts.part_lse, tp.row_sort, part.order);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || tp.k < 2) return e;
+    return out_bf16 ? launch_tail_merge<D, BLK, true>(g, part, tp, G, ts.part_o, ts.part_lse, O, lse, s)
+                    : launch_tail_merge<D, BLK, false>(g, part, tp, G, ts.part_o, ts.part_lse, O, lse, s);
+}
+
 }  // namespace
 
 hipError_t launch_attn_bf16(const Geom& g, const void* Q, const int32_t* sel, int keep,
@@ -1269,6 +1617,9 @@ hipError_t launch_attn_bf16(const Geom& g, const void* Q, const int32_t* sel, in
     if (g.d == 64 && g.block == 128)
         return launch_rows<64, 128>(g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale, part, O,
                              out_bf16, lse, s);
+    if (whole_rows(g, part) && use_wave_kernel(g, keep, g.H * g.nq))
+        return launch_wave<64>(g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale, part, O,
+                               out_bf16, lse, s);
     if (g.d == 64 && g.block == 64)
         return launch_shape<64, 64>(g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale, part, O,
                                     out_bf16, lse, s);
@@ -1285,6 +1636,8 @@ int64_t attn_tail_workspace_bytes(const Geom& g, int keep) {
         slots = resident_slots(attn_rows_kernel<128, 128, true, false>, CfgRows<128, 128>::THREADS, dyn);
     else if (g.d == 64 && g.block == 128)
         slots = resident_slots(attn_rows_kernel<64, 128, true, false>, CfgRows<64, 128>::THREADS, dyn);
+    else if (use_wave_kernel(g, keep, g.H * g.nq))
+        slots = resident_slots(attn_wave_kernel<64, true>, 64, dyn);
     else if (g.d == 64 && g.block == 64)
         slots = resident_slots(attn_bf16_kernel<64, 64, true>, Cfg<64, 64>::THREADS, dyn);
     else if (g.d == 128 && g.block == 64)

@@ -1,0 +1,63 @@
+"""The one-wave-per-row attention kernel (64-token blocks, d = 64, 1,800 rows or
+more, top-k width below n): rows at the threshold and past a round of resident
+waves (tail split by the workspace), ragged ends, one to several hundred kept
+blocks, lists with skipped entries, float32 and bf16 output, an explicit row order.
+The rows just below the threshold run the split-key kernel and serve as a check of
+the rule's other side. Bars: the parity suite's (bf16 2e-2 / 1e-3, lse 1e-4).
+"""
+
+import numpy as np
+import pytest
+
+import oracle as orc
+import paper_2609_32197_amd as sp
+from tests import _parity as P
+from tests.test_gpu_kernels import _pipeline, _rand_inputs, ctypes_scale
+
+pytestmark = pytest.mark.gpu
+
+# (H, L, i0, i1), keep, rows checked per head
+CASES = [
+    ((47, 2500, 2, 40), 3, 6),       # 1,786 rows: split-key side of the rule
+    ((48, 2433, 1, 39), 1, 38),      # 1,824 rows, last block one key, diagonal only
+    ((90, 1600, 0, 25), 24, 3),      # 2,250 rows: 202 past a round of 2,048
+    ((8, 16500, 20, 258), 257, 3),   # 1,904 rows of 257 kept blocks, two load rounds
+]
+
+
+@pytest.mark.parametrize("geo,keep,check", CASES, ids=lambda x: str(x).replace(" ", ""))
+def test_wave_kernel(gpu, geo, keep, check):
+    torch = P.torch()
+    H, L, i0, i1 = geo
+    d = b = 64
+    q, k, v = _rand_inputs(61, H, L, d, "bf16")
+    g = P.geometry(H, L, d, b, i0, i1, "bf16")
+    om, osel, sel, out = _pipeline(q, k, v, g, "bf16", keep)
+    sel = sel.clone()
+    rows = np.linspace(0, g.nq - 1, check).astype(int)
+    if keep > 4:  # entries to be skipped: out of range, and a block without a slot
+        for r in rows:
+            sel[:, r, 1] = -1
+            sel[:, r, keep // 2] = g.n
+        for h in range(H):
+            for r in rows:
+                om[h, r, osel[h, r, 1]] = False
+                om[h, r, osel[h, r, keep // 2]] = False
+    args = (g, P.to_device(q, "bf16"), sel, out["slot_of"], out["K_packed"], out["V_packed"],
+            ctypes_scale(d))
+    ws = torch.empty((sp.sparsp_attn_workspace_bytes(g, keep),), dtype=torch.uint8, device="cuda")
+    plain = sp.sparsp_block_sparse_attn(*args, out_dtype=sp.F32)
+    low = sp.sparsp_block_sparse_attn(*args, out_dtype=sp.BF16, workspace=ws)
+    order = torch.from_numpy(np.random.default_rng(1).permutation(H * g.nq).astype(np.int32)).cuda()
+    ordered = sp.sparsp_block_sparse_attn(*args, out_dtype=sp.F32, row_order=order)
+    assert torch.equal(plain[0], ordered[0]) and torch.equal(plain[1], ordered[1])
+    outs = [(o.float().cpu().numpy(), l.cpu().numpy()) for o, l in (plain, low)]
+    for h in sorted({0, H // 2, H - 1}):
+        f = [orc.decode_input(x[h], "bf16") for x in (q, k, v)]
+        for r in rows:
+            o_ref, l_ref = orc.attend_block(*f, om[h, r], i0 + r, L, b, ctypes_scale(d))
+            for o, l in outs:
+                P.check_attention(o[h, r * b:(r + 1) * b], o_ref, True, f"{geo} h={h} r={r}")
+                fin, lg = np.isfinite(l_ref), l[h, r * b:(r + 1) * b]
+                assert (np.isneginf(lg) == ~fin).all()
+                assert np.abs(lg[fin] - l_ref[fin]).max(initial=0) <= 1e-4
