@@ -5,7 +5,8 @@
 // Three kernels, one workgroup per (head, local query block) in all; the shape
 // and the number of rows pick the kernel.
 //
-// attn_rows_kernel (128-token blocks): four waves, wave w owns queries
+// attn_rows_kernel (128-token blocks, and 64-token blocks with enough rows of
+// like length; the figures here are for 128): four waves, wave w owns queries
 // 32 w .. +31 against all 128 keys of every kept block; single K and V tile
 // buffers (64 KB of LDS at d = 128), two workgroups per CU. The waves that
 // share a SIMD come from different workgroups and are not tied by a barrier,
@@ -22,7 +23,7 @@
 // of block jj+1 is issued right after the barrier that opens block jj and has
 // the whole of block jj's compute to land. One barrier per block.
 //
-// attn_wave_kernel (64-token blocks at d = 64, many rows): one wave per row,
+// attn_wave_kernel (64-token blocks at d = 64, 1,800 rows or more): one wave per row,
 // all 64 queries against all keys, tiles of its own, no barrier.
 //
 // Data movement (all). The kept blocks' K tile ([BLK, D]) and transposed V
@@ -618,8 +619,8 @@ void attn_bf16_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
     if (lse && g == 0 && store) lse[orow] = lse_out;
 }
 
-// Kernel for 128-token blocks: two independent workgroups per CU. Four waves
-// per workgroup, wave w owning queries 32 w .. +31 and every key of each kept
+// Kernel for 128-token blocks (and, with two waves, 64-token ones): two
+// independent workgroups per CU. Four waves per workgroup, wave w owning queries 32 w .. +31 and every key of each kept
 // block, so each wave runs one online softmax and no merge is needed; single
 // K and V tile buffers (64 KB of LDS at d = 128). The two waves that share a
 // SIMD belong to different workgroups and are not held in step by a common
@@ -1053,7 +1054,7 @@ void attn_rows_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
 // scores run. Every operand read feeds two MFMAs, half the LDS traffic of the
 // split-key kernel, and the work per block spreads over four times its scores.
 // Eight rows are in flight per CU, so a launch needs many rows of like length
-// (the rule stands at use_wave_kernel).
+// (the rule stands at kernel64).
 template <int D>
 struct CfgWave {
     static constexpr int BLK = 64;
@@ -1554,24 +1555,36 @@ hipError_t launch_shape(const Geom& g, const void* Q, const int32_t* sel, int ke
                     : launch_tail_merge<D, BLK, false>(g, part, tp, G, ts.part_o, ts.part_lse, O, lse, s);
 }
 
-// Where the one-wave-per-row kernel serves 64 x 64 blocks instead of the split-key
-// kernel, which has four waves on a row. The launch must
-//   - fill the chip with single waves: 2,048 rows are in flight. Attention alone,
-//     split-key / one wave (us): 1,000 rows of 12 kept blocks 25.8 / 27.0, 1,300
-//     of 60 107 / 123, 1,812 of 60 158 / 143, 2,500 of 60 187 / 181, 6,672 of 14
-//     163 / 151, of 139 1,144 / 1,109;
-//   - have rows of like length, as far as the host can tell (a row of several
-//     times the mean would end the launch alone, four times as late): whole rows
-//     over all blocks, with a top-k width (keep < n; a CDF list is n wide and
-//     padded). An explicit row order or a workspace does not enter, so that they
-//     leave a row's arithmetic as it is;
-//   - leave room for eight kept lists beside the tiles of a CU's rows (160 KB).
+// The kernel for 64-token blocks. The split-key kernel has four waves on a row and
+// double-buffered tiles (d = 128: 512 rows in flight, d = 64: 1,024); the rows
+// kernel two waves and single buffers (1,024 and 1,536), the wave kernel one wave
+// (2,048 at d = 64). Fewer waves a row do less work around each score and each
+// operand, but take a row longer, so they need rows that
+//   - fill the chip. Attention alone, split-key / rows / wave kernel (us):
+//       d = 128, rows x kept blocks: 500 x 60 90 / 96; 600 x 12 40 / 30, x 60
+//       104 / 97; 750 x 60 122 / 104; 1,050 x 60 159 / 150; 2,500 x 12 98 / 87,
+//       x 60 352 / 326; 6,672 x 60 974 / 829: the rows kernel past the split-key
+//       kernel's round of 512;
+//       d = 64: 675 x 60 65 / 74; 825 x 60 81 / 78; 1,000 x 60 85 / 81; 1,050 x 60
+//       92 / 102 (the split-key kernel's round of 1,024 and a few rows that its
+//       tail split spreads); 1,300 x 60 107 / 106 / 123; 1,500 x 60 130 / 115;
+//       1,812 x 60 158 / - / 143; 2,500 x 60 187 / - / 181; 6,672 x 14 163 / - /
+//       151, x 139 1,144 / - / 1,109;
+//   - are of like length, as far as the host can tell (a row of several times the
+//     mean would end the launch alone, that much later): whole rows over all
+//     blocks, with a top-k width (keep < n; a CDF list is n wide and padded). An
+//     explicit row order or a workspace does not enter, so that they leave a row's
+//     arithmetic as it is;
+//   - (wave kernel) leave room for eight kept lists beside the tiles of a CU's
+//     rows (160 KB).
 // Past 900,000 rows the split-key kernel's smaller tail split keeps the workspace
 // inside the library's fixed array.
-constexpr int kWaveRowsMin = 1800, kWaveRowsMax = 900000, kWaveKeepMax = 896;
-bool use_wave_kernel(const Geom& g, int keep, int G) {
-    return g.d == 64 && g.block == 64 && G >= kWaveRowsMin && G <= kWaveRowsMax &&
-           keep < g.n && keep <= kWaveKeepMax;
+enum class Kernel64 { kSplitKey, kRows, kWave };
+Kernel64 kernel64(const Geom& g, int keep, int G) {
+    if (keep >= g.n || G > 900000) return Kernel64::kSplitKey;
+    if (g.d == 128) return G > 512 ? Kernel64::kRows : Kernel64::kSplitKey;
+    if (G >= 1800 && keep <= 896) return Kernel64::kWave;
+    return G >= 800 && (G <= 1024 || G >= 1200) ? Kernel64::kRows : Kernel64::kSplitKey;
 }
 bool whole_rows(const Geom& g, const AttnPart& p) {
     return !p.acc && p.kv_lo == 0 && p.kv_hi == g.n && p.h_lo == 0 && p.h_hi == g.H;
@@ -1617,15 +1630,22 @@ hipError_t launch_attn_bf16(const Geom& g, const void* Q, const int32_t* sel, in
     if (g.d == 64 && g.block == 128)
         return launch_rows<64, 128>(g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale, part, O,
                              out_bf16, lse, s);
-    if (whole_rows(g, part) && use_wave_kernel(g, keep, g.H * g.nq))
-        return launch_wave<64>(g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale, part, O,
-                               out_bf16, lse, s);
-    if (g.d == 64 && g.block == 64)
-        return launch_shape<64, 64>(g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale, part, O,
-                                    out_bf16, lse, s);
-    if (g.d == 128 && g.block == 64)
-        return launch_shape<128, 64>(g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale, part, O,
-                                     out_bf16, lse, s);
+    if (g.block != 64 || (g.d != 64 && g.d != 128)) return hipErrorInvalidValue;
+    switch (whole_rows(g, part) ? kernel64(g, keep, g.H * g.nq) : Kernel64::kSplitKey) {
+        case Kernel64::kWave:
+            return launch_wave<64>(g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale, part, O,
+                                   out_bf16, lse, s);
+        case Kernel64::kRows:
+            return g.d == 64 ? launch_rows<64, 64>(g, Q, sel, keep, slot_of, Kp, Vp, capacity,
+                                                   scale, part, O, out_bf16, lse, s)
+                             : launch_rows<128, 64>(g, Q, sel, keep, slot_of, Kp, Vp, capacity,
+                                                    scale, part, O, out_bf16, lse, s);
+        case Kernel64::kSplitKey:
+            return g.d == 64 ? launch_shape<64, 64>(g, Q, sel, keep, slot_of, Kp, Vp, capacity,
+                                                    scale, part, O, out_bf16, lse, s)
+                             : launch_shape<128, 64>(g, Q, sel, keep, slot_of, Kp, Vp, capacity,
+                                                     scale, part, O, out_bf16, lse, s);
+    }
     return hipErrorInvalidValue;
 }
 
@@ -1636,12 +1656,25 @@ int64_t attn_tail_workspace_bytes(const Geom& g, int keep) {
         slots = resident_slots(attn_rows_kernel<128, 128, true, false>, CfgRows<128, 128>::THREADS, dyn);
     else if (g.d == 64 && g.block == 128)
         slots = resident_slots(attn_rows_kernel<64, 128, true, false>, CfgRows<64, 128>::THREADS, dyn);
-    else if (use_wave_kernel(g, keep, g.H * g.nq))
-        slots = resident_slots(attn_wave_kernel<64, true>, 64, dyn);
-    else if (g.d == 64 && g.block == 64)
-        slots = resident_slots(attn_bf16_kernel<64, 64, true>, Cfg<64, 64>::THREADS, dyn);
-    else if (g.d == 128 && g.block == 64)
-        slots = resident_slots(attn_bf16_kernel<128, 64, true>, Cfg<128, 64>::THREADS, dyn);
+    else if (g.block == 64 && (g.d == 64 || g.d == 128)) {
+        switch (kernel64(g, keep, g.H * g.nq)) {
+            case Kernel64::kWave:
+                slots = resident_slots(attn_wave_kernel<64, true>, 64, dyn);
+                break;
+            case Kernel64::kRows:
+                slots = g.d == 64 ? resident_slots(attn_rows_kernel<64, 64, true, false>,
+                                                   CfgRows<64, 64>::THREADS, dyn)
+                                  : resident_slots(attn_rows_kernel<128, 64, true, false>,
+                                                   CfgRows<128, 64>::THREADS, dyn);
+                break;
+            case Kernel64::kSplitKey:
+                slots = g.d == 64 ? resident_slots(attn_bf16_kernel<64, 64, true>,
+                                                   Cfg<64, 64>::THREADS, dyn)
+                                  : resident_slots(attn_bf16_kernel<128, 64, true>,
+                                                   Cfg<128, 64>::THREADS, dyn);
+                break;
+        }
+    }
     if (slots <= 0) return 0;
     // the row order, then the tail pieces, which never outnumber the resident slots
     return row_sort_bytes(g.H * g.nq) + int64_t(slots) * g.block * (g.d + 1) * 4;

@@ -1,9 +1,10 @@
-"""The one-wave-per-row attention kernel (64-token blocks, d = 64, 1,800 rows or
-more, top-k width below n): rows at the threshold and past a round of resident
-waves (tail split by the workspace), ragged ends, one to several hundred kept
-blocks, lists with skipped entries, float32 and bf16 output, an explicit row order.
-The rows just below the threshold run the split-key kernel and serve as a check of
-the rule's other side. Bars: the parity suite's (bf16 2e-2 / 1e-3, lse 1e-4).
+"""The attention kernels for 64-token blocks on both sides of the rule that picks
+one by the number of rows (split-key; rows kernel past 512 rows at d = 128 and for
+800 to 1,024 and 1,200 to 1,799 at d = 64; one wave per row from 1,800 at d = 64;
+whole top-k launches only): rows past a round of resident workgroups (tail split by
+the workspace), ragged ends, one to several hundred kept blocks, lists with skipped
+entries, float32 and bf16 output, an explicit row order (the same kernel, so the
+same bits). Bars: the parity suite's (bf16 2e-2 / 1e-3, lse 1e-4).
 """
 
 import numpy as np
@@ -16,20 +17,25 @@ from tests.test_gpu_kernels import _pipeline, _rand_inputs, ctypes_scale
 
 pytestmark = pytest.mark.gpu
 
-# (H, L, i0, i1), keep, rows checked per head
+# (H, L, d, i0, i1), keep, rows checked per head
 CASES = [
-    ((47, 2500, 2, 40), 3, 6),       # 1,786 rows: split-key side of the rule
-    ((48, 2433, 1, 39), 1, 38),      # 1,824 rows, last block one key, diagonal only
-    ((90, 1600, 0, 25), 24, 3),      # 2,250 rows: 202 past a round of 2,048
-    ((8, 16500, 20, 258), 257, 3),   # 1,904 rows of 257 kept blocks, two load rounds
+    ((16, 2433, 128, 7, 39), 5, 4),      # 512 rows: the split-key kernel's last, ragged end
+    ((19, 2433, 128, 12, 39), 1, 27),    # 513 rows, last block one key, diagonal only
+    ((60, 1600, 128, 0, 25), 24, 3),     # 1,500 rows: 476 past a round of 1,024
+    ((5, 16500, 128, 130, 258), 257, 3),  # 640 rows of 257 kept blocks
+    ((25, 2500, 64, 8, 40), 3, 4),       # 800 rows: the rows kernel's first
+    ((47, 2500, 64, 2, 40), 24, 3),      # 1,786 rows: its last, past a round of 1,536
+    ((48, 2433, 64, 1, 39), 1, 38),      # 1,824 rows, last block one key, diagonal only
+    ((90, 1600, 64, 0, 25), 24, 3),      # 2,250 rows: 202 past a round of 2,048
+    ((8, 16500, 64, 20, 258), 257, 3),   # 1,904 rows of 257 kept blocks, two load rounds
 ]
 
 
 @pytest.mark.parametrize("geo,keep,check", CASES, ids=lambda x: str(x).replace(" ", ""))
-def test_wave_kernel(gpu, geo, keep, check):
+def test_kernels_for_64_token_blocks(gpu, geo, keep, check):
     torch = P.torch()
-    H, L, i0, i1 = geo
-    d = b = 64
+    H, L, d, i0, i1 = geo
+    b = 64
     q, k, v = _rand_inputs(61, H, L, d, "bf16")
     g = P.geometry(H, L, d, b, i0, i1, "bf16")
     om, osel, sel, out = _pipeline(q, k, v, g, "bf16", keep)
