@@ -14,7 +14,8 @@
 // block's K is issued once the scores of the current block are done, the
 // next V once its output product is done.
 //
-// attn_bf16_kernel (64-token blocks): 2*BLK/32 waves: wave w owns query group
+// attn_bf16_kernel (64-token blocks, and 128-token blocks with a row per CU at
+// most): 2*BLK/32 waves: wave w owns query group
 // w % (BLK/32) (32 queries) and key half w / (BLK/32) of every kept block
 // (BLK/2 keys). Each wave runs its own online softmax over its key halves
 // (running max, running sum, output accumulator) and the two halves of a
@@ -1579,6 +1580,16 @@ hipError_t launch_shape(const Geom& g, const void* Q, const int32_t* sel, int ke
 //     rows (160 KB).
 // Past 900,000 rows the split-key kernel's smaller tail split keeps the workspace
 // inside the library's fixed array.
+//
+// The kernel for 128-token blocks: with at most one row per CU the split-key
+// kernel's eight waves on a row fill its SIMDs, where the rows kernel's four leave
+// each with one wave. Attention alone, rows / split-key (us), d = 128, without a
+// workspace: 50 rows of 30 kept blocks 71 / 57, 190 of 30 72 / 60, 250 of 6 21 /
+// 21, of 30 72 / 67, 252 CDF rows 56 / 46; with one (which splits the rows over the
+// free slots) 190 of 6 31 / 23, 250 of 6 34 / 23, 100 of 30 43 / 42; d = 64, 250 of
+// 30 48 / 41. Past one row per CU some CU has two, and the rows kernel is ahead.
+bool few_rows(int G) { return G <= kCus; }
+
 enum class Kernel64 { kSplitKey, kRows, kWave };
 Kernel64 kernel64(const Geom& g, int keep, int G) {
     if (keep >= g.n || G > 900000) return Kernel64::kSplitKey;
@@ -1624,12 +1635,18 @@ hipError_t launch_attn_bf16(const Geom& g, const void* Q, const int32_t* sel, in
                             int64_t capacity, float scale, const AttnPart& part, void* O,
                             bool out_bf16, float* lse, hipStream_t s) {
     (void)hipGetLastError();
-    if (g.d == 128 && g.block == 128)
-        return launch_rows<128, 128>(g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale, part, O,
-                              out_bf16, lse, s);
-    if (g.d == 64 && g.block == 128)
-        return launch_rows<64, 128>(g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale, part, O,
-                             out_bf16, lse, s);
+    if (g.block == 128 && (g.d == 64 || g.d == 128)) {
+        const bool few = few_rows((part.h_hi - part.h_lo) * g.nq);
+        if (g.d == 64)
+            return few ? launch_shape<64, 128>(g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale,
+                                               part, O, out_bf16, lse, s)
+                       : launch_rows<64, 128>(g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale,
+                                              part, O, out_bf16, lse, s);
+        return few ? launch_shape<128, 128>(g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale, part,
+                                            O, out_bf16, lse, s)
+                   : launch_rows<128, 128>(g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale, part,
+                                           O, out_bf16, lse, s);
+    }
     if (g.block != 64 || (g.d != 64 && g.d != 128)) return hipErrorInvalidValue;
     switch (whole_rows(g, part) ? kernel64(g, keep, g.H * g.nq) : Kernel64::kSplitKey) {
         case Kernel64::kWave:
@@ -1652,11 +1669,17 @@ hipError_t launch_attn_bf16(const Geom& g, const void* Q, const int32_t* sel, in
 int64_t attn_tail_workspace_bytes(const Geom& g, int keep) {
     const size_t dyn = size_t(keep) * sizeof(int32_t);
     int slots = 0;
-    if (g.d == 128 && g.block == 128)
-        slots = resident_slots(attn_rows_kernel<128, 128, true, false>, CfgRows<128, 128>::THREADS, dyn);
-    else if (g.d == 64 && g.block == 128)
-        slots = resident_slots(attn_rows_kernel<64, 128, true, false>, CfgRows<64, 128>::THREADS, dyn);
-    else if (g.block == 64 && (g.d == 64 || g.d == 128)) {
+    if (g.block == 128 && (g.d == 64 || g.d == 128)) {
+        const bool few = few_rows(g.H * g.nq);
+        if (g.d == 64)
+            slots = few ? resident_slots(attn_bf16_kernel<64, 128, true>, Cfg<64, 128>::THREADS, dyn)
+                        : resident_slots(attn_rows_kernel<64, 128, true, false>,
+                                         CfgRows<64, 128>::THREADS, dyn);
+        else
+            slots = few ? resident_slots(attn_bf16_kernel<128, 128, true>, Cfg<128, 128>::THREADS, dyn)
+                        : resident_slots(attn_rows_kernel<128, 128, true, false>,
+                                         CfgRows<128, 128>::THREADS, dyn);
+    } else if (g.block == 64 && (g.d == 64 || g.d == 128)) {
         switch (kernel64(g, keep, g.H * g.nq)) {
             case Kernel64::kWave:
                 slots = resident_slots(attn_wave_kernel<64, true>, 64, dyn);

@@ -1,5 +1,6 @@
-"""The attention kernels for 64-token blocks on both sides of the rule that picks
-one by the number of rows (split-key; rows kernel past 512 rows at d = 128 and for
+"""The bf16 attention kernels on both sides of the rules that pick one by the number
+of rows (128-token blocks: split-key up to 256 rows, rows kernel past them; 64-token
+blocks: split-key; rows kernel past 512 rows at d = 128 and for
 800 to 1,024 and 1,200 to 1,799 at d = 64; one wave per row from 1,800 at d = 64;
 whole top-k launches only): rows past a round of resident workgroups (tail split by
 the workspace), ragged ends, one to several hundred kept blocks, lists with skipped
@@ -17,25 +18,29 @@ from tests.test_gpu_kernels import _pipeline, _rand_inputs, ctypes_scale
 
 pytestmark = pytest.mark.gpu
 
-# (H, L, d, i0, i1), keep, rows checked per head
+# (H, L, d, block, i0, i1), keep, rows checked per head
 CASES = [
-    ((16, 2433, 128, 7, 39), 5, 4),      # 512 rows: the split-key kernel's last, ragged end
-    ((19, 2433, 128, 12, 39), 1, 27),    # 513 rows, last block one key, diagonal only
-    ((60, 1600, 128, 0, 25), 24, 3),     # 1,500 rows: 476 past a round of 1,024
-    ((5, 16500, 128, 130, 258), 257, 3),  # 640 rows of 257 kept blocks
-    ((25, 2500, 64, 8, 40), 3, 4),       # 800 rows: the rows kernel's first
-    ((47, 2500, 64, 2, 40), 24, 3),      # 1,786 rows: its last, past a round of 1,536
-    ((48, 2433, 64, 1, 39), 1, 38),      # 1,824 rows, last block one key, diagonal only
-    ((90, 1600, 64, 0, 25), 24, 3),      # 2,250 rows: 202 past a round of 2,048
-    ((8, 16500, 64, 20, 258), 257, 3),   # 1,904 rows of 257 kept blocks, two load rounds
+    ((16, 2433, 128, 64, 7, 39), 5, 4),      # 512 rows: the split-key kernel's last, ragged end
+    ((19, 2433, 128, 64, 12, 39), 1, 27),    # 513 rows, last block one key, diagonal only
+    ((60, 1600, 128, 64, 0, 25), 24, 3),     # 1,500 rows: 476 past a round of 1,024
+    ((5, 16500, 128, 64, 130, 258), 257, 3),  # 640 rows of 257 kept blocks
+    ((25, 2500, 64, 64, 8, 40), 3, 4),       # 800 rows: the rows kernel's first
+    ((47, 2500, 64, 64, 2, 40), 24, 3),      # 1,786 rows: its last, past a round of 1,536
+    ((48, 2433, 64, 64, 1, 39), 1, 38),      # 1,824 rows, last block one key, diagonal only
+    ((90, 1600, 64, 64, 0, 25), 24, 3),      # 2,250 rows: 202 past a round of 2,048
+    ((8, 16500, 64, 64, 20, 258), 257, 3),   # 1,904 rows of 257 kept blocks, two load rounds
+    ((8, 4097, 128, 128, 1, 33), 6, 4),  # 256 rows, last block one key: split-key
+    ((8, 4225, 64, 128, 2, 34), 1, 32),  # the same at d = 64, diagonal only
+    ((1, 35000, 128, 128, 17, 274), 8, 9),  # 257 rows: rows kernel
+    ((257, 300, 64, 128, 2, 3), 3, 1),   # the same at d = 64, the ragged block alone
+    ((2, 33000, 128, 128, 200, 258), 250, 3),  # 116 rows of 250 kept blocks, split in two
 ]
 
 
 @pytest.mark.parametrize("geo,keep,check", CASES, ids=lambda x: str(x).replace(" ", ""))
-def test_kernels_for_64_token_blocks(gpu, geo, keep, check):
+def test_kernels_by_rows(gpu, geo, keep, check):
     torch = P.torch()
-    H, L, d, i0, i1 = geo
-    b = 64
+    H, L, d, b, i0, i1 = geo
     q, k, v = _rand_inputs(61, H, L, d, "bf16")
     g = P.geometry(H, L, d, b, i0, i1, "bf16")
     om, osel, sel, out = _pipeline(q, k, v, g, "bf16", keep)
