@@ -195,10 +195,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void a
     }
 
     floatx4 o[NQ][DC];
-    float m[NQ], l[NQ];
+    float m[NQ], l[NQ], lim[NQ];         // lim: where m moves, kRescale above it
+    const float slack = kRescale / c2;  // in unscaled scores
 #pragma unroll
     for (int a = 0; a < NQ; ++a) {
-        m[a] = -INFINITY;
+        m[a] = lim[a] = -INFINITY;
         l[a] = 0.f;
 #pragma unroll
         for (int c = 0; c < DC; ++c) o[a][c] = floatx4{};
@@ -282,25 +283,30 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void a
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int a = 0; a < NQ; ++a) {
+            // Scores stay unscaled, the running max m too, and only their differences
+            // are scaled: the top probability is exactly 1 at any scale, and a key's
+            // rounding grows with its distance from the max, not with the score. (A
+            // scaled max, rounded, against fma(x, c2, -max): from scores of about 2^31
+            // on, the difference of the two roundings leaves the exponent's range.)
             floatx4 x = s[a][0] + s[a][1];
             if (kn < 16) {
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
                     if (4 * g + u >= kn) x[u] = -INFINITY;
             }
-            const float mx =
-                quad_max(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]))) * c2;
-            if (__ballot(mx > m[a] + kRescale) != 0) {
+            const float mx = quad_max(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])));
+            if (__ballot(mx > lim[a]) != 0) {
                 const float m_new = fmaxf(m[a], mx);
-                const float alpha = __builtin_amdgcn_exp2f(m[a] - m_new);
+                const float alpha = __builtin_amdgcn_exp2f((m[a] - m_new) * c2);
                 m[a] = m_new;
+                lim[a] = m_new + slack;
                 l[a] *= alpha;
 #pragma unroll
                 for (int c = 0; c < DC; ++c) o[a][c] *= alpha;
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                s[a][0][u] = __builtin_amdgcn_exp2f(fmaf(x[u], c2, -m[a]));
+                s[a][0][u] = __builtin_amdgcn_exp2f((x[u] - m[a]) * c2);
                 l[a] += s[a][0][u];
             }
         }
@@ -375,7 +381,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void a
             wt[w] = 0.f;
             if (w < KW) {
                 const float* st = area + w * STRIDE + DC * NQ * 256 + 2 * a * 16 + qi;
-                wt[w] = st[0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(st[0] - M);
+                wt[w] = st[0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((st[0] - M) * c2);
                 tot += wt[w] * st[16];
             }
         }
@@ -383,13 +389,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void a
         const float inv = live ? 1.0f / tot : 0.f;
         // Folding into a running result: the stored row weighs ka, this part kb.
         float ka = 0.f, kb = inv;
-        float lse_out = live ? (M + log2f(tot)) * kLn2 : -INFINITY;
+        const float lb2 = fmaf(M, c2, log2f(tot));  // this part's log-sum-exp, log2 units
+        float lse_out = live ? lb2 * kLn2 : -INFINITY;
         bool store = q0 + qrow < block;
         if (acc) {
             store = store && live;  // a row with no key in this part is left as it is
             if (live) {
                 const float la2 = l_old[a] * kLog2e;
-                const float lb2 = M + log2f(tot);
                 const float mm = fmaxf(la2, lb2);
                 const float wa = la2 == -INFINITY ? 0.f : exp2f(la2 - mm);
                 const float wb = exp2f(lb2 - mm);

@@ -71,3 +71,26 @@ def test_float32_attention_edges(gpu, geo, keep):
                                      accumulate=True)
     P.check_attention(O3.cpu().numpy(), O_ref, False, f"{geo} in two parts")
     assert np.abs(l3.cpu().numpy()[fin] - lse_ref[fin]).max() <= 1e-5
+
+
+@pytest.mark.parametrize("scale", [1.0, 300.0, 1e5, 1e8, 1e20, 1e30])
+def test_float32_attention_at_large_scales(gpu, scale):
+    """Scales up to the entry point's limit, where softmax picks the best keys. Inputs
+    are small whole numbers, so every q.k is exact in float32, best keys that tie tie
+    in both, and the next best are at least ``scale`` below. From scale 300 on O is
+    the mean of the V rows that tie (at most 32 of them here: below 1e-5 of rounding
+    for |V| <= 8); lse is rounded to its own 24 bits, in two steps."""
+    H, L, d, b, i0, i1, keep = 3, 1000, 64, 64, 0, 16, 9
+    rng = np.random.default_rng(17)
+    q, k = (rng.integers(-3, 4, (H, L, d)).astype(np.float32) for _ in range(2))
+    v = rng.integers(-8, 9, (H, L, d)).astype(np.float32)
+    g = P.geometry(H, L, d, b, i0, i1, "f32")
+    om, osel, sel, out = _pipeline(q, k, v, g, "f32", keep)
+    O, lse = sp.sparsp_block_sparse_attn(g, P.to_device(q, "f32"), sel, out["slot_of"],
+                                         out["K_packed"], out["V_packed"], scale)
+    O_ref, lse_ref = orc.sparse_attention(*(x.astype(np.float64) for x in (q, k, v)), om, L, b, i0,
+                                          float(np.float32(scale)))
+    P.check_attention(O.cpu().numpy(), O_ref, False, f"scale {scale}")
+    ln, fin = lse.cpu().numpy(), np.isfinite(lse_ref)
+    assert (np.isneginf(ln) == ~fin).all()
+    assert (np.abs(ln[fin] - lse_ref[fin]) <= 1e-5 + 4 * 2.0 ** -24 * np.abs(lse_ref[fin])).all()
