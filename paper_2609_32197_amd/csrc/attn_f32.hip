@@ -113,7 +113,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void a
     const float* __restrict__ Kp, const float* __restrict__ Vp, float* __restrict__ O,
     float* __restrict__ lse, int L, int n, int d, int block, int i0, int nq, int keep,
     int64_t capacity, float c2 /* scale * log2(e) */, int kv_lo, int kv_hi, int h_lo, int acc,
-    const int32_t* __restrict__ order, int rows, int parts /* workgroups per row */) {
+    const int32_t* __restrict__ order, int rows, int parts /* workgroups per row */,
+    int first, int count /* this launch's rows, or positions of the order */) {
     extern __shared__ __attribute__((aligned(16))) int32_t smem[];
     __shared__ int wave_cnt[8];
     const int tid = threadIdx.x, nthr = blockDim.x, KW = nthr >> 6;
@@ -130,13 +131,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void a
     if (order) {
         const int pos = (idx / parts) * 8 + xcd;
         part = idx % parts;
-        if (pos >= rows) return;
-        row = order[pos];
+        if (pos >= count) return;
+        row = order[first + pos];
         if (row < 0 || row >= rows) return;
     } else {
-        const int total = rows * parts, per = total >> 3, rem = total & 7;
+        const int total = count * parts, per = total >> 3, rem = total & 7;
         const int w = xcd * per + min(xcd, rem) + idx;
-        row = w / parts;
+        row = first + w / parts;
         part = w % parts;
     }
     const int q0 = part * 16 * NQ;  // first query of the block for this workgroup
@@ -446,11 +447,18 @@ hipError_t launch_dc(const Geom& g, const float* Q, const int32_t* sel, int keep
     const size_t dyn = max(size_t(kw) * 2 * DC * 1024 + size_t(keep) * 4,
                            size_t(kw) * merge_floats(DC, nqg) * 4);
     auto* kern = nqg == 2 ? attn_f32_kernel<DC, 2> : attn_f32_kernel<DC, 1>;
-    const int grid = part.order ? (G + 7) / 8 * 8 * parts : G * parts;
-    kern<<<grid, 64 * kw, dyn, s>>>(Q, sel, slot_of, Kp, Vp, O, lse, g.L, g.n, g.d, g.block,
-                                         g.i0, g.nq, keep, capacity, c2, part.kv_lo, part.kv_hi,
-                                         part.h_lo, part.acc, part.order, G, parts);
-    return hipGetLastError();
+    // A launch holds less than 2^32 threads, which 270 million queries in parts of 16
+    // (four waves each) would pass: such a call takes several launches.
+    const int most = int((UINT32_MAX / (64u * kw * parts)) & ~7u);
+    for (int first = 0; first < G; first += most) {
+        const int count = min(most, G - first);
+        const int grid = part.order ? (count + 7) / 8 * 8 * parts : count * parts;
+        kern<<<grid, 64 * kw, dyn, s>>>(Q, sel, slot_of, Kp, Vp, O, lse, g.L, g.n, g.d, g.block,
+                                        g.i0, g.nq, keep, capacity, c2, part.kv_lo, part.kv_hi,
+                                        part.h_lo, part.acc, part.order, G, parts, first, count);
+        if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace

@@ -95,3 +95,34 @@ def test_largest_head_count(gpu):
 ], ids=lambda g: "H{}L{}d{}b{}_{}-{}_{}".format(*g))
 def test_sequence_shorter_than_one_block(gpu, geo):
     _check(geo, keep=1, seed=13)
+
+
+def test_more_threads_than_one_launch_holds(gpu):
+    """float32 attention of 538 million queries (513 heads x 4,096 blocks of 256 at
+    d = 4): its workgroups hold more threads than a launch may, 2^32 - 1. Every
+    block attends itself alone; Q, K and V share one buffer. All of O is written,
+    and the rows at both ends and at the end of the first launch are compared."""
+    torch = P.torch()
+    if torch.cuda.get_device_properties(0).total_memory < 48 << 30:
+        pytest.skip("needs 48 GB of GPU memory")
+    H, n, b, d = 513, 4096, 256, 4
+    rows, scale = H * n, 0.5
+    X = torch.empty((H, n * b, d), dtype=torch.float32, device="cuda")
+    X.normal_(generator=torch.Generator(device="cuda").manual_seed(5))
+    Kp, Vp = X.view(rows, b, d), X.view(rows, d, b)
+    g = P.geometry(H, n * b, d, b, 0, n, "f32")
+    sel = torch.arange(n, dtype=torch.int32, device="cuda").repeat(H, 1).view(H, n, 1)
+    slot_of = torch.arange(rows, dtype=torch.int32, device="cuda").view(H, n)
+    order = torch.arange(rows - 1, -1, -1, dtype=torch.int32, device="cuda")
+    O, lse = torch.empty_like(X), torch.empty((H, n * b), device="cuda")
+    edge = (2 ** 32 - 1) // (256 * 8) // 8 * 8  # rows of the first launch
+    assert edge < rows
+    for row_order in (None, order):
+        O.fill_(float("nan"))
+        sp.sparsp_block_sparse_attn(g, X, sel, slot_of, Kp, Vp, scale, O=O, lse=lse,
+                                    row_order=row_order)
+        assert not any(bool(torch.isnan(o).any()) for o in O.split(64))
+        for r in (0, 1, edge - 1, edge, rows - edge - 1, rows - edge, rows - 1):
+            q, k, v = Kp[r].double().cpu(), Kp[r].double().cpu(), Vp[r].double().cpu()
+            ref = torch.softmax(q @ k.t() * scale, 1) @ v.t()
+            P.check_attention(O.view(rows, b, d)[r].cpu().numpy(), ref.numpy(), False, f"row {r}")
