@@ -252,8 +252,9 @@ hipError_t launch_cdf_s(const Geom& g, const float* scores, float tau, const Glo
 }
 
 // Row order for rows of unequal kept counts (CDF selection), for a launch
-// whose workgroup w runs on XCD w mod 8. Eight workgroups, one per queue; each
-// repeats steps 1 and 2, which is cheaper than handing their result on:
+// whose workgroup w runs on XCD w mod 8. Eight workgroups, one per queue (or one
+// for all of them, see launch_row_order); each repeats steps 1 and 2, which is
+// cheaper than handing their result on:
 //   1. totals per head; heads ranked by total (descending, then by index);
 //   2. heads dealt to the eight XCD queues largest first, each to the least
 //      loaded queue that still has room (H/8 heads per queue, the first H mod 8
@@ -386,39 +387,41 @@ __global__ __launch_bounds__(1024) void row_order_kernel(const int32_t* __restri
 #pragma unroll
     for (int x = 0; x < kXcds; ++x) ql[x] = (q_first[x + 1] - q_first[x]) * nq;
 
-    // 3. counting sort of this workgroup's queue by count, largest first, and
+    // 3. counting sort of this workgroup's queues by count, largest first, and
     // placement at the queue's round-robin positions
     const int per = (n + 1 + 1023) / 1024;
-    const int x = blockIdx.x;
-    if (ql[x] == 0) return;  // the whole workgroup
-    const int* qh = q_heads + q_first[x];
-    for (int c = tid; c <= n; c += 1024) start[c] = 0;
-    __syncthreads();
-    for (int i = tid; i < ql[x]; i += 1024) atomicAdd(&start[cnt_at(qh[i / nq] * nq + i % nq)], 1);
-    __syncthreads();
-    // exclusive scan over the count values n, n-1, ..., 0
-    int local = 0;
-    for (int k = 0; k < per; ++k) {
-        const int idx = tid * per + k;
-        if (idx <= n) local += start[n - idx];
-    }
-    int run = block_exclusive_scan(local, wave_sums);
-    for (int k = 0; k < per; ++k) {
-        const int idx = tid * per + k;
-        if (idx <= n) {
-            const int c = start[n - idx];
-            start[n - idx] = run;
-            run += c;
+    for (int x = blockIdx.x; x < kXcds; x += gridDim.x) {
+        if (ql[x] == 0) continue;  // the whole workgroup
+        const int* qh = q_heads + q_first[x];
+        for (int c = tid; c <= n; c += 1024) start[c] = 0;
+        __syncthreads();
+        for (int i = tid; i < ql[x]; i += 1024) atomicAdd(&start[cnt_at(qh[i / nq] * nq + i % nq)], 1);
+        __syncthreads();
+        // exclusive scan over the count values n, n-1, ..., 0
+        int local = 0;
+        for (int k = 0; k < per; ++k) {
+            const int idx = tid * per + k;
+            if (idx <= n) local += start[n - idx];
         }
-    }
-    __syncthreads();
-    for (int i = tid; i < ql[x]; i += 1024) {
-        const int r = qh[i / nq] * nq + i % nq;
-        const int k = atomicAdd(&start[cnt_at(r)], 1);  // place in queue x
-        int pos = 0;  // round-robin position of entry k of queue x
+        int run = block_exclusive_scan(local, wave_sums);
+        for (int k = 0; k < per; ++k) {
+            const int idx = tid * per + k;
+            if (idx <= n) {
+                const int c = start[n - idx];
+                start[n - idx] = run;
+                run += c;
+            }
+        }
+        __syncthreads();
+        for (int i = tid; i < ql[x]; i += 1024) {
+            const int r = qh[i / nq] * nq + i % nq;
+            const int k = atomicAdd(&start[cnt_at(r)], 1);  // place in queue x
+            int pos = 0;  // round-robin position of entry k of queue x
 #pragma unroll
-        for (int y = 0; y < kXcds; ++y) pos += min(k, ql[y]) + (y < x && ql[y] > k ? 1 : 0);
-        order[pos] = r;
+            for (int y = 0; y < kXcds; ++y) pos += min(k, ql[y]) + (y < x && ql[y] > k ? 1 : 0);
+            order[pos] = r;
+        }
+        __syncthreads();  // start is cleared by the next queue
     }
 }
 
@@ -451,7 +454,12 @@ hipError_t launch_topk(const Geom& g, const float* scores, int keep, const Globa
 hipError_t launch_row_order(const int32_t* counts, int H, int nq, int n, int32_t* order,
                             hipStream_t st) {
     (void)hipGetLastError();
-    row_order_kernel<<<kXcds, 1024, 0, st>>>(counts, H, nq, n, order);
+    // An order written over the counts (a view of the same tensor) takes one
+    // workgroup: up to kCountCache rows it has every count in its LDS before it
+    // writes, where one of eight could read what another has written.
+    const int64_t rows = int64_t(H) * nq;
+    const bool apart = counts + rows <= order || order + rows <= counts;
+    row_order_kernel<<<apart ? kXcds : 1, 1024, 0, st>>>(counts, H, nq, n, order);
     return hipGetLastError();
 }
 

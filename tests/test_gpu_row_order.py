@@ -66,6 +66,22 @@ def test_row_order_balances_heads_and_sorts_rows(gpu, H, nq, n, lo, hi):
         np.testing.assert_array_equal(seq, np.sort(seq)[::-1])  # longest first
 
 
+@pytest.mark.parametrize("H,nq,n", [(1, 5, 9), (40, 147, 591), (19, 9, 128), (112, 128, 256)])
+def test_row_order_over_its_own_counts(gpu, H, nq, n):
+    """The order may be written over the counts it is made from, up to the 14,336 rows
+    whose counts one workgroup holds: the same queues and counts as apart from them
+    (rows of equal count may differ)."""
+    torch = P.torch()
+    counts = np.random.default_rng(H).integers(0, n + 1, size=(H, nq)).astype(np.int32)
+    g = P.geometry(H, n * 64, 64, 64, 0, nq, "f32")
+    apart = sp.sparsp_row_order(g, torch.from_numpy(counts).cuda()).cpu().numpy()
+    for _ in range(5):
+        both = torch.from_numpy(counts).cuda()
+        got = sp.sparsp_row_order(g, both, order=both.view(-1)).cpu().numpy()
+        assert sorted(got.tolist()) == list(range(H * nq))
+        np.testing.assert_array_equal(counts.reshape(-1)[got], counts.reshape(-1)[apart])
+
+
 GEOMS = [
     (3, 9000, 128, 128, 20, 71, "bf16"),   # 128-token kernel
     (2, 4400, 64, 128, 3, 35, "bf16"),     # 128-token kernel, d = 64
