@@ -2,11 +2,11 @@
 // the packed K/V buffers (Eq. 1 over the kept blocks; softmax renormalised
 // over the kept keys, computed online in float32).
 //
-// Three kernels, one workgroup per (head, local query block) in all; the shape
+// Two kernels, one workgroup per (head, local query block) in both; the shape
 // and the number of rows pick the kernel.
 //
-// attn_rows_kernel (128-token blocks, and 64-token blocks with enough rows of
-// like length; the figures here are for 128): four waves, wave w owns queries
+// attn_rows_kernel (128-token blocks, and 64-token blocks at d = 128 with enough
+// rows of like length; the figures here are for 128): four waves, wave w owns queries
 // 32 w .. +31 against all 128 keys of every kept block; single K and V tile
 // buffers (64 KB of LDS at d = 128), two workgroups per CU. The waves that
 // share a SIMD come from different workgroups and are not tied by a barrier,
@@ -24,10 +24,7 @@
 // of block jj+1 is issued right after the barrier that opens block jj and has
 // the whole of block jj's compute to land. One barrier per block.
 //
-// attn_wave_kernel (64-token blocks at d = 64, 1,800 rows or more): one wave per row,
-// all 64 queries against all keys, tiles of its own, no barrier.
-//
-// Data movement (all). The kept blocks' K tile ([BLK, D]) and transposed V
+// Data movement (both). The kept blocks' K tile ([BLK, D]) and transposed V
 // tile ([D, BLK]) are copied HBM -> LDS with direct-to-LDS buffer loads
 // (buffer_load_dwordx4 ... lds); each wave waits for its own copies before the
 // barrier that publishes them. The split-key kernel reads all MFMA operands
@@ -69,6 +66,18 @@
 // only grows, so t errs on the side of moving the max; on spread rows t
 // reaches several units after the first blocks, and most blocks skip the
 // rescale (and the logarithm, which only rescale blocks compute).
+//
+// For 64-token blocks the rows kernel moves the max down as well, and for each half
+// of a block's keys by itself: m becomes the half's max whenever that carries more
+// than 2^-4.5 of the query's whole mass, above or below the max so far, so the top
+// probability of every half that matters is exact. With upward moves per block it
+// rounded more than the split-key kernel, whose two key halves hold an exact top
+// probability each: error of float32 O against 64 bits at d = 128, peaked rows of 14
+// to 200 blocks 5.8e-4 against 4.6e-4 (now 3.5e-4), unit normal inputs 1.51e-3
+// against 1.48e-3 at 14 blocks (now 1.45e-3). 2^-4 instead leaves unit normal inputs
+// 1.5% above the split-key kernel. At d = 64 the moves cost what the rows kernel had
+// gained there (1,000 to 6,672 rows: 6% over the split-key kernel's time to 5%
+// under without them, 2 to 13% over with them), so it is not used.
 #include <type_traits>
 
 #include "sparsp_internal.h"
@@ -91,6 +100,18 @@ constexpr int kCus = 256;                  // of an MI355X
 // exceed l / 4, and is forced beyond 2^8.
 __device__ __forceinline__ float rescale_threshold(float l) {
     return fminf(kRescaleThreshold, fmaxf(0.f, __log2f(l) - 2.f));
+}
+
+// The same where the max moves both ways: l is the query's whole mass, with the 1 of
+// the key that the max moves to. A move scales the sums up by at most 2^4.5.
+__device__ __forceinline__ float rescale_limit(float l) {
+    return fminf(kRescaleThreshold, __log2f(l) - 4.5f);
+}
+
+// The max after a move: up to the block's, or (DOWN) down to it if it is past the limit.
+template <bool DOWN>
+__device__ __forceinline__ float moved_max(float m, float mx, float lim) {
+    return DOWN && mx > lim ? mx : fmaxf(m, mx);
 }
 
 __device__ __forceinline__ int sigma(int m) {  // swap bits 2 and 3
@@ -620,7 +641,7 @@ void attn_bf16_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
     if (lse && g == 0 && store) lse[orow] = lse_out;
 }
 
-// Kernel for 128-token blocks (and, with two waves, 64-token ones): two
+// Kernel for 128-token blocks (and, with two waves, 64-token ones at d = 128): two
 // independent workgroups per CU. Four waves per workgroup, wave w owning queries 32 w .. +31 and every key of each kept
 // block, so each wave runs one online softmax and no merge is needed; single
 // K and V tile buffers (64 KB of LDS at d = 128). The two waves that share a
@@ -649,6 +670,9 @@ struct CfgRows {
     static constexpr int PT = BLK / 32;          // 32-key steps of the output product
     static constexpr int KT = D / 32;            // k steps of the score product
     static constexpr int DT = D / 16;            // d tiles of the output product
+    // The running max moves both ways, and for each half of a block's keys by itself.
+    static constexpr bool DOWN = BLK == 64;
+    static constexpr int PARTS = DOWN ? 2 : 1;
     static constexpr int TILE = BLK * D;
     static constexpr int CHUNKS = TILE / 8;
     static constexpr int DMA = CHUNKS / THREADS;
@@ -889,29 +913,52 @@ void attn_rows_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
                     if (key >= last_cnt) s[mt][0][rr] = s[mt][1][rr] = -INFINITY;
                 }
         }
-        float mx[2] = {-INFINITY, -INFINITY};
+        constexpr int MP = C::MT / C::PARTS;  // 16-key tiles per part of the block
+        float mx[2][C::PARTS];
 #pragma unroll
-        for (int a = 0; a < 2; ++a) {
+        for (int a = 0; a < 2; ++a)
 #pragma unroll
-            for (int mt = 0; mt < C::MT; ++mt)
+            for (int y = 0; y < C::PARTS; ++y) {
+                mx[a][y] = -INFINITY;
 #pragma unroll
-                for (int rr = 0; rr < 4; rr += 2)
-                    mx[a] = fmaxf(fmaxf(mx[a], s[mt][a][rr]), s[mt][a][rr + 1]);
-            mx[a] = quad_max(mx[a]) * c2;
-        }
-        const bool moved = __ballot(mx[0] > lim[0] || mx[1] > lim[1]) != 0;
+                for (int mt = MP * y; mt < MP * (y + 1); ++mt)
+#pragma unroll
+                    for (int rr = 0; rr < 4; rr += 2)
+                        mx[a][y] = fmaxf(fmaxf(mx[a][y], s[mt][a][rr]), s[mt][a][rr + 1]);
+                mx[a][y] = quad_max(mx[a][y]) * c2;
+            }
+        const bool moved = __ballot(mx[0][0] > lim[0] || mx[1][0] > lim[1]) != 0;
         if (moved) {
 #pragma unroll
             for (int a = 0; a < 2; ++a) {
-                const float m_new = fmaxf(m_run[a], mx[a]);
+                const float m_new = moved_max<C::DOWN>(m_run[a], mx[a][0], lim[a]);
                 const float alpha =
                     (m_new == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m_run[a] - m_new);
                 m_run[a] = m_new;
                 l_run[a] *= alpha;
-                lim[a] = m_run[a] + rescale_threshold(l_run[a]);
+                // (a limit that may let m fall has to be the same in a query's four lanes)
+                lim[a] = m_run[a] + (C::DOWN ? rescale_limit(quad_sum(l_run[a]) + 1.f)
+                                             : rescale_threshold(l_run[a]));
                 neg_m[a] = (m_run[a] == -INFINITY) ? 0.f : -m_run[a];
 #pragma unroll
                 for (int dt = 0; dt < C::DT; ++dt) oacc[dt][a] *= alpha;
+            }
+        }
+        // The second part's move is decided here too, so that its probabilities can be
+        // computed ahead; the sums follow between the parts' output products.
+        float neg_2[2] = {neg_m[0], neg_m[1]}, alpha_2[2] = {1.f, 1.f};
+        bool moved_2 = false;
+        if constexpr (C::PARTS == 2) {
+            moved_2 = __ballot(mx[0][1] > lim[0] || mx[1][1] > lim[1]) != 0;
+            if (moved_2) {
+#pragma unroll
+                for (int a = 0; a < 2; ++a) {
+                    const float m_new = moved_max<C::DOWN>(m_run[a], mx[a][1], lim[a]);
+                    alpha_2[a] =
+                        (m_new == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m_run[a] - m_new);
+                    m_run[a] = m_new;
+                    neg_2[a] = (m_new == -INFINITY) ? 0.f : -m_new;
+                }
             }
         }
 
@@ -922,7 +969,8 @@ void attn_rows_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
         // four, measured 0.4 to 1.1% slower than the compiler's own order.)
         // (the two partial sums of a group start from its first two
         // probabilities, not from 0 + p, which the compiler cannot drop)
-        float lsum[2][2];
+        float lsum[2][C::PARTS][2];
+        constexpr int TP = C::PT / C::PARTS;  // 32-key steps per part
         constexpr int DH = C::DT / 2;
         constexpr int VSTEPS = 2 * C::PT;
         bf16x8 vb[2][DH];
@@ -938,11 +986,11 @@ void attn_rows_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
             floatx8 p;
 #pragma unroll
             for (int v = 0; v < 8; ++v) {
-                p[v] = __builtin_amdgcn_exp2f(fmaf(s[2 * t + (v >> 2)][a][v & 3], c2, neg_m[a]));
-                if (t == 0 && v < 2)
-                    lsum[a][v] = p[v];
+                p[v] = __builtin_amdgcn_exp2f(fmaf(s[2 * t + (v >> 2)][a][v & 3], c2, t < TP ? neg_m[a] : neg_2[a]));
+                if (t % TP == 0 && v < 2)
+                    lsum[a][t / TP][v] = p[v];
                 else
-                    lsum[a][v & 1] += p[v];
+                    lsum[a][t / TP][v & 1] += p[v];
             }
             return __builtin_convertvector(p, bf16x8);
         };
@@ -959,6 +1007,20 @@ void attn_rows_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
                 pb[0] = pbn[0];
                 pb[1] = pbn[1];
             }
+            if (C::PARTS == 2 && i == VSTEPS / 2) {
+#pragma unroll
+                for (int a = 0; a < 2; ++a) l_run[a] += lsum[a][0][0] + lsum[a][0][1];
+                if (moved_2) {
+#pragma unroll
+                    for (int a = 0; a < 2; ++a) {
+                        l_run[a] *= alpha_2[a];
+                        lim[a] = m_run[a] + rescale_limit(quad_sum(l_run[a]) + 1.f);
+                        neg_m[a] = neg_2[a];
+#pragma unroll
+                        for (int dt = 0; dt < C::DT; ++dt) oacc[dt][a] *= alpha_2[a];
+                    }
+                }
+            }
             if (t + 1 < C::PT) pbn[hf] = pstep(t + 1, hf);
 #pragma unroll
             for (int x = 0; x < DH; ++x)
@@ -973,7 +1035,8 @@ void attn_rows_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
         else
             __builtin_amdgcn_s_setprio(0);
 #pragma unroll
-        for (int a = 0; a < 2; ++a) l_run[a] += lsum[a][0] + lsum[a][1];
+        for (int a = 0; a < 2; ++a)
+            l_run[a] += lsum[a][C::PARTS - 1][0] + lsum[a][C::PARTS - 1][1];
 
         wait_vmem_all();   // K(jj+1) landed
         __syncthreads();   // K(jj+1) visible; every wave is done with V(jj)
@@ -1044,300 +1107,6 @@ void attn_rows_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
             }
         }
         if (lse && g == 0) lse[orow] = lse_out;
-    }
-}
-
-// Kernel for 64-token blocks at d = 64 in large launches: one wave per row, a
-// workgroup of its own. The wave owns all 64 queries against all keys of every
-// kept block, stages K and V^T tiles (8 KB apiece) for itself and waits for its
-// own copies by count: there is no barrier and no merge. K of the next block is
-// copied while the softmax and output product of this one run, V while the next
-// scores run. Every operand read feeds two MFMAs, half the LDS traffic of the
-// split-key kernel, and the work per block spreads over four times its scores.
-// Eight rows are in flight per CU, so a launch needs many rows of like length
-// (the rule stands at kernel64).
-template <int D>
-struct CfgWave {
-    static constexpr int BLK = 64;
-    static constexpr int KT = D / 16;            // k steps of the score product
-    static constexpr int DT = D / 32;            // d tiles of the output product
-    static constexpr int TILE = BLK * D;
-    static constexpr int DMA = TILE / 8 / 64;    // copies per lane per tile
-    static_assert(D == 64, "one copy pattern serves the K and the V^T tile");
-};
-
-template <int D, bool OUT_BF16>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
-void attn_wave_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict__ sel,
-                      const int32_t* __restrict__ slot_of, const uint16_t* __restrict__ Kp,
-                      const uint16_t* __restrict__ Vp, void* __restrict__ O,
-                      float* __restrict__ lse, int L, int n, int i0, int nq, int keep,
-                      int64_t capacity, float c2 /* scale * log2(e) */, int G, int tail_first,
-                      int tail_k, float* __restrict__ part_o,
-                      float* __restrict__ part_lse, const int32_t* __restrict__ row_sort,
-                      const int32_t* __restrict__ order) {
-    using C = CfgWave<D>;
-    constexpr int BLK = C::BLK;
-    __shared__ __attribute__((aligned(16))) uint16_t lk[C::TILE];
-    __shared__ __attribute__((aligned(16))) uint16_t lv[C::TILE];
-    extern __shared__ int32_t codes[];
-
-    const int lane = threadIdx.x;
-    const int qi = lane & 31, g = lane >> 5;
-
-    const TailPiece tp = tail_piece(blockIdx.x, tail_first, tail_k);
-    int row;
-    if (order) {  // an explicit row order; no XCD remap
-        row = order[blockIdx.x];
-        if (row < 0 || row >= G) return;
-    } else {
-        row = sorted_row(xcd_row(tp.index, G), nq, row_sort);
-    }
-    const int h = row / nq, r = row % nq;
-
-    // The kept list: usable entries compacted in list order, four per lane and
-    // round so that a round's loads overlap.
-    int nkeep = 0;
-    {
-        const int32_t* srow = sel + int64_t(row) * keep;
-        const int32_t* hslot = slot_of + int64_t(h) * n;
-        const bool ragged = (L % BLK) != 0;
-        for (int base = 0; base < keep; base += 256) {
-            int code[4], j[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int jj = base + u * 64 + lane;
-                j[u] = jj < keep ? srow[jj] : -1;
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int sl = (j[u] >= 0 && j[u] < n) ? hslot[j[u]] : -1;
-                code[u] = (sl >= 0 && sl < capacity && sl < (1 << 30))
-                              ? 2 * sl + ((ragged && j[u] == n - 1) ? 1 : 0)
-                              : -1;
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const uint64_t bal = __ballot(code[u] >= 0);
-                const int below = __builtin_amdgcn_mbcnt_hi(
-                    uint32_t(bal >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(bal), 0));
-                if (code[u] >= 0) codes[nkeep + below] = code[u];
-                nkeep += __popcll(bal);
-            }
-        }
-        __syncthreads();  // (one wave: orders the list's writes before its reads)
-    }
-    const int32_t* kept = codes;  // this workgroup's kept list
-    if (tp.piece >= 0) {          // its share of a split tail row
-        const int e0 = tp.piece * nkeep / tail_k, e1 = (tp.piece + 1) * nkeep / tail_k;
-        kept = codes + e0;
-        nkeep = e1 - e0;
-    }
-
-    int voff[C::DMA];
-#pragma unroll
-    for (int u = 0; u < C::DMA; ++u) voff[u] = chunk_src_offset<D>(u * 64 + lane);
-    auto copy_k = [&](int code) {
-        copy_tile<1, C::DMA>(Kp + int64_t(code >> 1) * C::TILE, C::TILE * 2, lk, voff, 0);
-    };
-    auto copy_v = [&](int code) {
-        copy_tile<1, C::DMA>(Vp + int64_t(code >> 1) * C::TILE, C::TILE * 2, lv, voff, 0);
-    };
-
-    // Q^T operands: lane holds Q[q][16 kt + 8 g .. +7] of its query of each group.
-    bf16x8 qf[2][C::KT];
-    bool qvalid[2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a) {
-        const int qtok = (i0 + r) * BLK + 32 * a + qi;
-        qvalid[a] = qtok < L;
-        const uint16_t* qp = Q + (int64_t(h) * L + (qvalid[a] ? qtok : 0)) * D + 8 * g;
-#pragma unroll
-        for (int kt = 0; kt < C::KT; ++kt) {
-            uint4 v = qvalid[a] ? *reinterpret_cast<const uint4*>(qp + 16 * kt) : make_uint4(0, 0, 0, 0);
-            qf[a][kt] = __builtin_bit_cast(bf16x8, v);
-        }
-    }
-
-    floatx16 oacc[C::DT][2];
-#pragma unroll
-    for (int dt = 0; dt < C::DT; ++dt) oacc[dt][0] = oacc[dt][1] = floatx16{};
-    float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
-    // Set only where the max moves: lim = m_run + the rescale threshold,
-    // neg_m = -m_run, or 0 while the lane has seen no finite score.
-    float lim[2] = {-INFINITY, -INFINITY}, neg_m[2] = {0.f, 0.f};
-    const int last_cnt = L - (L / BLK) * BLK;
-
-    // From here on only the copies are in flight (see copy_tile).
-    wait_vmem_all();
-    int code = 0;
-    if (nkeep > 0) {
-        code = __builtin_amdgcn_readfirstlane(kept[0]);
-        copy_k(code);
-    }
-    for (int jj = 0; jj < nkeep; ++jj) {
-        const int cur = code;
-        copy_v(cur);
-        // (the last block's K is read again rather than none, so that the count
-        // of copies in flight is the same in every iteration)
-        const int next = kept[jj + 1 < nkeep ? jj + 1 : jj];
-        wait_vmem_keep<C::DMA>();  // K landed; V may still be in flight
-        __builtin_amdgcn_sched_barrier(0);
-        // Scores: s[mt][a][rr] is key 32 mt + 16 (rr/8) + 8 g + rr%8 of query
-        // 32 a + qi.
-        floatx16 s[2][2];
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt) s[mt][0] = s[mt][1] = floatx16{};
-        bf16x8 kb[2][2];
-        auto kread = [&](int kt, bf16x8 (&dst)[2]) {
-#pragma unroll
-            for (int mt = 0; mt < 2; ++mt) {
-                const int krow = 32 * mt + sigma(qi);
-                dst[mt] = *reinterpret_cast<const bf16x8*>(
-                    lk + krow * D + (((2 * kt + g) ^ swz<D>(krow)) * 8));
-            }
-        };
-        kread(0, kb[0]);
-#pragma unroll
-        for (int kt = 0; kt < C::KT; ++kt) {
-            if (kt + 1 < C::KT) kread(kt + 1, kb[(kt + 1) & 1]);
-#pragma unroll
-            for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-                for (int a = 0; a < 2; ++a)
-                    s[mt][a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kb[kt & 1][mt], qf[a][kt],
-                                                                      s[mt][a], 0, 0, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        code = __builtin_amdgcn_readfirstlane(next);
-        copy_k(code);
-        __builtin_amdgcn_sched_barrier(0);
-
-        __builtin_amdgcn_s_setprio(1);
-        if (cur & 1) {  // partial last block: keys past L do not exist
-#pragma unroll
-            for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-                for (int rr = 0; rr < 16; ++rr) {
-                    const int key = 32 * mt + 16 * (rr >> 3) + 8 * g + (rr & 7);
-                    if (key >= last_cnt) s[mt][0][rr] = s[mt][1][rr] = -INFINITY;
-                }
-        }
-        float mx[2] = {-INFINITY, -INFINITY};
-#pragma unroll
-        for (int a = 0; a < 2; ++a) {
-#pragma unroll
-            for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-                for (int rr = 0; rr < 16; rr += 2)
-                    mx[a] = fmaxf(fmaxf(mx[a], s[mt][a][rr]), s[mt][a][rr + 1]);
-            mx[a] = pair_max(mx[a]) * c2;
-        }
-        const bool moved = __ballot(mx[0] > lim[0] || mx[1] > lim[1]) != 0;
-        if (moved) {
-#pragma unroll
-            for (int a = 0; a < 2; ++a) {
-                const float m_new = fmaxf(m_run[a], mx[a]);
-                const float alpha =
-                    (m_new == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m_run[a] - m_new);
-                m_run[a] = m_new;
-                l_run[a] *= alpha;
-                lim[a] = m_run[a] + rescale_threshold(l_run[a]);
-                neg_m[a] = (m_run[a] == -INFINITY) ? 0.f : -m_run[a];
-#pragma unroll
-                for (int dt = 0; dt < C::DT; ++dt) oacc[dt][a] *= alpha;
-            }
-        }
-        wait_vmem_keep<C::DMA>();  // V landed; the next K may still be in flight
-        __builtin_amdgcn_sched_barrier(0);
-        // Output product by 16-key steps; the probabilities of step t+1 are
-        // computed while the MFMAs of step t run.
-        float lsum[2][2];
-        bf16x8 vb[2][C::DT];
-        auto vread = [&](int t, bf16x8 (&dst)[C::DT]) {
-#pragma unroll
-            for (int dt = 0; dt < C::DT; ++dt) {
-                const int vrow = 32 * dt + qi;
-                dst[dt] = *reinterpret_cast<const bf16x8*>(
-                    lv + vrow * BLK + (((2 * t + g) ^ swz<BLK>(vrow)) * 8));
-            }
-        };
-        auto pstep = [&](int t, int a) -> bf16x8 {
-            floatx8 p;
-#pragma unroll
-            for (int v = 0; v < 8; ++v) {
-                p[v] = __builtin_amdgcn_exp2f(fmaf(s[t >> 1][a][8 * (t & 1) + v], c2, neg_m[a]));
-                if (t == 0 && v < 2)
-                    lsum[a][v] = p[v];
-                else
-                    lsum[a][v & 1] += p[v];
-            }
-            return __builtin_convertvector(p, bf16x8);
-        };
-        vread(0, vb[0]);
-        bf16x8 pbn[2];
-        pbn[0] = pstep(0, 0);
-        pbn[1] = pstep(0, 1);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            if (t + 1 < 4) vread(t + 1, vb[(t + 1) & 1]);
-            __builtin_amdgcn_sched_barrier(0);
-            const bf16x8 pb[2] = {pbn[0], pbn[1]};
-            if (t + 1 < 4) {
-                pbn[0] = pstep(t + 1, 0);
-                pbn[1] = pstep(t + 1, 1);
-            }
-#pragma unroll
-            for (int dt = 0; dt < C::DT; ++dt)
-#pragma unroll
-                for (int a = 0; a < 2; ++a)
-                    oacc[dt][a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vb[t & 1][dt], pb[a],
-                                                                         oacc[dt][a], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        __builtin_amdgcn_s_setprio(0);
-#pragma unroll
-        for (int a = 0; a < 2; ++a) l_run[a] += lsum[a][0] + lsum[a][1];
-    }
-    wait_vmem_all();  // no copy may land after the wave has gone
-
-    const int64_t orow0 = int64_t(row) * BLK;
-#pragma unroll
-    for (int a = 0; a < 2; ++a) {
-        const float l_tot = pair_sum(l_run[a]);
-        const bool live = qvalid[a] && l_tot > 0.f;
-        const float inv = live ? 1.0f / l_tot : 0.f;
-        const int q = 32 * a + qi;
-        const float lse_out = live ? (m_run[a] + __log2f(l_tot)) * kLn2 : -INFINITY;
-        const int64_t prow = int64_t(blockIdx.x - tail_first) * BLK + q;  // row of a piece's partials
-#pragma unroll
-        for (int dt = 0; dt < C::DT; ++dt) {
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                float o4[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) o4[u] = live ? oacc[dt][a][4 * q4 + u] * inv : 0.f;
-                const int d0 = 32 * dt + 8 * q4 + 4 * g;
-                if (tp.piece >= 0) {  // a piece of a split tail row: float32 partial
-                    *reinterpret_cast<float4*>(part_o + prow * D + d0) =
-                        make_float4(o4[0], o4[1], o4[2], o4[3]);
-                } else if constexpr (OUT_BF16) {
-                    uint2 w;
-                    w.x = f32_to_bf16_bits(o4[0]) | (f32_to_bf16_bits(o4[1]) << 16);
-                    w.y = f32_to_bf16_bits(o4[2]) | (f32_to_bf16_bits(o4[3]) << 16);
-                    *reinterpret_cast<uint2*>(static_cast<uint16_t*>(O) + (orow0 + q) * D + d0) = w;
-                } else {
-                    *reinterpret_cast<float4*>(static_cast<float*>(O) + (orow0 + q) * D + d0) =
-                        make_float4(o4[0], o4[1], o4[2], o4[3]);
-                }
-            }
-        }
-        if (g == 0) {
-            if (tp.piece >= 0)
-                part_lse[prow] = lse_out;
-            else if (lse)
-                lse[orow0 + q] = lse_out;
-        }
     }
 }
 
@@ -1556,28 +1325,19 @@ hipError_t launch_shape(const Geom& g, const void* Q, const int32_t* sel, int ke
                     : launch_tail_merge<D, BLK, false>(g, part, tp, G, ts.part_o, ts.part_lse, O, lse, s);
 }
 
-// The kernel for 64-token blocks. The split-key kernel has four waves on a row and
-// double-buffered tiles (d = 128: 512 rows in flight, d = 64: 1,024); the rows
-// kernel two waves and single buffers (1,024 and 1,536), the wave kernel one wave
-// (2,048 at d = 64). Fewer waves a row do less work around each score and each
-// operand, but take a row longer, so they need rows that
-//   - fill the chip. Attention alone, split-key / rows / wave kernel (us):
-//       d = 128, rows x kept blocks: 500 x 60 90 / 96; 600 x 12 40 / 30, x 60
-//       104 / 97; 750 x 60 122 / 104; 1,050 x 60 159 / 150; 2,500 x 12 98 / 87,
-//       x 60 352 / 326; 6,672 x 60 974 / 829: the rows kernel past the split-key
-//       kernel's round of 512;
-//       d = 64: 675 x 60 65 / 74; 825 x 60 81 / 78; 1,000 x 60 85 / 81; 1,050 x 60
-//       92 / 102 (the split-key kernel's round of 1,024 and a few rows that its
-//       tail split spreads); 1,300 x 60 107 / 106 / 123; 1,500 x 60 130 / 115;
-//       1,812 x 60 158 / - / 143; 2,500 x 60 187 / - / 181; 6,672 x 14 163 / - /
-//       151, x 139 1,144 / - / 1,109;
+// The kernel for 64-token blocks at d = 128 (at d = 64 it is always the split-key
+// kernel). The split-key kernel has four waves on a row and double-buffered tiles (512
+// rows in flight); the rows kernel two waves and single buffers (1,024). Fewer waves a
+// row do less work around each score and each operand, but take a row longer, so they
+// need rows that
+//   - fill the chip. Attention alone, split-key / rows kernel (us), rows x kept blocks:
+//       800 x 14 54 / 48, x 60 148 / 137, x 139 297 / 264; 1,790 x 60 251 / 249;
+//       2,000 x 60 290 / 269; 5,000 x 14 252 / 223, x 60 724 / 682;
 //   - are of like length, as far as the host can tell (a row of several times the
 //     mean would end the launch alone, that much later): whole rows over all
 //     blocks, with a top-k width (keep < n; a CDF list is n wide and padded). An
 //     explicit row order or a workspace does not enter, so that they leave a row's
-//     arithmetic as it is;
-//   - (wave kernel) leave room for eight kept lists beside the tiles of a CU's
-//     rows (160 KB).
+//     arithmetic as it is.
 // Past 900,000 rows the split-key kernel's smaller tail split keeps the workspace
 // inside the library's fixed array.
 //
@@ -1590,42 +1350,11 @@ hipError_t launch_shape(const Geom& g, const void* Q, const int32_t* sel, int ke
 // 30 48 / 41. Past one row per CU some CU has two, and the rows kernel is ahead.
 bool few_rows(int G) { return G <= kCus; }
 
-enum class Kernel64 { kSplitKey, kRows, kWave };
-Kernel64 kernel64(const Geom& g, int keep, int G) {
-    if (keep >= g.n || G > 900000) return Kernel64::kSplitKey;
-    if (g.d == 128) return G > 512 ? Kernel64::kRows : Kernel64::kSplitKey;
-    if (G >= 1800 && keep <= 896) return Kernel64::kWave;
-    return G >= 800 && (G <= 1024 || G >= 1200) ? Kernel64::kRows : Kernel64::kSplitKey;
+bool rows64(const Geom& g, int keep, int G) {
+    return g.d == 128 && keep < g.n && G > 512 && G <= 900000;
 }
 bool whole_rows(const Geom& g, const AttnPart& p) {
     return !p.acc && p.kv_lo == 0 && p.kv_hi == g.n && p.h_lo == 0 && p.h_hi == g.H;
-}
-
-template <int D>
-hipError_t launch_wave(const Geom& g, const void* Q, const int32_t* sel, int keep,
-                       const int32_t* slot_of, const void* Kp, const void* Vp, int64_t cap,
-                       float scale, const AttnPart& part, void* O, bool out_bf16, float* lse,
-                       hipStream_t s) {
-    constexpr int BLK = 64;
-    const int G = g.H * g.nq;
-    const float c2 = scale * kLog2e;
-    const size_t dyn = size_t(keep) * sizeof(int32_t);
-    TailPlan tp;
-    void* partials = nullptr;
-    if (hipError_t e = balanced_plan(attn_wave_kernel<D, true>, 64, dyn, g, part, sel, keep, G,
-                                     int64_t(BLK) * (D + 1) * 4, s, &tp, &partials);
-        e != hipSuccess)
-        return e;
-    const TailSpace ts = tp.k > 1 ? tail_space(partials, tp, G, D, BLK) : TailSpace{nullptr, nullptr};
-    const int grid = tp.first + (G - tp.first) * tp.k;
-    auto* kern = out_bf16 ? attn_wave_kernel<D, true> : attn_wave_kernel<D, false>;
-    kern<<<grid, 64, dyn, s>>>((const uint16_t*)Q, sel, slot_of, (const uint16_t*)Kp,
-                               (const uint16_t*)Vp, O, lse, g.L, g.n, g.i0, g.nq, keep, cap, c2, G,
-                               tp.first, tp.k, ts.part_o, ts.part_lse, tp.row_sort, part.order);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || tp.k < 2) return e;
-    return out_bf16 ? launch_tail_merge<D, BLK, true>(g, part, tp, G, ts.part_o, ts.part_lse, O, lse, s)
-                    : launch_tail_merge<D, BLK, false>(g, part, tp, G, ts.part_o, ts.part_lse, O, lse, s);
 }
 
 }  // namespace
@@ -1648,22 +1377,14 @@ hipError_t launch_attn_bf16(const Geom& g, const void* Q, const int32_t* sel, in
                                            O, out_bf16, lse, s);
     }
     if (g.block != 64 || (g.d != 64 && g.d != 128)) return hipErrorInvalidValue;
-    switch (whole_rows(g, part) ? kernel64(g, keep, g.H * g.nq) : Kernel64::kSplitKey) {
-        case Kernel64::kWave:
-            return launch_wave<64>(g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale, part, O,
-                                   out_bf16, lse, s);
-        case Kernel64::kRows:
-            return g.d == 64 ? launch_rows<64, 64>(g, Q, sel, keep, slot_of, Kp, Vp, capacity,
-                                                   scale, part, O, out_bf16, lse, s)
-                             : launch_rows<128, 64>(g, Q, sel, keep, slot_of, Kp, Vp, capacity,
-                                                    scale, part, O, out_bf16, lse, s);
-        case Kernel64::kSplitKey:
-            return g.d == 64 ? launch_shape<64, 64>(g, Q, sel, keep, slot_of, Kp, Vp, capacity,
-                                                    scale, part, O, out_bf16, lse, s)
-                             : launch_shape<128, 64>(g, Q, sel, keep, slot_of, Kp, Vp, capacity,
-                                                     scale, part, O, out_bf16, lse, s);
-    }
-    return hipErrorInvalidValue;
+    if (g.d == 64)
+        return launch_shape<64, 64>(g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale, part, O,
+                                    out_bf16, lse, s);
+    return whole_rows(g, part) && rows64(g, keep, g.H * g.nq)
+               ? launch_rows<128, 64>(g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale, part, O,
+                                      out_bf16, lse, s)
+               : launch_shape<128, 64>(g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale, part, O,
+                                       out_bf16, lse, s);
 }
 
 int64_t attn_tail_workspace_bytes(const Geom& g, int keep) {
@@ -1680,23 +1401,13 @@ int64_t attn_tail_workspace_bytes(const Geom& g, int keep) {
                         : resident_slots(attn_rows_kernel<128, 128, true, false>,
                                          CfgRows<128, 128>::THREADS, dyn);
     } else if (g.block == 64 && (g.d == 64 || g.d == 128)) {
-        switch (kernel64(g, keep, g.H * g.nq)) {
-            case Kernel64::kWave:
-                slots = resident_slots(attn_wave_kernel<64, true>, 64, dyn);
-                break;
-            case Kernel64::kRows:
-                slots = g.d == 64 ? resident_slots(attn_rows_kernel<64, 64, true, false>,
-                                                   CfgRows<64, 64>::THREADS, dyn)
-                                  : resident_slots(attn_rows_kernel<128, 64, true, false>,
-                                                   CfgRows<128, 64>::THREADS, dyn);
-                break;
-            case Kernel64::kSplitKey:
-                slots = g.d == 64 ? resident_slots(attn_bf16_kernel<64, 64, true>,
-                                                   Cfg<64, 64>::THREADS, dyn)
-                                  : resident_slots(attn_bf16_kernel<128, 64, true>,
-                                                   Cfg<128, 64>::THREADS, dyn);
-                break;
-        }
+        if (g.d == 64)
+            slots = resident_slots(attn_bf16_kernel<64, 64, true>, Cfg<64, 64>::THREADS, dyn);
+        else
+            slots = rows64(g, keep, g.H * g.nq)
+                        ? resident_slots(attn_rows_kernel<128, 64, true, false>,
+                                         CfgRows<128, 64>::THREADS, dyn)
+                        : resident_slots(attn_bf16_kernel<128, 64, true>, Cfg<128, 64>::THREADS, dyn);
     }
     if (slots <= 0) return 0;
     // the row order, then the tail pieces, which never outnumber the resident slots

@@ -90,9 +90,9 @@ int64_t attn_tail_workspace_bytes(const Geom& g, int keep);
 // Size of the fixed device array that the no-allocation attention entry point
 // uses in place of a workspace (per GPU). 36 MiB holds the largest tail splits on
 // a 256-CU part with their row orders: 512 slots x 128 x 129 x 4 bytes (128-token
-// blocks, d = 128) = 33.8 MB and up to 983,040 local rows, or 2,048 x 64 x 65 x 4
-// (64 x 64, one wave per row) = 34.1 MB and the 900,000 rows up to which that
-// kernel and the rows kernel for 64-token blocks are used.
+// blocks, d = 128) or 1,024 x 64 x 129 x 4 (64-token blocks) = 33.8 MB, and up to
+// 983,040 local rows (64-token blocks take those slots up to 900,000 rows, and half
+// of them past that).
 constexpr int64_t kScratchBytes = int64_t(36) << 20;
 
 // The bf16 attention of the whole geometry with the tail split's partials in

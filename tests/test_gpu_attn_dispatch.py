@@ -1,11 +1,10 @@
 """The bf16 attention kernels on both sides of the rules that pick one by the number
 of rows (128-token blocks: split-key up to 256 rows, rows kernel past them; 64-token
-blocks: split-key; rows kernel past 512 rows at d = 128 and for
-800 to 1,024 and 1,200 to 1,799 at d = 64; one wave per row from 1,800 at d = 64;
-whole top-k launches only): rows past a round of resident workgroups (tail split by
-the workspace), ragged ends, one to several hundred kept blocks, lists with skipped
-entries, float32 and bf16 output, an explicit row order (the same kernel, so the
-same bits). Bars: the parity suite's (bf16 2e-2 / 1e-3, lse 1e-4).
+blocks: split-key, and at d = 128 in whole top-k launches past 512 rows the rows
+kernel): rows past a round of resident workgroups (tail split by the workspace), ragged
+ends, one to several hundred kept blocks, lists with skipped entries, float32 and bf16
+output, an explicit row order (the same kernel, so the same bits). Bars: the parity
+suite's (bf16 2e-2 / 1e-3, lse 1e-4).
 """
 
 import numpy as np
@@ -24,11 +23,11 @@ CASES = [
     ((19, 2433, 128, 64, 12, 39), 1, 27),    # 513 rows, last block one key, diagonal only
     ((60, 1600, 128, 64, 0, 25), 24, 3),     # 1,500 rows: 476 past a round of 1,024
     ((5, 16500, 128, 64, 130, 258), 257, 3),  # 640 rows of 257 kept blocks
-    ((25, 2500, 64, 64, 8, 40), 3, 4),       # 800 rows: the rows kernel's first
-    ((47, 2500, 64, 64, 2, 40), 24, 3),      # 1,786 rows: its last, past a round of 1,536
+    ((25, 2500, 64, 64, 8, 40), 3, 4),       # 800 rows at d = 64
+    ((47, 2500, 64, 64, 2, 40), 24, 3),      # 1,786 rows: 762 past a round of 1,024
     ((48, 2433, 64, 64, 1, 39), 1, 38),      # 1,824 rows, last block one key, diagonal only
-    ((90, 1600, 64, 64, 0, 25), 24, 3),      # 2,250 rows: 202 past a round of 2,048
-    ((8, 16500, 64, 64, 20, 258), 257, 3),   # 1,904 rows of 257 kept blocks, two load rounds
+    ((90, 1600, 64, 64, 0, 25), 24, 3),      # 2,250 rows: 202 past two rounds
+    ((8, 16500, 64, 64, 20, 258), 257, 3),   # 1,904 rows of 257 kept blocks
     ((8, 4097, 128, 128, 1, 33), 6, 4),  # 256 rows, last block one key: split-key
     ((8, 4225, 64, 128, 2, 34), 1, 32),  # the same at d = 64, diagonal only
     ((1, 35000, 128, 128, 17, 274), 8, 9),  # 257 rows: rows kernel
