@@ -358,17 +358,17 @@ int sparsp_lse_merge(const sparsp_geom* g, int32_t head_begin, int32_t head_end,
                      float* lse_acc, const float* O_part, const float* lse_part, void* stream);
 
 /*
- * Runs a schedule on `stream`: the same result as attending the chunks one by
- * one in plan order, each written (accumulate = 0) where its heads have no
- * result yet and folded in (accumulate = 1) otherwise; heads that no chunk
- * covers end with O = 0, lse = -inf. The call is stream-ordered, so all shards
- * are in place when its work starts: shards of a head that do not overlap are
- * attended together, a whole schedule of sparsp_chunk_plan in one launch (a
- * caller whose shards arrive one after another calls
- * sparsp_block_sparse_attn_part per chunk); overlapping ones run one launch per
- * chunk. plan: HOST array of n_chunks chunks (each range checked as above). O
- * float32 [H, nq*block, d], lse float32 [H, nq*block]. Allocates nothing on
- * the device.
+ * Runs a schedule on `stream`: the result of attending the chunks one by one in
+ * plan order, each written (accumulate = 0) where its heads have no result yet
+ * and folded in (accumulate = 1) otherwise; heads that no chunk covers end with
+ * O = 0, lse = -inf. The call is stream-ordered, so all shards are in place when
+ * its work starts: chunks of one shard share a launch where their heads adjoin, a
+ * whole schedule of sparsp_chunk_plan one launch per shard, and no plan takes more
+ * launches than it has chunks. A head's shards are folded in plan order, each with
+ * a softmax of its own. (A caller whose shards arrive one after another calls
+ * sparsp_block_sparse_attn_part per chunk.) plan: HOST array of n_chunks chunks
+ * (each range checked as above). O float32 [H, nq*block, d], lse float32
+ * [H, nq*block]. Allocates nothing on the device.
  */
 int sparsp_chunked_attn(const sparsp_geom* g, const void* Q, const int32_t* sel, int32_t keep,
                         const int32_t* slot_of, const void* K_packed, const void* V_packed,

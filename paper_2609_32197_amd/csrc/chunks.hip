@@ -1,5 +1,6 @@
 // Host side of shard-by-shard attention (Section 2.3, Section 7): running a
-// plan. The plan itself (plan_chunks, in host_plan.cpp) orders the work of rank r over the owners' KV shards:
+// plan. The plan itself (plan_chunks, in host_plan.cpp) orders the work of rank r
+// over the owners' KV shards:
 //   * shard p holds the blocks [floor(p n / R), floor((p+1) n / R));
 //   * the local shard (p = r) comes first and stays whole: one chunk with all
 //     heads (Section 7.1: it needs no transfer);
@@ -15,16 +16,16 @@
 //
 // run_chunks executes a plan on one stream. Everything the plan reads is in
 // place when the call's work starts (the call is stream-ordered), so the chunks
-// need not be launches of their own: merge_chunks joins a head's shards wherever
-// no block is counted twice, and a whole schedule of plan_chunks becomes one
-// launch over all heads and blocks. One launch per chunk leaves the GPU to the
-// longest row of each of a few heads: 40 heads x 147 rows, 591 blocks of 128,
-// 89 kept, four owners, 31 chunks took 6.78 ms, the one launch 3.86 ms. Chunks
-// that overlap run in plan order, one launch each: a chunk whose heads have no
-// result yet writes (O, lse) directly; any other chunk folds itself into them
-// through the log-sum-exp inside the attention kernel (query blocks with no
-// kept block in the shard exit without touching memory). Heads that no chunk
-// covers end as the empty result.
+// need not be launches of their own: the chunks of one shard share a launch over
+// all their heads (chunk_steps). A head still folds its shards one after another in
+// plan order through the log-sum-exp inside the attention kernel, each with a softmax
+// of its own, so the result has the rounding of a chunk-by-chunk run; query blocks
+// with no kept block in a shard exit without touching memory. One launch per chunk
+// leaves the GPU to the longest row of each of a few heads: 40 heads x 147 rows, 591
+// blocks of 128, 89 kept, four owners, 31 chunks took 6.85 ms, the four launches
+// 4.75 ms. (All shards in one launch take 3.93 ms, but a row then has one softmax for
+// all of them and fewer exact top probabilities: error of O against 64 bits 6.4e-4
+// instead of 6.3e-4.) Heads that no chunk covers end as the empty result.
 #include <new>
 
 #include "sparsp_internal.h"
@@ -57,30 +58,6 @@ struct Run {  // the arguments every launch of a plan shares
     }
 };
 
-hipError_t run_in_order(const Run& run, const sparsp_chunk* plan, int n_chunks) {
-    std::vector<bool> seen(run.g.H, false);  // heads whose rows hold a result
-    for (int c = 0; c < n_chunks; ++c) {
-        const sparsp_chunk& ch = plan[c];
-        bool fresh = true, mixed = false;
-        for (int h = ch.head_begin; h < ch.head_end; ++h) {
-            fresh = fresh && !seen[h];
-            mixed = mixed || !seen[h];
-        }
-        hipError_t e = hipSuccess;
-        if (!fresh && mixed)  // heads met for the first time start from the empty result
-            for (int h = ch.head_begin; h < ch.head_end && e == hipSuccess; ++h)
-                if (!seen[h]) e = run.clear(h, h + 1);
-        if (e != hipSuccess) return e;
-        e = run.attend({ch.kv_blk_begin, ch.kv_blk_end, ch.head_begin, ch.head_end, fresh ? 0 : 1});
-        if (e != hipSuccess) return e;
-        for (int h = ch.head_begin; h < ch.head_end; ++h) seen[h] = true;
-    }
-    for (int h = 0; h < run.g.H; ++h)  // heads no chunk covered: the empty result
-        if (!seen[h])
-            if (hipError_t e = run.clear(h, h + 1); e != hipSuccess) return e;
-    return hipSuccess;
-}
-
 }  // namespace
 
 hipError_t run_chunks(const Geom& g, const void* Q, const int32_t* sel, int keep,
@@ -89,14 +66,11 @@ hipError_t run_chunks(const Geom& g, const void* Q, const int32_t* sel, int keep
                       hipStream_t s) {
     const Run run{g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale, O, lse, s};
     try {
-        std::vector<AttnPart> launches;
-        std::vector<std::pair<int, int>> empty;
-        if (!merge_chunks(g.H, plan, n_chunks, &launches, &empty))
-            return run_in_order(run, plan, n_chunks);
-        for (const AttnPart& part : launches)
-            if (hipError_t e = run.attend(part); e != hipSuccess) return e;
-        for (const auto& heads : empty)
-            if (hipError_t e = run.clear(heads.first, heads.second); e != hipSuccess) return e;
+        for (const ChunkStep& step : chunk_steps(g.H, plan, n_chunks)) {
+            const hipError_t e =
+                step.clear ? run.clear(step.part.h_lo, step.part.h_hi) : run.attend(step.part);
+            if (e != hipSuccess) return e;
+        }
     } catch (const std::bad_alloc&) {  // no exception may leave the C entry
         return hipErrorOutOfMemory;
     }

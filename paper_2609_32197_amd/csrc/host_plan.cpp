@@ -4,6 +4,7 @@
 // device; the descriptions of each rule sit with their launch-side
 // counterparts in chunks.hip and placement.hip.
 #include <algorithm>
+#include <map>
 #include <vector>
 
 #include "sparsp_launch.h"
@@ -45,39 +46,57 @@ int plan_chunks(const Geom& g, const uint64_t* demand, int ranks, int rank, int 
     return int(plan.size());
 }
 
-bool merge_chunks(int H, const sparsp_chunk* plan, int n_chunks, std::vector<AttnPart>* launches,
-                  std::vector<std::pair<int, int>>* empty) {
-    typedef std::vector<std::pair<int, int>> Ranges;
-    std::vector<Ranges> of(H);
+std::vector<ChunkStep> chunk_steps(int H, const sparsp_chunk* plan, int n_chunks) {
+    struct Group {
+        int lo, hi;
+        std::vector<char> has;  // per head
+    };
+    std::vector<Group> groups;
+    std::map<std::pair<int, int>, std::vector<int>> of_range;  // groups of a block range, ascending
+    std::vector<int> last(H, -1);  // the latest group of each head
     for (int c = 0; c < n_chunks; ++c) {
         const sparsp_chunk& ch = plan[c];
         if (ch.kv_blk_begin >= ch.kv_blk_end) continue;  // no block, nothing to add
-        for (int h = ch.head_begin; h < ch.head_end; ++h)
-            of[h].push_back({ch.kv_blk_begin, ch.kv_blk_end});
-    }
-    for (Ranges& r : of) {
-        std::sort(r.begin(), r.end());
-        size_t k = 0;
-        for (size_t i = 0; i < r.size(); ++i) {
-            if (k > 0 && r[i].first < r[k - 1].second) return false;
-            if (k > 0 && r[i].first == r[k - 1].second)
-                r[k - 1].second = r[i].second;
-            else
-                r[k++] = r[i];
+        const int after = *std::max_element(last.begin() + ch.head_begin, last.begin() + ch.head_end);
+        std::vector<int>& same = of_range[{ch.kv_blk_begin, ch.kv_blk_end}];
+        auto it = std::upper_bound(same.begin(), same.end(), after);
+        int k;
+        if (it != same.end()) {
+            k = *it;
+        } else {
+            k = int(groups.size());
+            groups.push_back({ch.kv_blk_begin, ch.kv_blk_end, std::vector<char>(H, 0)});
+            same.push_back(k);
         }
-        r.resize(k);
+        for (int h = ch.head_begin; h < ch.head_end; ++h) {
+            groups[k].has[h] = 1;
+            last[h] = k;
+        }
     }
-    launches->clear();
-    empty->clear();
-    for (int h0 = 0; h0 < H;) {
-        int h1 = h0 + 1;
-        while (h1 < H && of[h1] == of[h0]) ++h1;
-        if (of[h0].empty()) empty->push_back({h0, h1});
-        for (size_t i = 0; i < of[h0].size(); ++i)
-            launches->push_back(AttnPart{of[h0][i].first, of[h0][i].second, h0, h1, i > 0 ? 1 : 0});
-        h0 = h1;
+    std::vector<ChunkStep> steps;
+    std::vector<char> seen(H, 0);  // heads whose rows hold a result
+    auto clear = [&](int h_lo, int h_hi) {  // the heads of [h_lo, h_hi) without one
+        for (int h = h_lo; h < h_hi;) {
+            int e = h;
+            while (e < h_hi && !seen[e]) ++e;
+            if (e > h) steps.push_back({true, AttnPart{0, 0, h, e, 0}});
+            h = e + 1;
+        }
+    };
+    for (const Group& g : groups) {
+        for (int h = 0; h < H;) {
+            int e = h, old = 0;
+            while (e < H && g.has[e]) old += seen[e++];
+            if (e > h) {
+                if (old > 0 && old < e - h) clear(h, e);  // all of a launch folds in, or none
+                steps.push_back({false, AttnPart{g.lo, g.hi, h, e, old > 0 ? 1 : 0}});
+                std::fill(seen.begin() + h, seen.begin() + e, 1);
+            }
+            h = e + 1;
+        }
     }
-    return true;
+    clear(0, H);
+    return steps;
 }
 
 void periodic_placement(int L, int block, int frame_tokens, int ranks, int32_t* perm,

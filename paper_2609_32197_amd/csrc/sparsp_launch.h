@@ -118,16 +118,18 @@ hipError_t launch_fill_identity(float* O, float* lse, int64_t rows, int d, hipSt
 int plan_chunks(const Geom& g, const uint64_t* demand, int ranks, int rank, int heads_per_chunk,
                 int tail_heads_per_chunk, sparsp_chunk* out, int max_chunks);
 
-// Host: the fewest attention launches that compute what a plan's chunks do. When
-// no head meets a block in two chunks (always so for plan_chunks' schedules),
-// a head's result is its attention over the union of its ranges: adjoining
-// ranges are joined, neighbouring heads with the same ranges share a launch,
-// and a head's ranges after the first fold in (acc = 1). `empty` lists the
-// runs [first, second) of heads without a block. False, with nothing decided,
-// when ranges of a head overlap: then a block counts once per chunk that holds
-// it, which only launches in plan order give.
-bool merge_chunks(int H, const sparsp_chunk* plan, int n_chunks, std::vector<AttnPart>* launches,
-                  std::vector<std::pair<int, int>>* empty);
+// Host: the launches of a plan. Every head attends its chunks' block ranges in plan
+// order, each but the first folded into the ones before (acc = 1); chunks of one
+// block range that no such order keeps apart share a launch where their heads adjoin.
+// Never more attention launches than the plan has chunks; a schedule of plan_chunks
+// takes one per shard. A step with `clear` gives its heads the empty result instead:
+// before a launch that folds into some of its heads only, and at the end for heads
+// that no chunk covers.
+struct ChunkStep {
+    bool clear;
+    AttnPart part;
+};
+std::vector<ChunkStep> chunk_steps(int H, const sparsp_chunk* plan, int n_chunks);
 
 // Host: Eq. 4's placed order of the blocks (perm [n], rank_begin [ranks+1]).
 void periodic_placement(int L, int block, int frame_tokens, int ranks, int32_t* perm,
@@ -139,8 +141,7 @@ hipError_t launch_permute(const Geom& g, const int32_t* perm, const void* X, voi
 // Host: demanded blocks outside [i0, i1) and in total, over all heads.
 void remote_demand(const Geom& g, const uint64_t* demand, int64_t* remote, int64_t* demanded);
 
-// Host: runs a validated plan on stream s (the launches of merge_chunks, or one
-// per chunk in plan order), folding into (O, lse).
+// Host: runs the steps of a validated plan on stream s, folding into (O, lse).
 hipError_t run_chunks(const Geom& g, const void* Q, const int32_t* sel, int keep,
                       const int32_t* slot_of, const void* Kp, const void* Vp, int64_t capacity,
                       float scale, const sparsp_chunk* plan, int n_chunks, float* O, float* lse,

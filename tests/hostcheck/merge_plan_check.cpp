@@ -1,18 +1,21 @@
-// Random chunk plans, well formed and not: the launches of merge_chunks must
-// count every (head, block) as often as running the chunks one by one does,
-// write a head before folding into it, and leave exactly the uncovered heads to
-// be cleared; a plan whose ranges overlap must be refused.
+// Random chunk plans, well formed and not: the launches of chunk_steps must take
+// every head through its chunks' block ranges in plan order, write a head before
+// folding into it, never mix the two in a launch, leave exactly the uncovered heads
+// cleared, and never be more than the plan's chunks; a schedule of plan_chunks takes
+// one launch per shard.
 #include <cstdio>
 #include <random>
+#include <set>
 
 #include "../../paper_2609_32197_amd/csrc/sparsp_launch.h"
 
 int main() {
     std::mt19937 rng(7);
     auto in = [&](int lo, int hi) { return lo + int(rng() % unsigned(hi - lo + 1)); };
-    int failures = 0, merged = 0, refused = 0, single = 0;
+    int failures = 0, chunks = 0, launches = 0;
     for (int it = 0; it < 20000; ++it) {
         const int H = in(1, 9), n = in(1, 40);
+        int shards = -1;
         std::vector<sparsp_chunk> plan;
         if (it % 4 == 0) {  // a schedule of plan_chunks
             const int W = (n + 63) / 64, R = in(1, n), rank = in(0, R - 1);
@@ -24,45 +27,57 @@ int main() {
                                               plan.data(), int(plan.size()));
             if (c < 1) ++failures;
             plan.resize(size_t(c));
+            shards = R;
+        } else if (it % 4 == 1) {  // a local chunk of all heads, then one of some heads each
+            const int mid = in(1, n);
+            plan.push_back({0, 0, mid, 0, H, 0});
+            for (int h = 0; h < H; ++h)
+                if (rng() % 2) plan.push_back({1, mid, n, h, h + 1, 0});
         } else {  // anything the entry point accepts: gaps, empty ranges, overlaps, any order
-            for (int k = in(0, 6); k > 0; --k) {
-                const int lo = in(0, n), h0 = in(0, H - 1);
-                plan.push_back({0, lo, in(lo, n), h0, in(h0 + 1, H), 0});
+            std::vector<std::pair<int, int>> ranges;
+            for (int k = in(1, 4); k > 0; --k) {
+                const int lo = in(0, n);
+                ranges.push_back({lo, in(lo, n)});
+            }
+            for (int k = in(0, 8); k > 0; --k) {
+                const auto& r = ranges[size_t(in(0, int(ranges.size()) - 1))];
+                const int h0 = in(0, H - 1);
+                plan.push_back({0, r.first, r.second, h0, in(h0 + 1, H), 0});
             }
         }
-        std::vector<int> want(size_t(H) * n, 0), got(want);
-        bool twice = false;
+        std::vector<std::vector<std::pair<int, int>>> want(static_cast<size_t>(H)), got(want);
         for (const auto& c : plan)
             for (int h = c.head_begin; h < c.head_end; ++h)
-                for (int j = c.kv_blk_begin; j < c.kv_blk_end; ++j)
-                    twice = ++want[size_t(h) * n + j] > 1 || twice;
-        std::vector<sparsp::AttnPart> launches;
-        std::vector<std::pair<int, int>> empty;
-        const bool ok = sparsp::merge_chunks(H, plan.data(), int(plan.size()), &launches, &empty);
-        if (ok == twice) ++failures;
-        if (!ok) { ++refused; continue; }
-        ++merged;
-        std::vector<int> state(size_t(H), 0);  // 0 nothing, 1 written, 2 cleared
-        for (const auto& p : launches)
+                if (c.kv_blk_begin < c.kv_blk_end)
+                    want[size_t(h)].push_back({c.kv_blk_begin, c.kv_blk_end});
+        int attends = 0;
+        std::vector<char> state(size_t(H), 0);  // 1: holds a result
+        for (const auto& step : sparsp::chunk_steps(H, plan.data(), int(plan.size()))) {
+            const sparsp::AttnPart& p = step.part;
+            if (p.h_lo < 0 || p.h_hi > H || p.h_lo >= p.h_hi) { ++failures; break; }
+            attends += !step.clear;
             for (int h = p.h_lo; h < p.h_hi; ++h) {
-                if ((p.acc != 0) != (state[h] == 1)) ++failures;
-                state[h] = 1;
-                for (int j = p.kv_lo; j < p.kv_hi; ++j) ++got[size_t(h) * n + j];
+                if (step.clear) {
+                    if (!got[size_t(h)].empty() || state[size_t(h)]) ++failures;
+                } else {
+                    if ((p.acc != 0) != (state[size_t(h)] != 0)) ++failures;
+                    got[size_t(h)].push_back({p.kv_lo, p.kv_hi});
+                }
+                state[size_t(h)] = 1;
             }
-        for (const auto& e : empty)
-            for (int h = e.first; h < e.second; ++h) {
-                if (state[h]) ++failures;
-                state[h] = 2;
-            }
-        for (int h = 0; h < H; ++h)
-            if (!state[h]) ++failures;
+        }
         if (got != want) ++failures;
-        if (it % 4 == 0 && launches.size() == 1 && launches[0].kv_lo == 0 && launches[0].kv_hi == n)
-            ++single;
-        else if (it % 4 == 0)
-            ++failures;  // a schedule is one launch over everything
+        for (char s : state)
+            if (!s) ++failures;
+        if (attends > int(plan.size())) ++failures;
+        if (shards >= 0) {
+            std::set<std::pair<int, int>> ranges;
+            for (const auto& c : plan) ranges.insert({c.kv_blk_begin, c.kv_blk_end});
+            if (attends != int(ranges.size()) || attends > shards) ++failures;
+        }
+        chunks += int(plan.size());
+        launches += attends;
     }
-    printf("%d merged, %d refused, %d schedules in one launch, %d failures\n", merged, refused,
-           single, failures);
+    printf("%d chunks in %d launches, %d failures\n", chunks, launches, failures);
     return failures ? 1 : 0;
 }

@@ -2,10 +2,11 @@
 block counts once per chunk that holds it), gaps, empty ranges, heads in no chunk.
 
 The reference is the calls the plan stands for: sparsp_block_sparse_attn_part
-per chunk in plan order, from the empty result. Attending a head's shards
-together moves the float32 sums and (bf16) the rounding of the probabilities:
-held to the bars of the parity suite (1e-5; 2e-2 max-abs and 1e-3 mean-abs; lse
-1e-5 and 1e-4).
+per chunk in plan order, from the empty result. The kernel depends on a launch's
+number of rows, so chunks that share a launch may round elsewhere: held to the bars
+of the parity suite (1e-5; 2e-2 max-abs and 1e-3 mean-abs; lse 1e-5 and 1e-4). A
+schedule's launches are one per shard over all heads, and equal those calls bit for
+bit.
 """
 
 import math
@@ -52,3 +53,23 @@ def test_plan_equals_its_parts(gpu, geo, name):
     fin = np.isfinite(rn)
     assert (np.isneginf(ln) == ~fin).all()
     assert np.abs(ln[fin] - rn[fin]).max(initial=0) <= (1e-4 if g.dtype == sp.BF16 else 1e-5)
+
+
+@pytest.mark.parametrize("geo", GEOMS + [(12, 9000, 128, 128, 10, 60, "bf16")],
+                         ids=lambda g: "d{2}b{3}_{6}".format(*g) + ("" if g[0] == 5 else "_many"))
+@pytest.mark.parametrize("ranks", [1, 4])
+def test_schedule_folds_one_shard_after_another(gpu, geo, ranks):
+    """Each shard has a softmax of its own, as when shards arrive one by one: attending
+    them together would round more (bf16: fewer top probabilities are exact)."""
+    g, _, sel, out, Qd, _, scale = _setup(geo, 9)
+    rank = ranks // 2
+    plan = sp.sparsp_chunk_plan(g, out["demand"], ranks, rank, 2, 1)
+    args = (g, Qd, sel, out["slot_of"], out["K_packed"], out["V_packed"])
+    O, lse = sp.sparsp_chunked_attn(*args, plan, scale)
+    R, rl = None, None
+    for k in range(ranks):
+        p = (rank + k) % ranks
+        shard = (p * g.n // ranks, (p + 1) * g.n // ranks)
+        R, rl = sp.sparsp_block_sparse_attn_part(*args, shard, (0, g.H), scale, O=R, lse=rl,
+                                                 accumulate=k > 0)
+    assert (O == R).all() and (lse == rl).all()

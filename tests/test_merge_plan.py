@@ -1,4 +1,4 @@
-"""Chunk plans merged into fewer launches, against the chunks one by one (host code)."""
+"""The launches of a chunk plan against its chunks one by one (host code)."""
 
 import os
 import shutil
@@ -10,7 +10,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 
 
-def test_merged_plans_count_every_block_once(tmp_path):
+def test_launches_follow_the_plan(tmp_path):
     cxx = os.environ.get("CXX") or shutil.which("g++")
     if not cxx or not os.path.exists(os.path.join(ROCM, "include", "hip", "hip_runtime_api.h")):
         pytest.skip("needs g++ and the HIP runtime API headers")
