@@ -15,7 +15,7 @@
 // next V once its output product is done.
 //
 // attn_bf16_kernel (64-token blocks, and 128-token blocks with a row per CU at
-// most): 2*BLK/32 waves: wave w owns query group
+// most, see split_key128): 2*BLK/32 waves: wave w owns query group
 // w % (BLK/32) (32 queries) and key half w / (BLK/32) of every kept block
 // (BLK/2 keys). Each wave runs its own online softmax over its key halves
 // (running max, running sum, output accumulator) and the two halves of a
@@ -1228,6 +1228,13 @@ TailSpace tail_space(void* ws, const TailPlan& tp, int G, int D, int BLK) {
     return {o, o + pieces * BLK * D};
 }
 
+// Whether a launch may split each of its G rows in two (where it has the slots).
+bool can_split(const AttnPart& part, int G, int64_t piece_bytes) {
+    if (!part.ws || part.order || part.acc) return false;
+    const int64_t sb = row_sort_bytes(G);
+    return part.ws_bytes - (part.ws_bytes >= sb ? sb : 0) >= 2 * int64_t(G) * piece_bytes;
+}
+
 // The balanced launch's workspace holds the row order first (when it fits),
 // then the float32 partials of the tail split. Writes the order (one small
 // kernel on stream s) and returns the tail plan and where the partials go.
@@ -1341,14 +1348,30 @@ hipError_t launch_shape(const Geom& g, const void* Q, const int32_t* sel, int ke
 // Past 900,000 rows the split-key kernel's smaller tail split keeps the workspace
 // inside the library's fixed array.
 //
-// The kernel for 128-token blocks: with at most one row per CU the split-key
-// kernel's eight waves on a row fill its SIMDs, where the rows kernel's four leave
-// each with one wave. Attention alone, rows / split-key (us), d = 128, without a
-// workspace: 50 rows of 30 kept blocks 71 / 57, 190 of 30 72 / 60, 250 of 6 21 /
-// 21, of 30 72 / 67, 252 CDF rows 56 / 46; with one (which splits the rows over the
-// free slots) 190 of 6 31 / 23, 250 of 6 34 / 23, 100 of 30 43 / 42; d = 64, 250 of
-// 30 48 / 41. Past one row per CU some CU has two, and the rows kernel is ahead.
-bool few_rows(int G) { return G <= kCus; }
+// The kernel for 128-token blocks. With at most one row per CU the split-key kernel's
+// eight waves on a row fill its SIMDs, where the rows kernel's four leave each with
+// one wave. Attention alone, rows / split-key (us), d = 128: 50 rows of 30 kept blocks
+// 65 / 59, 190 of 30 67 / 61, of 90 183 / 159, 250 of 6 22 / 23, of 200 428 / 390;
+// d = 64, 250 of 30 49 / 41. Past one row per CU some CU has two, and the rows kernel is
+// ahead.
+// A workspace turns that around for long lists, since it splits each row over the
+// free slots: the rows kernel has 512 of them and the split-key kernel 256, which is
+// none to spare past 128 rows. `split` says that every row can be split in two or
+// more; then the rows kernel takes lists long enough to carry the pieces' merge. With
+// a workspace, rows / split-key kernel, d = 128 (d = 64 within 5%):
+//                     kept blocks   8     24     48    100    200
+//      72 rows (4 / 3 pieces)     1.09   1.11   1.11   1.12   1.12
+//     100 rows (4 / 2)            1.19   1.03   1.03   0.93   0.89
+//     130 rows (3 / 1)            1.24   0.91   0.77   0.68   0.64
+//     168 rows (3 / 1)            1.32   1.05   0.88   0.73   0.63
+//     200 rows (2 / 1)            1.30   1.10   1.01   0.87   0.84
+// No row is left whole there, so a workspace still leaves every unsplit row's bits as
+// they are without one.
+bool split_key128(int G, int keep, bool split) {
+    if (G > kCus) return false;
+    if (!split || G <= kCus / 3) return true;
+    return keep < (G > kCus / 2 && G <= 2 * kCus / 3 ? 24 : 48);
+}
 
 bool rows64(const Geom& g, int keep, int G) {
     return g.d == 128 && keep < g.n && G > 512 && G <= 900000;
@@ -1365,7 +1388,8 @@ hipError_t launch_attn_bf16(const Geom& g, const void* Q, const int32_t* sel, in
                             bool out_bf16, float* lse, hipStream_t s) {
     (void)hipGetLastError();
     if (g.block == 128 && (g.d == 64 || g.d == 128)) {
-        const bool few = few_rows((part.h_hi - part.h_lo) * g.nq);
+        const int G = (part.h_hi - part.h_lo) * g.nq;
+        const bool few = split_key128(G, keep, can_split(part, G, int64_t(g.block) * (g.d + 1) * 4));
         if (g.d == 64)
             return few ? launch_shape<64, 128>(g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale,
                                                part, O, out_bf16, lse, s)
@@ -1391,7 +1415,7 @@ int64_t attn_tail_workspace_bytes(const Geom& g, int keep) {
     const size_t dyn = size_t(keep) * sizeof(int32_t);
     int slots = 0;
     if (g.block == 128 && (g.d == 64 || g.d == 128)) {
-        const bool few = few_rows(g.H * g.nq);
+        const bool few = split_key128(g.H * g.nq, keep, true);
         if (g.d == 64)
             slots = few ? resident_slots(attn_bf16_kernel<64, 128, true>, Cfg<64, 128>::THREADS, dyn)
                         : resident_slots(attn_rows_kernel<64, 128, true, false>,
