@@ -1337,9 +1337,24 @@ hipError_t launch_shape(const Geom& g, const void* Q, const int32_t* sel, int ke
 // rows in flight); the rows kernel two waves and single buffers (1,024). Fewer waves a
 // row do less work around each score and each operand, but take a row longer, so they
 // need rows that
-//   - fill the chip. Attention alone, split-key / rows kernel (us), rows x kept blocks:
-//       800 x 14 54 / 48, x 60 148 / 137, x 139 297 / 264; 1,790 x 60 251 / 249;
-//       2,000 x 60 290 / 269; 5,000 x 14 252 / 223, x 60 724 / 682;
+//   - fill their last round: past a round of 1,024 the rest of the rows run nearly
+//     alone, which four waves a row bear better than two, and with a workspace the
+//     split-key kernel's smaller rounds leave it other rows to split. Rows kernel
+//     over split-key kernel, attention alone, without / with a workspace:
+//       rows, kept blocks:    8            24           60           139
+//         544              0.90 / 0.93  0.94 / 1.11  0.94 / 1.18  0.92 / 1.21
+//         768              0.91 / 0.75  1.01 / 0.89  0.99 / 0.94  0.96 / 0.98
+//         800              0.85 / 0.86  0.89 / 0.90  0.88 / 0.88  0.89 / 0.88
+//       1,024              0.85 / 0.87  0.90 / 0.92  0.92 / 0.92  0.92 / 0.92
+//       1,100              0.96 / 0.86  1.12 / 0.94  1.15 / 0.97  1.17 / 0.96
+//       1,500              0.98 / 1.11  1.10 / 1.07  1.09 / 0.99  1.08 / 0.95
+//       1,680              0.93 / 0.83  0.97 / 0.92  0.95 / 0.95  0.95 / 0.97
+//       2,000              0.95 / 0.96  0.94 / 0.95  0.92 / 0.92  0.92 / 0.93
+//       2,064              0.95 / 1.00  1.02 / 1.09  1.05 / 1.06  1.06 / 1.06
+//       2,560              0.95 / 1.05  1.03 / 1.04  1.00 / 1.00  1.00 / 0.98
+//       2,640              0.88 / 0.85  0.96 / 0.93  0.94 / 0.95  0.94 / 0.96
+//       3,136              0.90 / 0.94  0.99 / 1.03  1.00 / 0.99  1.02 / 0.94
+//       5,000              0.86 / 0.86  0.91 / 0.91  0.93 / 0.93  0.93 / 0.92
 //   - are of like length, as far as the host can tell (a row of several times the
 //     mean would end the launch alone, that much later): whole rows over all
 //     blocks, with a top-k width (keep < n; a CDF list is n wide and padded). An
@@ -1374,7 +1389,9 @@ bool split_key128(int G, int keep, bool split) {
 }
 
 bool rows64(const Geom& g, int keep, int G) {
-    return g.d == 128 && keep < g.n && G > 512 && G <= 900000;
+    if (g.d != 128 || keep >= g.n || G > 900000) return false;
+    if (G <= 768) return G > 512 && keep <= 8;
+    return G <= 1024 || (G >= 1664 && G <= 2000) || G > 2560;
 }
 bool whole_rows(const Geom& g, const AttnPart& p) {
     return !p.acc && p.kv_lo == 0 && p.kv_hi == g.n && p.h_lo == 0 && p.h_hi == g.H;

@@ -1,7 +1,7 @@
 """The bf16 attention kernels on both sides of the rules that pick one by the number
 of rows (128-token blocks: split-key up to 256 rows, rows kernel past them; 64-token
-blocks: split-key, and at d = 128 in whole top-k launches past 512 rows the rows
-kernel): rows past a round of resident workgroups (tail split by the workspace), ragged
+blocks: split-key, and at d = 128 in whole top-k launches the rows kernel at 513 to 768
+rows of 8 kept blocks or fewer, 769 to 1,024, 1,664 to 2,000 and past 2,560): rows past a round of resident workgroups (tail split by the workspace), ragged
 ends, one to several hundred kept blocks, lists with skipped entries, float32 and bf16
 output, an explicit row order (the same kernel, so the same bits). Bars: the parity
 suite's (bf16 2e-2 / 1e-3, lse 1e-4).
@@ -21,8 +21,14 @@ pytestmark = pytest.mark.gpu
 CASES = [
     ((16, 2433, 128, 64, 7, 39), 5, 4),      # 512 rows: the split-key kernel's last, ragged end
     ((19, 2433, 128, 64, 12, 39), 1, 27),    # 513 rows, last block one key, diagonal only
-    ((60, 1600, 128, 64, 0, 25), 24, 3),     # 1,500 rows: 476 past a round of 1,024
-    ((5, 16500, 128, 64, 130, 258), 257, 3),  # 640 rows of 257 kept blocks
+    ((60, 1600, 128, 64, 0, 25), 24, 3),     # 1,500 rows: split-key, 476 past a round of 512
+    ((5, 16500, 128, 64, 130, 258), 257, 3),  # 640 rows of 257 kept blocks: split-key
+    ((12, 4200, 128, 64, 2, 66), 8, 3),      # 768 rows: the rows kernel with its longest list
+    ((12, 4200, 128, 64, 2, 66), 9, 3),      # and one block more: split-key
+    ((14, 3521, 128, 64, 1, 56), 24, 3),     # 770 rows, last block one key: rows kernel
+    ((4, 16500, 128, 64, 50, 258), 257, 3),  # 832 rows of 257 kept blocks, three load rounds
+    ((26, 4100, 128, 64, 1, 65), 24, 3),     # 1,664 rows: rows kernel, 640 past its round
+    ((50, 4100, 128, 64, 1, 65), 14, 2),     # 3,200 rows: rows kernel, 128 past three rounds
     ((25, 2500, 64, 64, 8, 40), 3, 4),       # 800 rows at d = 64
     ((47, 2500, 64, 64, 2, 40), 24, 3),      # 1,786 rows: 762 past a round of 1,024
     ((48, 2433, 64, 64, 1, 39), 1, 38),      # 1,824 rows, last block one key, diagonal only
