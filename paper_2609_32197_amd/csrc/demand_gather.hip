@@ -8,20 +8,19 @@
 //                block's slot = head_off[h] + rank of the block in D_h, which
 //                fills slot_of and gather_blk. Both ends of an exchange could
 //                derive these offsets locally from the same bitsets.
-// gather_stream_kernel / gather_blocks_kernel / gather_kernel
+// gather_stream_kernel / gather_slots_kernel / gather_kernel
 //                copy the demanded blocks, reading the slot count and the
-//                slot -> (head, block) map (head_off, gather_blk) or block ->
-//                slot (slot_of) on the device, so the grid is fixed and no host
-//                round trip is needed.
+//                slot -> (head, block) map (head_off, gather_blk) on the device,
+//                so the grid is fixed and no host round trip is needed.
 //                K blocks are copied with 16-byte loads and stores; V blocks
 //                are written transposed ([d, block]) so the attention kernel
 //                reads V^T MFMA operands with contiguous 16-byte loads (each
 //                thread moves a VEC x VEC sub-block and transposes it in
 //                registers). Rows past L are written as zero. The streaming
 //                kernel strides over the packed buffers as flat arrays (blocks
-//                of whole 16 KB steps), the blocked one gives a workgroup a few
-//                blocks (smaller ones in whole 4 KB groups); the windowed kernel
-//                walks the slots in windows (any other shape).
+//                in whole 4 KB groups), the slots kernel gives a workgroup a few
+//                slots (small ones of those that are not whole 16 KB steps); the
+//                windowed kernel walks the slots in windows (any other shape).
 #include "sparsp_internal.h"
 
 namespace sparsp {
@@ -247,15 +246,15 @@ __global__ __launch_bounds__(256) void gather_kernel(const int32_t* __restrict__
 // over the packed buffers as flat arrays, so at any moment the workgroups
 // read and write neighbouring pieces of memory, the way a plain streaming
 // copy does; loads and stores are non-temporal (the data is used once, by
-// the next kernel). K moves in steps of 1,024 16-byte chunks and V in groups
-// of 64 VEC x VEC sub-blocks (one wave); neither straddles two slots, which
-// holds when a K block is a multiple of 1,024 chunks and a V block of 64
+// the next kernel). K moves in groups of 256 16-byte chunks and V in groups
+// of 64 VEC x VEC sub-blocks (one wave); a group never straddles two slots,
+// which holds when a K block is a multiple of 256 chunks and a V block of 64
 // sub-blocks with 8 | block / VEC and 8 | d / VEC. The V transpose places
 // eight consecutive sub-blocks of a row (8 VEC tokens) in eight consecutive
 // lanes, so every store instruction writes whole 128-byte row segments.
 constexpr int kStreamGrid = 512;
 
-template <bool BF16>
+template <bool BF16, bool WHOLE>  // WHOLE: a K block is a multiple of 1,024 chunks
 __global__ __launch_bounds__(256) void gather_stream_kernel(
     const int32_t* __restrict__ head_off, const int32_t* __restrict__ gather_blk,
     const char* __restrict__ K, const char* __restrict__ V, char* __restrict__ Kp,
@@ -280,20 +279,51 @@ __global__ __launch_bounds__(256) void gather_stream_kernel(
     const uint32_t k_total = uint32_t(total_slots) * uint32_t(k_items);
     for (uint32_t e0 = blockIdx.x * 1024u; e0 < k_total; e0 += gridDim.x * 1024u) {
         uint4 x[4];
-        const int slot = int(e0 / uint32_t(k_items));  // the step lies in one slot
-        const int cbase = int(e0 - uint32_t(slot) * uint32_t(k_items));
-        while (slot >= hoff[h + 1]) ++h;
-        const int tok0 = gather_blk[slot] * block;
-        const int valid = min(block, L - tok0) * row_chunks;
-        const char* src = K + (int64_t(h % H_src) * L + tok0) * d * ES;
-        char* dst = Kp + int64_t(e0) * 16;
+        int64_t dst_off[4];
+        // slot and in-slot offset of each group; a group of 256 chunks never
+        // straddles slots and k_items >= 256, so the next group wraps at most once
+        int slot = int(e0 / uint32_t(k_items));
+        int cbase = int(e0 - uint32_t(slot) * uint32_t(k_items));
+        if constexpr (WHOLE) {  // the step lies in one slot
+            while (slot >= hoff[h + 1]) ++h;
+            const int tok0 = gather_blk[slot] * block;
+            const int valid = min(block, L - tok0) * row_chunks;
+            const char* src = K + (int64_t(h % H_src) * L + tok0) * d * ES;
+            char* dst = Kp + int64_t(e0) * 16;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int c = cbase + i * 256 + tid;
-            x[i] = c < valid ? load_nt(src + int64_t(c) * 16) : make_uint4(0, 0, 0, 0);
+            for (int i = 0; i < 4; ++i) {
+                const int c = cbase + i * 256 + tid;
+                x[i] = c < valid ? load_nt(src + int64_t(c) * 16) : make_uint4(0, 0, 0, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) store_nt(dst + (i * 256 + tid) * 16, x[i]);
+            continue;
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) store_nt(dst + (i * 256 + tid) * 16, x[i]);
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t eg = e0 + i * 256u;  // first chunk of the group
+            if (i > 0) {
+                cbase += 256;
+                if (cbase >= k_items) {
+                    cbase -= k_items;
+                    ++slot;
+                }
+            }
+            dst_off[i] = -1;
+            x[i] = make_uint4(0, 0, 0, 0);
+            if (eg < k_total) {
+                const int c = cbase + tid;
+                while (slot >= hoff[h + 1]) ++h;
+                const int tok0 = gather_blk[slot] * block;
+                const int valid = min(block, L - tok0) * row_chunks;
+                if (c < valid)
+                    x[i] = load_nt(K + (int64_t(h % H_src) * L + tok0) * d * ES + int64_t(c) * 16);
+                dst_off[i] = int64_t(eg + tid) * 16;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (dst_off[i] >= 0) store_nt(Kp + dst_off[i], x[i]);
     }
 
     // V: step u covers sub-blocks [256 u, 256 u + 256) of the flat V buffer,
@@ -328,71 +358,85 @@ __global__ __launch_bounds__(256) void gather_stream_kernel(
     }
 }
 
-// Blocked form, for shapes whose K blocks are whole groups of 256 chunks but not
-// whole steps of 1,024 (bf16 64 x 64, float32 64 x 96, ...), where the flat walk
-// would look a slot up for every group. A workgroup takes `per` consecutive
-// blocks of one head, as many as give each thread a full pass, and finds their
-// slots in slot_of; blockIdx.z picks K (VEC chunks per thread and pass) or V (one
-// transposed sub-block), each a stream of its own. 278 blocks x 48 heads of bf16
-// 64 x 64: 80.1 us as the flat walk, 75.8; 75 x 12 of float32 64 x 96: 23.5 and
-// 16.8 us. On whole steps the flat walk stays ahead (591 x 40 of bf16 128 x 128,
-// 82% demanded: 421 against 448 us).
-constexpr int kMaxPer = 8;  // blocks per workgroup, at most: 256 * VEC / 256
+// The same copy by slots, for small blocks that are whole groups of 256 chunks but
+// not whole steps of 1,024 (float32 64 x 96, bf16 64 x 64, ...), where the flat walk
+// looks a slot up for every group. A workgroup takes `per` consecutive slots, as many
+// as give each thread a full pass of VEC chunks, and finds their heads and blocks at
+// once; blockIdx.y picks K or V (one transposed sub-block a thread and pass), each a
+// stream of its own. Workgroups past the last slot leave at once, so a sparse demand
+// costs what it holds. Flat walk / by slots (us, the whole call), 280 blocks x 40 heads,
+// 10% and 80% of them demanded: float32 32 x 32 (256 chunks) 31 / 14 and 45 / 33,
+// 64 x 96 (1,536) 39 / 30 and 192 / 156, 160 x 96 (3,840) 72 / 63 and 456 / 418;
+// bf16 64 x 64 (512) 31 / 16 and 60 / 57. Past that a slot is too much for one
+// workgroup: float32 224 x 96 (5,376), 64 blocks x 40 heads, 10% 35 / 38; 992 x 96
+// (23,808), 64 x 8, 36 / 73; and bf16 64 x 192 (1,536), 1,200 x 40, 80% 653 / 690, where
+// 256 threads take eight chunks each and the flat walk streams better.
+constexpr int kMaxPer = 8;  // slots per workgroup, at most: 256 * VEC / 256
 
 template <bool BF16>
-__global__ __launch_bounds__(256) void gather_blocks_kernel(
-    const int32_t* __restrict__ slot_of, const char* __restrict__ K, const char* __restrict__ V,
-    char* __restrict__ Kp, char* __restrict__ Vp, int n, int L, int d, int block, int H_src, int lo,
-    int hi, int per) {
+__global__ __launch_bounds__(256) void gather_slots_kernel(
+    const int32_t* __restrict__ head_off, const int32_t* __restrict__ gather_blk,
+    const char* __restrict__ K, const char* __restrict__ V, char* __restrict__ Kp,
+    char* __restrict__ Vp, int H, int L, int d, int block, int H_src, int per) {
     constexpr int ES = BF16 ? 2 : 4;
     constexpr int VEC = 16 / ES;
-    __shared__ int32_t slots[kMaxPer];
+    __shared__ int32_t hoff[kMaxHeads + 1];
+    __shared__ int64_t src_at[kMaxPer];  // byte offset of the block's first row in K and V
+    __shared__ int32_t cnts[kMaxPer];    // its valid token rows
     const int tid = threadIdx.x;
-    const int h = blockIdx.y, j0 = lo + blockIdx.x * per;
-    const int nb = min(per, hi - j0);
-    if (tid < nb) slots[tid] = slot_of[int64_t(h) * n + j0 + tid];
+    const int s0 = blockIdx.x * per;
+    const int total = head_off[H];
+    if (s0 >= total) return;
+    const int ns = min(per, total - s0);
+    const int j = tid < ns ? gather_blk[s0 + tid] : 0;
+    for (int i = tid; i <= H; i += 256) hoff[i] = head_off[i];
+    __syncthreads();
+    if (tid < ns) {
+        int lo = 0, hi = H;  // hoff[lo] <= slot < hoff[hi]
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (hoff[mid] <= s0 + tid) lo = mid;
+            else hi = mid;
+        }
+        const int tok0 = j * block;
+        src_at[tid] = (int64_t(lo % H_src) * L + tok0) * d * ES;
+        cnts[tid] = min(block, L - tok0);
+    }
     __syncthreads();
     const int row_chunks = d / VEC;
     const int64_t blk_bytes = int64_t(block) * d * ES;
-    const int64_t src0 = (int64_t(h % H_src) * L + int64_t(j0) * block) * d * ES;  // block j0's first row
-    if (blockIdx.z == 0) {
+    if (blockIdx.y == 0) {
         const int k_items = block * row_chunks;  // chunks per K block, a multiple of 256
-        for (int base = 0; base < nb * k_items; base += 256 * VEC) {
+        char* dst = Kp + s0 * blk_bytes;
+        for (int base = 0; base < ns * k_items; base += 256 * VEC) {
             uint4 x[VEC];
-            char* dst[VEC];
 #pragma unroll
             for (int u = 0; u < VEC; ++u) {
-                const int e0 = base + u * 256;  // first chunk of the group: one block's
+                const int e0 = base + u * 256;  // first chunk of the group: one slot's
                 const int b = e0 / k_items;
-                dst[u] = nullptr;
+                const int c = e0 - b * k_items + tid;
                 x[u] = make_uint4(0, 0, 0, 0);
-                if (b < nb && slots[b] >= 0) {
-                    const int c = e0 - b * k_items + tid;
-                    const int valid = min(block, L - (j0 + b) * block) * row_chunks;
-                    if (c < valid) x[u] = load_nt(K + src0 + b * blk_bytes + int64_t(c) * 16);
-                    dst[u] = Kp + slots[b] * blk_bytes + int64_t(c) * 16;
-                }
+                if (b < ns && c < cnts[b] * row_chunks) x[u] = load_nt(K + src_at[b] + int64_t(c) * 16);
             }
 #pragma unroll
             for (int u = 0; u < VEC; ++u)
-                if (dst[u]) store_nt(dst[u], x[u]);
+                if (base + u * 256 < ns * k_items)
+                    store_nt(dst + int64_t(base + u * 256 + tid) * 16, x[u]);
         }
         return;
     }
     const int kgroups = block / VEC / 8;
     const int v_items = (block / VEC) * (d / VEC);  // sub-blocks per V block, a multiple of 64
     const int wave0 = __builtin_amdgcn_readfirstlane(tid & ~63);
-    for (int t0 = wave0; t0 < nb * v_items; t0 += 256) {
+    for (int t0 = wave0; t0 < ns * v_items; t0 += 256) {
         const int b = t0 / v_items;
-        const int slot = slots[b];
-        if (slot < 0) continue;
         // Sub-block t of a block as in the streaming kernel.
         const int grp = (t0 - b * v_items) >> 6;
         const int kb = (tid & 7) + 8 * (grp % kgroups);
         const int db = ((tid >> 3) & 7) + 8 * (grp / kgroups);
-        const int cnt = min(block, L - (j0 + b) * block);
-        const char* src = V + src0 + b * blk_bytes;
-        char* dst = Vp + slot * blk_bytes;
+        const int cnt = cnts[b];
+        const char* src = V + src_at[b];
+        char* dst = Vp + (s0 + b) * blk_bytes;
         uint4 rows[VEC], cols[VEC];
 #pragma unroll
         for (int rr = 0; rr < VEC; ++rr) {
@@ -419,32 +463,32 @@ hipError_t launch_demand_gather(const Geom& g, const uint64_t* mask, const void*
     offsets_kernel<<<g.H, 256, 0, s>>>(demand, g.H, g.n, g.W, head_off, slot_of, gather_blk);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_gather(g, g.H, 0, g.n, head_off, slot_of, gather_blk, K, V, Kp, Vp, s);
+    return launch_gather(g, g.H, head_off, gather_blk, K, V, Kp, Vp, s);
 }
 
-// Packed copies for n_vheads (virtual) heads, whose slots all belong to blocks of
-// [lo, hi): virtual head v reads K/V head v % g.H.
-hipError_t launch_gather(const Geom& g, int n_vheads, int lo, int hi, const int32_t* head_off,
-                         const int32_t* slot_of, const int32_t* gather_blk, const void* K,
-                         const void* V, void* Kp, void* Vp, hipStream_t s) {
+// Packed copies of n_vheads (virtual) heads: virtual head v reads K/V head v % g.H.
+hipError_t launch_gather(const Geom& g, int n_vheads, const int32_t* head_off,
+                         const int32_t* gather_blk, const void* K, const void* V, void* Kp,
+                         void* Vp, hipStream_t s) {
     const int vec = g.bf16 ? 8 : 4;
     const int v_items = (g.d / vec) * (g.block / vec);  // V sub-blocks per slot
     const int k_items = g.block * (g.d / vec);            // K chunks per slot
     const int64_t max_slots = int64_t(n_vheads) * g.n;
     if (k_items % 256 == 0 && v_items % 64 == 0 && (g.block / vec) % 8 == 0 &&
         (g.d / vec) % 8 == 0) {
-        if (k_items % 1024 != 0) {
-            if (hi <= lo) return hipSuccess;  // no block, no slot
+        const bool whole = k_items % 1024 == 0;
+        if (!whole && k_items <= (g.bf16 ? 1024 : 4096)) {
             const int per = max(1, 256 * vec / k_items);
-            auto* kern = g.bf16 ? gather_blocks_kernel<true> : gather_blocks_kernel<false>;
-            kern<<<dim3((hi - lo + per - 1) / per, n_vheads, 2), 256, 0, s>>>(
-                slot_of, (const char*)K, (const char*)V, (char*)Kp, (char*)Vp, g.n, g.L, g.d,
-                g.block, g.H, lo, hi, per);
+            auto* kern = g.bf16 ? gather_slots_kernel<true> : gather_slots_kernel<false>;
+            kern<<<dim3(unsigned((max_slots + per - 1) / per), 2), 256, 0, s>>>(
+                head_off, gather_blk, (const char*)K, (const char*)V, (char*)Kp, (char*)Vp, n_vheads,
+                g.L, g.d, g.block, g.H, per);
             return hipGetLastError();
         }
         // The streaming kernel's flat chunk indices must fit 31 bits.
         if (max_slots * k_items + int64_t(kStreamGrid) * 1024 < (int64_t(1) << 31)) {
-            auto* kern = g.bf16 ? gather_stream_kernel<true> : gather_stream_kernel<false>;
+            auto* kern = g.bf16 ? (whole ? gather_stream_kernel<true, true> : gather_stream_kernel<true, false>)
+                                : (whole ? gather_stream_kernel<false, true> : gather_stream_kernel<false, false>);
             kern<<<kStreamGrid, 256, 0, s>>>(head_off, gather_blk, (const char*)K, (const char*)V,
                                              (char*)Kp, (char*)Vp, n_vheads, g.L, g.d, g.block, g.H);
             return hipGetLastError();
@@ -509,7 +553,7 @@ hipError_t launch_pack_for_consumers(const Geom& g, const uint64_t* demands, int
     offsets_kernel<<<nv, 256, 0, s>>>(provide, nv, g.n, g.W, head_off, slot_of, gather_blk);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_gather(g, nv, lo, hi, head_off, slot_of, gather_blk, K, V, Kp, Vp, s);
+    return launch_gather(g, nv, head_off, gather_blk, K, V, Kp, Vp, s);
 }
 
 }  // namespace sparsp

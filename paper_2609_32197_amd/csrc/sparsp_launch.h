@@ -62,11 +62,10 @@ struct AttnPart {
     int64_t ws_bytes = 0;
 };
 
-// Packed K/V copies of n_vheads virtual heads (virtual head v reads head v % g.H)
-// whose slots belong to blocks of [lo, hi).
-hipError_t launch_gather(const Geom& g, int n_vheads, int lo, int hi, const int32_t* head_off,
-                         const int32_t* slot_of, const int32_t* gather_blk, const void* K,
-                         const void* V, void* Kp, void* Vp, hipStream_t s);
+// Packed K/V copies of n_vheads virtual heads (virtual head v reads head v % g.H).
+hipError_t launch_gather(const Geom& g, int n_vheads, const int32_t* head_off,
+                         const int32_t* gather_blk, const void* K, const void* V, void* Kp,
+                         void* Vp, hipStream_t s);
 
 // Producer p's packing for every other rank (demands: device [ranks, H, W]).
 hipError_t launch_pack_for_consumers(const Geom& g, const uint64_t* demands, int ranks,

@@ -31,8 +31,8 @@ hipError_t launch_cdf(const Geom&, const float*, float, const GlobalSet&, uint64
 hipError_t launch_demand_gather(const Geom&, const uint64_t*, const void*, const void*,
                                 uint64_t*, int32_t*, int32_t*, int32_t*, void*, void*,
                                 hipStream_t) { return launched(); }
-hipError_t launch_gather(const Geom&, int, int, int, const int32_t*, const int32_t*,
-                         const int32_t*, const void*, const void*, void*, void*, hipStream_t) { return launched(); }
+hipError_t launch_gather(const Geom&, int, const int32_t*, const int32_t*, const void*,
+                         const void*, void*, void*, hipStream_t) { return launched(); }
 hipError_t launch_pack_for_consumers(const Geom&, const uint64_t*, int, int, int, int,
                                      const void*, const void*, uint64_t*, int32_t*, int32_t*,
                                      int32_t*, void*, void*, hipStream_t) { return launched(); }

@@ -1,7 +1,8 @@
-"""The blocked gather kernel at the edges of its workgroups: one block or several
-per workgroup, blocks past the end of the last one, heads whose blocks are all or
-none demanded, ragged last blocks; for the demand gather and for the per-consumer
-packing (a shard that starts and ends inside a workgroup). Bit-exact."""
+"""The gather by slots at the edges of its workgroups (one slot or several each, slots
+past the end of the last one, heads whose blocks are all or none demanded, more heads
+than a workgroup has threads, ragged last blocks) and the flat walk of blocks that are
+no whole 16 KB steps; for the demand gather and for the per-consumer packing (a shard
+that starts and ends inside a workgroup). Bit-exact."""
 
 import numpy as np
 import pytest
@@ -13,9 +14,12 @@ from tests.test_gpu_kernels import _rand_inputs
 
 pytestmark = pytest.mark.gpu
 
-# (H, n, tail, d, block, dtype): K blocks of 256, 512, 1,536, 2,304 and 768 16-byte chunks
+# (H, n, tail, d, block, dtype): K blocks of 256, 512, 1,536 (bf16: flat walk), 2,304, 768,
+# 512, 3,840, 5,376 (flat walk), 30,720 (flat walk) and, in 300 heads, 256 16-byte chunks
 CASES = [(3, 9, 5, 32, 32, "f32"), (2, 21, 64, 64, 64, "bf16"), (3, 13, 1, 192, 64, "bf16"),
-         (2, 4, 50, 96, 96, "f32"), (2, 1, 7, 96, 32, "f32")]
+         (2, 4, 50, 96, 96, "f32"), (2, 1, 7, 96, 32, "f32"),
+         (5, 1, 3, 64, 64, "bf16"), (2, 9, 159, 96, 160, "f32"), (2, 5, 200, 96, 224, "f32"),
+         (1, 4, 900, 64, 3840, "bf16"), (300, 5, 31, 32, 32, "f32")]
 
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "n{1}d{3}b{4}_{5}".format(*c))
