@@ -207,8 +207,11 @@ int64_t sparsp_attn_workspace_bytes(const sparsp_geom* g, int32_t keep);
  * and a second kernel merges each row's pieces through the log-sum-exp: the
  * online-softmax merge of Section 2.3. k shrinks to fit workspace_bytes.
  *   - Rows outside the last round are computed exactly as by
- *     sparsp_block_sparse_attn, bit for bit; split rows differ from it by
- *     float32 rounding only.
+ *     sparsp_block_sparse_attn, bit for bit; a split row's pieces have running
+ *     maxima of their own, so it differs from that call by rounding (float32
+ *     sums, bf16 probabilities).
+ *   - Where R <= 256 rows of 128-token blocks are all split, P is that of the
+ *     kernel whose split fills the GPU better for this keep.
  *   - workspace: caller-owned device memory, 16-byte aligned; contents on entry
  *     do not matter and on return are unspecified. Calls that share a workspace
  *     must not overlap. A workspace too small for the row order leaves the

@@ -80,7 +80,7 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ sco
         int gt = 0;
 #pragma unroll
         for (int s = 0; s < S; ++s) gt += popc64(__ballot(cand[s] && key[s] > T));
-        need = k - gt;  // >= 1 by the choice of T
+        need = k - gt;  // 0 where the search ended early above every tie
     }
 
     uint64_t* mrow = mask + int64_t(row) * W;
