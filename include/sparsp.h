@@ -365,8 +365,8 @@ int sparsp_lse_merge(const sparsp_geom* g, int32_t head_begin, int32_t head_end,
  * plan order, each written (accumulate = 0) where its heads have no result yet
  * and folded in (accumulate = 1) otherwise; heads that no chunk covers end with
  * O = 0, lse = -inf. The call is stream-ordered, so all shards are in place when
- * its work starts: chunks of one shard share a launch where their heads adjoin, a
- * whole schedule of sparsp_chunk_plan one launch per shard, and no plan takes more
+ * its work starts: a bf16 schedule of sparsp_chunk_plan over up to 16 ranks is one
+ * launch, a float32 one a launch per shard, and no plan takes more attention
  * launches than it has chunks. A head's shards are folded in plan order, each with
  * a softmax of its own. (A caller whose shards arrive one after another calls
  * sparsp_block_sparse_attn_part per chunk.) plan: HOST array of n_chunks chunks

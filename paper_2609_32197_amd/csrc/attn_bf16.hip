@@ -301,7 +301,15 @@ __device__ __forceinline__ void copy_tile(const uint16_t* tile, int tile_bytes, 
 #endif
 }
 
-template <int D, int BLK, bool OUT_BF16>
+// SHARDS: the row attends several block ranges one after another, each with a softmax
+// of its own and folded into (O, lse) as a launch of its own would fold it. (What a
+// range's fold reads of the one before, the lane itself wrote, or, of lse, a lane of its
+// workgroup before the barriers of the list's compaction.)
+struct NoShards {};
+template <bool SHARDS>
+using ShardsArg = std::conditional_t<SHARDS, Shards, NoShards>;
+
+template <int D, int BLK, bool OUT_BF16, bool SHARDS>
 __global__ __launch_bounds__(4 * BLK) __attribute__((amdgpu_waves_per_eu(2)))
 void attn_bf16_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict__ sel,
                       const int32_t* __restrict__ slot_of, const uint16_t* __restrict__ Kp,
@@ -311,7 +319,7 @@ void attn_bf16_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
                       int h_lo, int n_heads, int acc, int remap,
                       const int32_t* __restrict__ order, int tail_first, int tail_k,
                       float* __restrict__ part_o, float* __restrict__ part_lse,
-                      const int32_t* __restrict__ row_sort) {
+                      const int32_t* __restrict__ row_sort, ShardsArg<SHARDS> shards) {
     using C = Cfg<D, BLK>;
     // [buffer][K tile | V tile]; reused for the final merge.
     __shared__ __attribute__((aligned(16))) uint16_t lds[2][2][C::TILE];
@@ -342,303 +350,318 @@ void attn_bf16_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
     // Resolve the kept list once: sel -> slot (and partial-block flag), keeping
     // only the usable entries inside [kv_lo, kv_hi), compacted in list order.
     __shared__ int wave_cnt[C::NW];
-    int nkeep = 0;
-    {
-        const int32_t* srow = sel + (int64_t(h) * nq + r) * keep;
-        const int32_t* hslot = slot_of + int64_t(h) * n;
-        const bool ragged = (L % BLK) != 0;
-        for (int base = 0; base < keep; base += C::THREADS) {
-            const int jj = base + tid;
-            int code = -1;
-            if (jj < keep) {
-                const int j = srow[jj];
-                if (j >= kv_lo && j < kv_hi && j >= 0 && j < n) {
-                    const int sl = hslot[j];
-                    if (sl >= 0 && sl < capacity && sl < (1 << 30))
-                        code = 2 * sl + ((ragged && j == n - 1) ? 1 : 0);
+    int n_shards = 1;
+    if constexpr (SHARDS) n_shards = shards.n;
+    for (int shard = 0; shard < n_shards; ++shard) {
+        if constexpr (SHARDS) {
+            kv_lo = shards.lo[shard];
+            kv_hi = shards.hi[shard];
+            if (shard > 0) acc = 1;
+        }
+        int nkeep = 0;
+        {
+            const int32_t* srow = sel + (int64_t(h) * nq + r) * keep;
+            const int32_t* hslot = slot_of + int64_t(h) * n;
+            const bool ragged = (L % BLK) != 0;
+            for (int base = 0; base < keep; base += C::THREADS) {
+                const int jj = base + tid;
+                int code = -1;
+                if (jj < keep) {
+                    const int j = srow[jj];
+                    if (j >= kv_lo && j < kv_hi && j >= 0 && j < n) {
+                        const int sl = hslot[j];
+                        if (sl >= 0 && sl < capacity && sl < (1 << 30))
+                            code = 2 * sl + ((ragged && j == n - 1) ? 1 : 0);
+                    }
                 }
+                const uint64_t bal = __ballot(code >= 0);
+                if (lane == 0) wave_cnt[wave] = __popcll(bal);
+                __syncthreads();
+                int off = nkeep, total = 0;
+#pragma unroll
+                for (int w = 0; w < C::NW; ++w) {
+                    off += w < wave ? wave_cnt[w] : 0;
+                    total += wave_cnt[w];
+                }
+                const int below = __builtin_amdgcn_mbcnt_hi(
+                    uint32_t(bal >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(bal), 0));
+                if (code >= 0) codes[off + below] = code;
+                nkeep += total;
+                __syncthreads();  // wave_cnt is rewritten by the next round
             }
-            const uint64_t bal = __ballot(code >= 0);
-            if (lane == 0) wave_cnt[wave] = __popcll(bal);
-            __syncthreads();
-            int off = nkeep, total = 0;
+        }
+
+        int kvoff[C::DMA], vvoff[C::DMA];
 #pragma unroll
-            for (int w = 0; w < C::NW; ++w) {
-                off += w < wave ? wave_cnt[w] : 0;
-                total += wave_cnt[w];
+        for (int u = 0; u < C::DMA; ++u) {
+            const int p = (u * C::NW + wave) * 64 + lane;
+            kvoff[u] = chunk_src_offset<D>(p);
+            vvoff[u] = chunk_src_offset<BLK>(p);
+        }
+        auto issue = [&](int code, int buf) {
+            code = __builtin_amdgcn_readfirstlane(code);  // wave-uniform: scalar address arithmetic
+            const int64_t off = int64_t(code < 0 ? 0 : (code >> 1)) * C::TILE;
+            copy_tile<C::NW, C::DMA>(Kp + off, C::TILE * 2, &lds[buf][0][0], kvoff, wave);
+            copy_tile<C::NW, C::DMA>(Vp + off, C::TILE * 2, &lds[buf][1][0], vvoff, wave);
+        };
+
+        // Q^T operand: lane holds Q[qtok][16 kt + 8 g .. +7] for every k step.
+        bf16x8 qf[C::KT];
+        {
+            const uint16_t* qp = Q + (int64_t(h) * L + (qvalid ? qtok : 0)) * D + 8 * g;
+#pragma unroll
+            for (int kt = 0; kt < C::KT; ++kt) {
+                uint4 v = qvalid ? *reinterpret_cast<const uint4*>(qp + 16 * kt) : make_uint4(0, 0, 0, 0);
+                qf[kt] = __builtin_bit_cast(bf16x8, v);
             }
-            const int below = __builtin_amdgcn_mbcnt_hi(
-                uint32_t(bal >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(bal), 0));
-            if (code >= 0) codes[off + below] = code;
-            nkeep += total;
-            __syncthreads();  // wave_cnt is rewritten by the next round
         }
-    }
-
-    int kvoff[C::DMA], vvoff[C::DMA];
-#pragma unroll
-    for (int u = 0; u < C::DMA; ++u) {
-        const int p = (u * C::NW + wave) * 64 + lane;
-        kvoff[u] = chunk_src_offset<D>(p);
-        vvoff[u] = chunk_src_offset<BLK>(p);
-    }
-    auto issue = [&](int code, int buf) {
-        code = __builtin_amdgcn_readfirstlane(code);  // wave-uniform: scalar address arithmetic
-        const int64_t off = int64_t(code < 0 ? 0 : (code >> 1)) * C::TILE;
-        copy_tile<C::NW, C::DMA>(Kp + off, C::TILE * 2, &lds[buf][0][0], kvoff, wave);
-        copy_tile<C::NW, C::DMA>(Vp + off, C::TILE * 2, &lds[buf][1][0], vvoff, wave);
-    };
-
-    // Q^T operand: lane holds Q[qtok][16 kt + 8 g .. +7] for every k step.
-    bf16x8 qf[C::KT];
-    {
-        const uint16_t* qp = Q + (int64_t(h) * L + (qvalid ? qtok : 0)) * D + 8 * g;
-#pragma unroll
-        for (int kt = 0; kt < C::KT; ++kt) {
-            uint4 v = qvalid ? *reinterpret_cast<const uint4*>(qp + 16 * kt) : make_uint4(0, 0, 0, 0);
-            qf[kt] = __builtin_bit_cast(bf16x8, v);
+        // Folding into a running result: nothing to add when no block is kept here.
+        if (acc && nkeep == 0) {
+            if constexpr (SHARDS) continue;
+            return;
         }
-    }
-    // Folding into a running result: nothing to add when no block is kept here.
-    if (acc && nkeep == 0) return;
-    const int32_t* kept = codes;  // this workgroup's kept list
-    if (tp.piece >= 0) {          // its share of a split tail row
-        const int e0 = tp.piece * nkeep / tail_k, e1 = (tp.piece + 1) * nkeep / tail_k;
-        kept = codes + e0;
-        nkeep = e1 - e0;
-    }
-    // (the last compaction round ended with a barrier: codes are visible)
-    int code = nkeep > 0 ? kept[0] : -1;
-    if (nkeep > 0) issue(code, 0);
-    int next_code = nkeep > 1 ? kept[1] : -1;
-
-    floatx16 oacc[C::DT];
-#pragma unroll
-    for (int dt = 0; dt < C::DT; ++dt) oacc[dt] = floatx16{};
-    float m_run = -INFINITY;  // running max of scaled scores, log2 units
-    float l_run = 0.f;        // this lane's partial row sum
-    // Set only where the max moves: lim = m_run + the rescale threshold (see
-    // above), neg_m = -m_run, or 0 while the lane has seen no finite score.
-    float lim = -INFINITY, neg_m = 0.f;
-    const int last_cnt = L - (L / BLK) * BLK;  // valid keys of a partial last block
-
-    // One block of the loop. The buffer index is a compile-time constant (the
-    // loop below is unrolled by two), so the LDS operand addresses of both
-    // buffers are per-lane constants plus an immediate offset, with no address
-    // arithmetic inside the loop.
-    auto step = [&](int jj, auto buf_c) {
-        constexpr int buf = decltype(buf_c)::value;
-        const int cur = code;
-        // A workgroup barrier does not wait for outstanding vector-memory
-        // loads, and the compiler does not add that wait for direct-to-LDS
-        // copies: each wave waits for its own copies of block jj (the only
-        // ones in flight) before the barrier publishes the whole tile.
-        wait_vmem_all();
-        __syncthreads();  // block jj in LDS; everyone is done with block jj-1
-        if (jj + 1 < nkeep) {
-            issue(next_code, buf ^ 1);
-            code = next_code;
-            next_code = (jj + 2 < nkeep) ? kept[jj + 2] : -1;
+        const int32_t* kept = codes;  // this workgroup's kept list
+        if (tp.piece >= 0) {          // its share of a split tail row
+            const int e0 = tp.piece * nkeep / tail_k, e1 = (tp.piece + 1) * nkeep / tail_k;
+            kept = codes + e0;
+            nkeep = e1 - e0;
         }
-        if (cur < 0) return;
+        // (the last compaction round ended with a barrier: codes are visible)
+        int code = nkeep > 0 ? kept[0] : -1;
+        if (nkeep > 0) issue(code, 0);
+        int next_code = nkeep > 1 ? kept[1] : -1;
 
-        const uint16_t* lk = &lds[buf][0][0];
-        const uint16_t* lv = &lds[buf][1][0];
+        floatx16 oacc[C::DT];
+#pragma unroll
+        for (int dt = 0; dt < C::DT; ++dt) oacc[dt] = floatx16{};
+        float m_run = -INFINITY;  // running max of scaled scores, log2 units
+        float l_run = 0.f;        // this lane's partial row sum
+        // Set only where the max moves: lim = m_run + the rescale threshold (see
+        // above), neg_m = -m_run, or 0 while the lane has seen no finite score.
+        float lim = -INFINITY, neg_m = 0.f;
+        const int last_cnt = L - (L / BLK) * BLK;  // valid keys of a partial last block
 
-        // S^T for this wave's key half: s[mt][rr] is key
-        // HALF*kh + 32 mt + 16 (rr/8) + 8 g + rr%8 of query qi.
-        floatx16 s[C::MTW];
-#pragma unroll
-        for (int mt = 0; mt < C::MTW; ++mt) s[mt] = floatx16{};
-        // The score MFMAs run at raised wave priority, so the matrix pipe is
-        // fed first while the SIMD's other wave fills in with softmax work.
-        // All K operands of the block are read from LDS before the first MFMA,
-        // so the LDS latency is paid once per block instead of once per pair
-        // of MFMAs (the scheduler would otherwise sink each read to its use).
-        bf16x8 ka[C::KT][C::MTW];
-#pragma unroll
-        for (int kt = 0; kt < C::KT; ++kt)
-#pragma unroll
-            for (int mt = 0; mt < C::MTW; ++mt) {
-                const int krow = C::HALF * kh + 32 * mt + sigma(qi);
-                ka[kt][mt] = *reinterpret_cast<const bf16x8*>(
-                    lk + krow * D + (((2 * kt + g) ^ swz<D>(krow)) * 8));
+        // One block of the loop. The buffer index is a compile-time constant (the
+        // loop below is unrolled by two), so the LDS operand addresses of both
+        // buffers are per-lane constants plus an immediate offset, with no address
+        // arithmetic inside the loop.
+        auto step = [&](int jj, auto buf_c) {
+            constexpr int buf = decltype(buf_c)::value;
+            const int cur = code;
+            // A workgroup barrier does not wait for outstanding vector-memory
+            // loads, and the compiler does not add that wait for direct-to-LDS
+            // copies: each wave waits for its own copies of block jj (the only
+            // ones in flight) before the barrier publishes the whole tile.
+            wait_vmem_all();
+            __syncthreads();  // block jj in LDS; everyone is done with block jj-1
+            if (jj + 1 < nkeep) {
+                issue(next_code, buf ^ 1);
+                code = next_code;
+                next_code = (jj + 2 < nkeep) ? kept[jj + 2] : -1;
             }
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_setprio(1);
+            if (cur < 0) return;
+
+            const uint16_t* lk = &lds[buf][0][0];
+            const uint16_t* lv = &lds[buf][1][0];
+
+            // S^T for this wave's key half: s[mt][rr] is key
+            // HALF*kh + 32 mt + 16 (rr/8) + 8 g + rr%8 of query qi.
+            floatx16 s[C::MTW];
 #pragma unroll
-        for (int kt = 0; kt < C::KT; ++kt)
+            for (int mt = 0; mt < C::MTW; ++mt) s[mt] = floatx16{};
+            // The score MFMAs run at raised wave priority, so the matrix pipe is
+            // fed first while the SIMD's other wave fills in with softmax work.
+            // All K operands of the block are read from LDS before the first MFMA,
+            // so the LDS latency is paid once per block instead of once per pair
+            // of MFMAs (the scheduler would otherwise sink each read to its use).
+            bf16x8 ka[C::KT][C::MTW];
+#pragma unroll
+            for (int kt = 0; kt < C::KT; ++kt)
+#pragma unroll
+                for (int mt = 0; mt < C::MTW; ++mt) {
+                    const int krow = C::HALF * kh + 32 * mt + sigma(qi);
+                    ka[kt][mt] = *reinterpret_cast<const bf16x8*>(
+                        lk + krow * D + (((2 * kt + g) ^ swz<D>(krow)) * 8));
+                }
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+            for (int kt = 0; kt < C::KT; ++kt)
+#pragma unroll
+                for (int mt = 0; mt < C::MTW; ++mt)
+                    s[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[kt][mt], qf[kt], s[mt], 0, 0, 0);
+            __builtin_amdgcn_s_setprio(0);
+            // The V^T operands of the whole block, read before the softmax so that
+            // the LDS latency overlaps the exponentials.
+            bf16x8 va[C::PTW][C::DT];
+#pragma unroll
+            for (int t = 0; t < C::PTW; ++t)
+#pragma unroll
+                for (int dt = 0; dt < C::DT; ++dt) {
+                    const int tg = C::PTW * kh + t;
+                    const int vrow = 32 * dt + qi;
+                    va[t][dt] = *reinterpret_cast<const bf16x8*>(
+                        lv + vrow * BLK + (((2 * tg + g) ^ swz<BLK>(vrow)) * 8));
+                }
+            __builtin_amdgcn_sched_barrier(0);
+            if (cur & 1) {  // partial last block: keys past L do not exist
+#pragma unroll
+                for (int mt = 0; mt < C::MTW; ++mt)
+#pragma unroll
+                    for (int rr = 0; rr < 16; ++rr) {
+                        const int key = C::HALF * kh + 32 * mt + 16 * (rr >> 3) + 8 * g + (rr & 7);
+                        if (key >= last_cnt) s[mt][rr] = -INFINITY;
+                    }
+            }
+
+            float mx = -INFINITY;
 #pragma unroll
             for (int mt = 0; mt < C::MTW; ++mt)
-                s[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[kt][mt], qf[kt], s[mt], 0, 0, 0);
-        __builtin_amdgcn_s_setprio(0);
-        // The V^T operands of the whole block, read before the softmax so that
-        // the LDS latency overlaps the exponentials.
-        bf16x8 va[C::PTW][C::DT];
 #pragma unroll
-        for (int t = 0; t < C::PTW; ++t)
+                for (int rr = 0; rr < 16; rr += 2) mx = fmaxf(fmaxf(mx, s[mt][rr]), s[mt][rr + 1]);
+            mx = pair_max(mx) * c2;
+            // The max moves by the rule above (always on the first block a lane sees).
+            const bool moved = __ballot(mx > lim) != 0;
+            if (moved) {
+                const float m_new = fmaxf(m_run, mx);
+                const float alpha = (m_new == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m_run - m_new);
+                m_run = m_new;
+                l_run *= alpha;
+                lim = m_run + rescale_threshold(l_run);
+                neg_m = (m_run == -INFINITY) ? 0.f : -m_run;
 #pragma unroll
-            for (int dt = 0; dt < C::DT; ++dt) {
-                const int tg = C::PTW * kh + t;
-                const int vrow = 32 * dt + qi;
-                va[t][dt] = *reinterpret_cast<const bf16x8*>(
-                    lv + vrow * BLK + (((2 * tg + g) ^ swz<BLK>(vrow)) * 8));
+                for (int dt = 0; dt < C::DT; ++dt) oacc[dt] *= alpha;
             }
-        __builtin_amdgcn_sched_barrier(0);
-        if (cur & 1) {  // partial last block: keys past L do not exist
+
+            // (the two partial sums start from the first two probabilities, not
+            // from 0 + p, which the compiler cannot drop)
+            float lsum[2];
 #pragma unroll
-            for (int mt = 0; mt < C::MTW; ++mt)
+            for (int t = 0; t < C::PTW; ++t) {
+                const int mt = t >> 1, hf = t & 1;
+                floatx8 p;
 #pragma unroll
-                for (int rr = 0; rr < 16; ++rr) {
-                    const int key = C::HALF * kh + 32 * mt + 16 * (rr >> 3) + 8 * g + (rr & 7);
-                    if (key >= last_cnt) s[mt][rr] = -INFINITY;
+                for (int v = 0; v < 8; ++v) {
+                    p[v] = __builtin_amdgcn_exp2f(fmaf(s[mt][8 * hf + v], c2, neg_m));
+                    if (t == 0 && v < 2)
+                        lsum[v] = p[v];
+                    else
+                        lsum[v & 1] += p[v];
                 }
-        }
-
-        float mx = -INFINITY;
+                const bf16x8 pb = __builtin_convertvector(p, bf16x8);
 #pragma unroll
-        for (int mt = 0; mt < C::MTW; ++mt)
-#pragma unroll
-            for (int rr = 0; rr < 16; rr += 2) mx = fmaxf(fmaxf(mx, s[mt][rr]), s[mt][rr + 1]);
-        mx = pair_max(mx) * c2;
-        // The max moves by the rule above (always on the first block a lane sees).
-        const bool moved = __ballot(mx > lim) != 0;
-        if (moved) {
-            const float m_new = fmaxf(m_run, mx);
-            const float alpha = (m_new == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m_run - m_new);
-            m_run = m_new;
-            l_run *= alpha;
-            lim = m_run + rescale_threshold(l_run);
-            neg_m = (m_run == -INFINITY) ? 0.f : -m_run;
-#pragma unroll
-            for (int dt = 0; dt < C::DT; ++dt) oacc[dt] *= alpha;
-        }
-
-        // (the two partial sums start from the first two probabilities, not
-        // from 0 + p, which the compiler cannot drop)
-        float lsum[2];
-#pragma unroll
-        for (int t = 0; t < C::PTW; ++t) {
-            const int mt = t >> 1, hf = t & 1;
-            floatx8 p;
-#pragma unroll
-            for (int v = 0; v < 8; ++v) {
-                p[v] = __builtin_amdgcn_exp2f(fmaf(s[mt][8 * hf + v], c2, neg_m));
-                if (t == 0 && v < 2)
-                    lsum[v] = p[v];
-                else
-                    lsum[v & 1] += p[v];
+                for (int dt = 0; dt < C::DT; ++dt)
+                    oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[t][dt], pb, oacc[dt], 0, 0, 0);
             }
-            const bf16x8 pb = __builtin_convertvector(p, bf16x8);
+            l_run += lsum[0] + lsum[1];
+        };
+        for (int jj = 0; jj < nkeep; jj += 2) {
+            step(jj, std::integral_constant<int, 0>{});
+            if (jj + 1 < nkeep) step(jj + 1, std::integral_constant<int, 1>{});
+        }
+
+        // Merge the two key halves of each query group through their log-sum-exp.
+        const float l_half = pair_sum(l_run);
+        __syncthreads();  // every wave is done with the tiles
+        float* mrg = reinterpret_cast<float*>(&lds[0][0][0]);
+        constexpr int REGS = C::DT * 16;
+        float* mine = mrg + qg * 64 * (REGS + 2);
+        if (kh == 1) {
 #pragma unroll
             for (int dt = 0; dt < C::DT; ++dt)
-                oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[t][dt], pb, oacc[dt], 0, 0, 0);
+#pragma unroll
+                for (int rr = 0; rr < 16; ++rr) mine[(dt * 16 + rr) * 64 + lane] = oacc[dt][rr];
+            mine[REGS * 64 + lane] = m_run;
+            mine[(REGS + 1) * 64 + lane] = l_half;
         }
-        l_run += lsum[0] + lsum[1];
-    };
-    for (int jj = 0; jj < nkeep; jj += 2) {
-        step(jj, std::integral_constant<int, 0>{});
-        if (jj + 1 < nkeep) step(jj + 1, std::integral_constant<int, 1>{});
-    }
+        __syncthreads();
+        if (kh == 1) {
+            if constexpr (SHARDS) continue;
+            return;
+        }
 
-    // Merge the two key halves of each query group through their log-sum-exp.
-    const float l_half = pair_sum(l_run);
-    __syncthreads();  // every wave is done with the tiles
-    float* mrg = reinterpret_cast<float*>(&lds[0][0][0]);
-    constexpr int REGS = C::DT * 16;
-    float* mine = mrg + qg * 64 * (REGS + 2);
-    if (kh == 1) {
+        const float m_b = mine[REGS * 64 + lane];
+        const float l_b = mine[(REGS + 1) * 64 + lane];
+        const float m = fmaxf(m_run, m_b);
+        const float w_a = (m_run == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m_run - m);
+        const float w_b = (m_b == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m_b - m);
+        const float l_tot = l_half * w_a + l_b * w_b;
+        const bool live = qvalid && l_tot > 0.f;
+        const float inv = live ? 1.0f / l_tot : 0.f;
+        const float fa = w_a * inv, fb = w_b * inv;
+        const int64_t orow = int64_t(h) * nq * BLK + int64_t(r) * BLK + qg * 32 + qi;
+        float lse_out = live ? (m + __log2f(l_tot)) * kLn2 : -INFINITY;
+        if (tp.piece >= 0) {  // a piece of a split tail row: float32 partial into the workspace
+            const int64_t prow = int64_t(blockIdx.x - tail_first) * BLK + qg * 32 + qi;
 #pragma unroll
-        for (int dt = 0; dt < C::DT; ++dt)
+            for (int dt = 0; dt < C::DT; ++dt)
 #pragma unroll
-            for (int rr = 0; rr < 16; ++rr) mine[(dt * 16 + rr) * 64 + lane] = oacc[dt][rr];
-        mine[REGS * 64 + lane] = m_run;
-        mine[(REGS + 1) * 64 + lane] = l_half;
-    }
-    __syncthreads();
-    if (kh == 1) return;
-
-    const float m_b = mine[REGS * 64 + lane];
-    const float l_b = mine[(REGS + 1) * 64 + lane];
-    const float m = fmaxf(m_run, m_b);
-    const float w_a = (m_run == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m_run - m);
-    const float w_b = (m_b == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m_b - m);
-    const float l_tot = l_half * w_a + l_b * w_b;
-    const bool live = qvalid && l_tot > 0.f;
-    const float inv = live ? 1.0f / l_tot : 0.f;
-    const float fa = w_a * inv, fb = w_b * inv;
-    const int64_t orow = int64_t(h) * nq * BLK + int64_t(r) * BLK + qg * 32 + qi;
-    float lse_out = live ? (m + __log2f(l_tot)) * kLn2 : -INFINITY;
-    if (tp.piece >= 0) {  // a piece of a split tail row: float32 partial into the workspace
-        const int64_t prow = int64_t(blockIdx.x - tail_first) * BLK + qg * 32 + qi;
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    float o4[4];
 #pragma unroll
-        for (int dt = 0; dt < C::DT; ++dt)
+                    for (int u = 0; u < 4; ++u) {
+                        const int rr = 4 * q4 + u;
+                        o4[u] = live ? oacc[dt][rr] * fa + mine[(dt * 16 + rr) * 64 + lane] * fb : 0.f;
+                    }
+                    *reinterpret_cast<float4*>(part_o + prow * D + 32 * dt + 8 * q4 + 4 * g) =
+                        make_float4(o4[0], o4[1], o4[2], o4[3]);
+                }
+            if (g == 0) part_lse[prow] = lse_out;
+            return;
+        }
+        // Folding into a running result (O, lse, float32): with both log-sum-exps
+        // in log2 units, the stored rows weigh ka and this part kb. Both lanes of
+        // a row pair read the stored lse before the g == 0 lane rewrites it (the
+        // rewrite depends on the value read).
+        float ka = 0.f, kb = 1.f;
+        bool store = true;
+        if (!OUT_BF16 && acc) {
+            store = live;
+            if (live) {
+                const float la2 = lse[orow] * kLog2e;
+                const float lb2 = m + __log2f(l_tot);
+                const float mm = fmaxf(la2, lb2);
+                const float wa = (la2 == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(la2 - mm);
+                const float wb = __builtin_amdgcn_exp2f(lb2 - mm);
+                const float t = wa + wb;
+                ka = wa / t;
+                kb = wb / t;
+                lse_out = (mm + __log2f(t)) * kLn2;
+            }
+        }
+#pragma unroll
+        for (int dt = 0; dt < C::DT; ++dt) {
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) {
+                const int d0 = 32 * dt + 8 * q4 + 4 * g;
                 float o4[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const int rr = 4 * q4 + u;
                     o4[u] = live ? oacc[dt][rr] * fa + mine[(dt * 16 + rr) * 64 + lane] * fb : 0.f;
                 }
-                *reinterpret_cast<float4*>(part_o + prow * D + 32 * dt + 8 * q4 + 4 * g) =
-                    make_float4(o4[0], o4[1], o4[2], o4[3]);
-            }
-        if (g == 0) part_lse[prow] = lse_out;
-        return;
-    }
-    // Folding into a running result (O, lse, float32): with both log-sum-exps
-    // in log2 units, the stored rows weigh ka and this part kb. Both lanes of
-    // a row pair read the stored lse before the g == 0 lane rewrites it (the
-    // rewrite depends on the value read).
-    float ka = 0.f, kb = 1.f;
-    bool store = true;
-    if (!OUT_BF16 && acc) {
-        store = live;
-        if (live) {
-            const float la2 = lse[orow] * kLog2e;
-            const float lb2 = m + __log2f(l_tot);
-            const float mm = fmaxf(la2, lb2);
-            const float wa = (la2 == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(la2 - mm);
-            const float wb = __builtin_amdgcn_exp2f(lb2 - mm);
-            const float t = wa + wb;
-            ka = wa / t;
-            kb = wb / t;
-            lse_out = (mm + __log2f(t)) * kLn2;
-        }
-    }
-#pragma unroll
-    for (int dt = 0; dt < C::DT; ++dt) {
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-            const int d0 = 32 * dt + 8 * q4 + 4 * g;
-            float o4[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int rr = 4 * q4 + u;
-                o4[u] = live ? oacc[dt][rr] * fa + mine[(dt * 16 + rr) * 64 + lane] * fb : 0.f;
-            }
-            if (!store) continue;
-            if constexpr (OUT_BF16) {
-                uint16_t* op = static_cast<uint16_t*>(O) + orow * D + d0;
-                uint2 w;
-                w.x = f32_to_bf16_bits(o4[0]) | (f32_to_bf16_bits(o4[1]) << 16);
-                w.y = f32_to_bf16_bits(o4[2]) | (f32_to_bf16_bits(o4[3]) << 16);
-                *reinterpret_cast<uint2*>(op) = w;
-            } else {
-                float* op = static_cast<float*>(O) + orow * D + d0;
-                if (acc) {
-                    const float4 prev = *reinterpret_cast<const float4*>(op);
-                    o4[0] = ka * prev.x + kb * o4[0];
-                    o4[1] = ka * prev.y + kb * o4[1];
-                    o4[2] = ka * prev.z + kb * o4[2];
-                    o4[3] = ka * prev.w + kb * o4[3];
+                if (!store) continue;
+                if constexpr (OUT_BF16) {
+                    uint16_t* op = static_cast<uint16_t*>(O) + orow * D + d0;
+                    uint2 w;
+                    w.x = f32_to_bf16_bits(o4[0]) | (f32_to_bf16_bits(o4[1]) << 16);
+                    w.y = f32_to_bf16_bits(o4[2]) | (f32_to_bf16_bits(o4[3]) << 16);
+                    *reinterpret_cast<uint2*>(op) = w;
+                } else {
+                    float* op = static_cast<float*>(O) + orow * D + d0;
+                    if (acc) {
+                        const float4 prev = *reinterpret_cast<const float4*>(op);
+                        o4[0] = ka * prev.x + kb * o4[0];
+                        o4[1] = ka * prev.y + kb * o4[1];
+                        o4[2] = ka * prev.z + kb * o4[2];
+                        o4[3] = ka * prev.w + kb * o4[3];
+                    }
+                    *reinterpret_cast<float4*>(op) = make_float4(o4[0], o4[1], o4[2], o4[3]);
                 }
-                *reinterpret_cast<float4*>(op) = make_float4(o4[0], o4[1], o4[2], o4[3]);
             }
         }
+        if (lse && g == 0 && store) lse[orow] = lse_out;
     }
-    if (lse && g == 0 && store) lse[orow] = lse_out;
 }
 
 // Kernel for 128-token blocks (and, with two waves, 64-token ones at d = 128): two
@@ -714,7 +737,7 @@ __device__ __forceinline__ void wait_vmem_keep() {
 
 // ORDERED: an explicit row order is given (an instance of its own, so that the
 // others carry no test of it in their loop).
-template <int D, int BLK, bool OUT_BF16, bool ORDERED>
+template <int D, int BLK, bool OUT_BF16, bool ORDERED, bool SHARDS>
 __global__ __launch_bounds__(64 * (BLK / 32)) __attribute__((amdgpu_waves_per_eu(2)))
 void attn_rows_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict__ sel,
                     const int32_t* __restrict__ slot_of, const uint16_t* __restrict__ Kp,
@@ -724,15 +747,11 @@ void attn_rows_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
                     int h_lo, int n_heads, int acc, int remap,
                     const int32_t* __restrict__ order, int tail_first, int tail_k,
                     float* __restrict__ part_o, float* __restrict__ part_lse,
-                    const int32_t* __restrict__ row_sort) {
+                    const int32_t* __restrict__ row_sort, ShardsArg<SHARDS> shards) {
     using C = CfgRows<D, BLK>;
     __shared__ __attribute__((aligned(16))) uint16_t lk[C::TILE];
     __shared__ __attribute__((aligned(16))) uint16_t lv[C::TILE];
     extern __shared__ int32_t codes[];
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int qi = lane & 15, g = lane >> 4;
 
     // Longest-first launches end with their longest rows when nothing speeds those
     // up: a row of several hundred blocks takes the whole launch on half a CU.
@@ -754,359 +773,377 @@ void attn_rows_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
     }
     const int h = h_lo + wg / nq, r = wg % nq;
     __shared__ int wave_cnt[C::NW];
-    int nkeep = 0;
-    {
-        const int32_t* srow = sel + (int64_t(h) * nq + r) * keep;
-        const int32_t* hslot = slot_of + int64_t(h) * n;
-        const bool ragged = (L % BLK) != 0;
-        for (int base = 0; base < keep; base += C::THREADS) {
-            const int jj = base + tid;
-            int code = -1;
-            if (jj < keep) {
-                const int j = srow[jj];
-                if (j >= kv_lo && j < kv_hi && j >= 0 && j < n) {
-                    const int sl = hslot[j];
-                    if (sl >= 0 && sl < capacity && sl < (1 << 30))
-                        code = 2 * sl + ((ragged && j == n - 1) ? 1 : 0);
+    int n_shards = 1;
+    if constexpr (SHARDS) n_shards = shards.n;
+    for (int shard = 0; shard < n_shards; ++shard) {
+        if constexpr (SHARDS) {
+            kv_lo = shards.lo[shard];
+            kv_hi = shards.hi[shard];
+            if (shard > 0) acc = 1;
+        }
+        int tid = threadIdx.x;
+        // (hidden from the compiler, so that it does not keep every address it derives from
+        // the lane in registers from one range to the next: at d = 128 those are all taken)
+        if constexpr (SHARDS) asm volatile("" : "+v"(tid));
+        const int lane = tid & 63, wave = tid >> 6;
+        const int qi = lane & 15, g = lane >> 4;
+        int nkeep = 0;
+        {
+            const int32_t* srow = sel + (int64_t(h) * nq + r) * keep;
+            const int32_t* hslot = slot_of + int64_t(h) * n;
+            const bool ragged = (L % BLK) != 0;
+            for (int base = 0; base < keep; base += C::THREADS) {
+                const int jj = base + tid;
+                int code = -1;
+                if (jj < keep) {
+                    const int j = srow[jj];
+                    if (j >= kv_lo && j < kv_hi && j >= 0 && j < n) {
+                        const int sl = hslot[j];
+                        if (sl >= 0 && sl < capacity && sl < (1 << 30))
+                            code = 2 * sl + ((ragged && j == n - 1) ? 1 : 0);
+                    }
                 }
-            }
-            const uint64_t bal = __ballot(code >= 0);
-            if (lane == 0) wave_cnt[wave] = __popcll(bal);
-            __syncthreads();
-            int off = nkeep, total = 0;
+                const uint64_t bal = __ballot(code >= 0);
+                if (lane == 0) wave_cnt[wave] = __popcll(bal);
+                __syncthreads();
+                int off = nkeep, total = 0;
 #pragma unroll
-            for (int w = 0; w < C::NW; ++w) {
-                off += w < wave ? wave_cnt[w] : 0;
-                total += wave_cnt[w];
+                for (int w = 0; w < C::NW; ++w) {
+                    off += w < wave ? wave_cnt[w] : 0;
+                    total += wave_cnt[w];
+                }
+                const int below = __builtin_amdgcn_mbcnt_hi(
+                    uint32_t(bal >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(bal), 0));
+                if (code >= 0) codes[off + below] = code;
+                nkeep += total;
+                __syncthreads();
             }
-            const int below = __builtin_amdgcn_mbcnt_hi(
-                uint32_t(bal >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(bal), 0));
-            if (code >= 0) codes[off + below] = code;
-            nkeep += total;
-            __syncthreads();
         }
-    }
-    if (acc && nkeep == 0) return;
-    const int32_t* kept = codes;  // this workgroup's kept list
-    if (tp.piece >= 0) {          // its share of a split tail row
-        const int e0 = tp.piece * nkeep / tail_k, e1 = (tp.piece + 1) * nkeep / tail_k;
-        kept = codes + e0;
-        nkeep = e1 - e0;
-    }
-
-    int kvoff[C::DMA], vvoff[C::DMA];
-#pragma unroll
-    for (int u = 0; u < C::DMA; ++u) {
-        const int p = (u * C::NW + wave) * 64 + lane;
-        kvoff[u] = k16_src_offset<D>(p);
-        vvoff[u] = chunk_src_offset<BLK>(p);
-    }
-    // (codes are wave-uniform; taking them into scalar registers keeps the
-    // copies' address arithmetic on the scalar unit)
-    auto copy_k = [&](int code) {
-        code = __builtin_amdgcn_readfirstlane(code);
-        copy_tile<C::NW, C::DMA>(Kp + int64_t(code >> 1) * C::TILE, C::TILE * 2, lk, kvoff, wave);
-    };
-    auto copy_v = [&](int code) {
-        code = __builtin_amdgcn_readfirstlane(code);
-        copy_tile<C::NW, C::DMA>(Vp + int64_t(code >> 1) * C::TILE, C::TILE * 2, lv, vvoff, wave);
-    };
-
-    // Q^T operands: lane holds Q[q][32 kt + 8 g .. +7] of its query of each group.
-    bf16x8 qf[2][C::KT];
-    bool qvalid[2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a) {
-        const int qtok = (i0 + r) * BLK + 32 * wave + 16 * a + qi;
-        qvalid[a] = qtok < L;
-        const uint16_t* qp = Q + (int64_t(h) * L + (qvalid[a] ? qtok : 0)) * D + 8 * g;
-#pragma unroll
-        for (int kt = 0; kt < C::KT; ++kt) {
-            uint4 v = qvalid[a] ? *reinterpret_cast<const uint4*>(qp + 32 * kt) : make_uint4(0, 0, 0, 0);
-            qf[a][kt] = __builtin_bit_cast(bf16x8, v);
+        if (acc && nkeep == 0) {
+            if constexpr (SHARDS) continue;
+            return;
         }
-    }
-    // From here on nothing the compiler tracks is in flight: the Q loads are
-    // waited for here, and the copies are issued behind its back (copy_tile).
-    wait_vmem_all();
-    if (nkeep > 0) {
-        copy_k(kept[0]);
-        copy_v(kept[0]);
-    }
+        const int32_t* kept = codes;  // this workgroup's kept list
+        if (tp.piece >= 0) {          // its share of a split tail row
+            const int e0 = tp.piece * nkeep / tail_k, e1 = (tp.piece + 1) * nkeep / tail_k;
+            kept = codes + e0;
+            nkeep = e1 - e0;
+        }
 
-    floatx4 oacc[C::DT][2];
+        int kvoff[C::DMA], vvoff[C::DMA];
 #pragma unroll
-    for (int dt = 0; dt < C::DT; ++dt) oacc[dt][0] = oacc[dt][1] = floatx4{};
-    float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
-    // Set only where the max moves: lim = m_run + the rescale threshold,
-    // neg_m = -m_run, or 0 while the lane has seen no finite score.
-    float lim[2] = {-INFINITY, -INFINITY}, neg_m[2] = {0.f, 0.f};
-    const int last_cnt = L - (L / BLK) * BLK;
-
-    // Entering block jj: K(jj) and V(jj) are in flight, K issued first.
-    if (nkeep > 0) {
-        wait_vmem_keep<C::DMA>();  // K(0) landed (V(0) may still be in flight)
-        __syncthreads();
-    }
-    if (first_round) __builtin_amdgcn_s_setprio(2);
-    for (int jj = 0; jj < nkeep; ++jj) {
-        const int cur = kept[jj];
-        // Scores: S^T for the wave's 32 queries over all 128 keys of the block;
-        // s[2t+u][a][r] is key 32 t + 8 g + 4 u + r of query 16 a + qi.
-        // k step outermost, four key tiles at a time, so the accumulators
-        // advance together and no MFMA waits on the one before it; the K
-        // operands of the next step are read while the eight MFMAs of this one
-        // run.
-        floatx4 s[C::MT][2];
-#pragma unroll
-        for (int mt = 0; mt < C::MT; ++mt) s[mt][0] = s[mt][1] = floatx4{};
-        constexpr int MH = C::MT / 2;       // key tiles per step
-        constexpr int KSTEPS = 2 * C::KT;   // step i: k step i/2, half i%2 of the tiles
-        bf16x8 kb[2][MH];
-        auto kread = [&](int i, bf16x8 (&dst)[MH]) {
-#pragma unroll
-            for (int x = 0; x < MH; ++x) {
-                const int mt = MH * (i & 1) + x;
-                const int krow = 32 * (mt >> 1) + 8 * (qi >> 2) + 4 * (mt & 1) + (qi & 3);
-                dst[x] = *reinterpret_cast<const bf16x8*>(
-                    lk + krow * D + (((4 * (i >> 1) + g) ^ swz_k16<D>(krow)) * 8));
-            }
+        for (int u = 0; u < C::DMA; ++u) {
+            const int p = (u * C::NW + wave) * 64 + lane;
+            kvoff[u] = k16_src_offset<D>(p);
+            vvoff[u] = chunk_src_offset<BLK>(p);
+        }
+        // (codes are wave-uniform; taking them into scalar registers keeps the
+        // copies' address arithmetic on the scalar unit)
+        auto copy_k = [&](int code) {
+            code = __builtin_amdgcn_readfirstlane(code);
+            copy_tile<C::NW, C::DMA>(Kp + int64_t(code >> 1) * C::TILE, C::TILE * 2, lk, kvoff, wave);
         };
-        kread(0, kb[0]);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < KSTEPS; ++i) {
-            if (i + 1 < KSTEPS) kread(i + 1, kb[(i + 1) & 1]);
-#pragma unroll
-            for (int x = 0; x < MH; ++x)
-#pragma unroll
-                for (int a = 0; a < 2; ++a) {
-                    const int mt = MH * (i & 1) + x;
-                    s[mt][a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kb[i & 1][x], qf[a][i >> 1],
-                                                                      s[mt][a], 0, 0, 0);
-                }
-        }
-        // Keep that order: the reads of step i+1 ahead of the MFMAs of step i.
-#pragma unroll
-        for (int i = 0; i < KSTEPS; ++i) {
-            if (i + 1 < KSTEPS) __builtin_amdgcn_sched_group_barrier(0x100, MH, 0);  // LDS reads
-            __builtin_amdgcn_sched_group_barrier(0x008, 2 * MH, 0);                  // MFMAs
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        wait_vmem_all();   // V(jj) landed
-        __syncthreads();   // V(jj) visible; every wave is done with K(jj)
-        if (jj + 1 < nkeep) copy_k(kept[jj + 1]);
+        auto copy_v = [&](int code) {
+            code = __builtin_amdgcn_readfirstlane(code);
+            copy_tile<C::NW, C::DMA>(Vp + int64_t(code >> 1) * C::TILE, C::TILE * 2, lv, vvoff, wave);
+        };
 
-        // Softmax and output product at raised priority: where the other wave
-        // on the SIMD is in its score MFMAs, this wave's VALU work issues first
-        // and the matrix pipe stays fed by both.
-        if (first_round)
-            __builtin_amdgcn_s_setprio(3);
-        else
-            __builtin_amdgcn_s_setprio(1);
-        if (cur & 1) {
+        // Q^T operands: lane holds Q[q][32 kt + 8 g .. +7] of its query of each group.
+        bf16x8 qf[2][C::KT];
+        bool qvalid[2];
 #pragma unroll
-            for (int mt = 0; mt < C::MT; ++mt)
+        for (int a = 0; a < 2; ++a) {
+            const int qtok = (i0 + r) * BLK + 32 * wave + 16 * a + qi;
+            qvalid[a] = qtok < L;
+            const uint16_t* qp = Q + (int64_t(h) * L + (qvalid[a] ? qtok : 0)) * D + 8 * g;
 #pragma unroll
-                for (int rr = 0; rr < 4; ++rr) {
-                    const int key = 32 * (mt >> 1) + 8 * g + 4 * (mt & 1) + rr;
-                    if (key >= last_cnt) s[mt][0][rr] = s[mt][1][rr] = -INFINITY;
+            for (int kt = 0; kt < C::KT; ++kt) {
+                uint4 v = qvalid[a] ? *reinterpret_cast<const uint4*>(qp + 32 * kt) : make_uint4(0, 0, 0, 0);
+                qf[a][kt] = __builtin_bit_cast(bf16x8, v);
+            }
+        }
+        // From here on nothing the compiler tracks is in flight: the Q loads are
+        // waited for here, and the copies are issued behind its back (copy_tile).
+        wait_vmem_all();
+        if (nkeep > 0) {
+            copy_k(kept[0]);
+            copy_v(kept[0]);
+        }
+
+        floatx4 oacc[C::DT][2];
+#pragma unroll
+        for (int dt = 0; dt < C::DT; ++dt) oacc[dt][0] = oacc[dt][1] = floatx4{};
+        float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
+        // Set only where the max moves: lim = m_run + the rescale threshold,
+        // neg_m = -m_run, or 0 while the lane has seen no finite score.
+        float lim[2] = {-INFINITY, -INFINITY}, neg_m[2] = {0.f, 0.f};
+        const int last_cnt = L - (L / BLK) * BLK;
+
+        // Entering block jj: K(jj) and V(jj) are in flight, K issued first.
+        if (nkeep > 0) {
+            wait_vmem_keep<C::DMA>();  // K(0) landed (V(0) may still be in flight)
+            __syncthreads();
+        }
+        if (first_round) __builtin_amdgcn_s_setprio(2);
+        for (int jj = 0; jj < nkeep; ++jj) {
+            const int cur = kept[jj];
+            // Scores: S^T for the wave's 32 queries over all 128 keys of the block;
+            // s[2t+u][a][r] is key 32 t + 8 g + 4 u + r of query 16 a + qi.
+            // k step outermost, four key tiles at a time, so the accumulators
+            // advance together and no MFMA waits on the one before it; the K
+            // operands of the next step are read while the eight MFMAs of this one
+            // run.
+            floatx4 s[C::MT][2];
+#pragma unroll
+            for (int mt = 0; mt < C::MT; ++mt) s[mt][0] = s[mt][1] = floatx4{};
+            constexpr int MH = C::MT / 2;       // key tiles per step
+            constexpr int KSTEPS = 2 * C::KT;   // step i: k step i/2, half i%2 of the tiles
+            bf16x8 kb[2][MH];
+            auto kread = [&](int i, bf16x8 (&dst)[MH]) {
+#pragma unroll
+                for (int x = 0; x < MH; ++x) {
+                    const int mt = MH * (i & 1) + x;
+                    const int krow = 32 * (mt >> 1) + 8 * (qi >> 2) + 4 * (mt & 1) + (qi & 3);
+                    dst[x] = *reinterpret_cast<const bf16x8*>(
+                        lk + krow * D + (((4 * (i >> 1) + g) ^ swz_k16<D>(krow)) * 8));
                 }
-        }
-        constexpr int MP = C::MT / C::PARTS;  // 16-key tiles per part of the block
-        float mx[2][C::PARTS];
+            };
+            kread(0, kb[0]);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
+            for (int i = 0; i < KSTEPS; ++i) {
+                if (i + 1 < KSTEPS) kread(i + 1, kb[(i + 1) & 1]);
 #pragma unroll
-            for (int y = 0; y < C::PARTS; ++y) {
-                mx[a][y] = -INFINITY;
+                for (int x = 0; x < MH; ++x)
 #pragma unroll
-                for (int mt = MP * y; mt < MP * (y + 1); ++mt)
-#pragma unroll
-                    for (int rr = 0; rr < 4; rr += 2)
-                        mx[a][y] = fmaxf(fmaxf(mx[a][y], s[mt][a][rr]), s[mt][a][rr + 1]);
-                mx[a][y] = quad_max(mx[a][y]) * c2;
+                    for (int a = 0; a < 2; ++a) {
+                        const int mt = MH * (i & 1) + x;
+                        s[mt][a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kb[i & 1][x], qf[a][i >> 1],
+                                                                          s[mt][a], 0, 0, 0);
+                    }
             }
-        const bool moved = __ballot(mx[0][0] > lim[0] || mx[1][0] > lim[1]) != 0;
-        if (moved) {
+            // Keep that order: the reads of step i+1 ahead of the MFMAs of step i.
 #pragma unroll
-            for (int a = 0; a < 2; ++a) {
-                const float m_new = moved_max<C::DOWN>(m_run[a], mx[a][0], lim[a]);
-                const float alpha =
-                    (m_new == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m_run[a] - m_new);
-                m_run[a] = m_new;
-                l_run[a] *= alpha;
-                // (a limit that may let m fall has to be the same in a query's four lanes)
-                lim[a] = m_run[a] + (C::DOWN ? rescale_limit(quad_sum(l_run[a]) + 1.f)
-                                             : rescale_threshold(l_run[a]));
-                neg_m[a] = (m_run[a] == -INFINITY) ? 0.f : -m_run[a];
-#pragma unroll
-                for (int dt = 0; dt < C::DT; ++dt) oacc[dt][a] *= alpha;
+            for (int i = 0; i < KSTEPS; ++i) {
+                if (i + 1 < KSTEPS) __builtin_amdgcn_sched_group_barrier(0x100, MH, 0);  // LDS reads
+                __builtin_amdgcn_sched_group_barrier(0x008, 2 * MH, 0);                  // MFMAs
             }
-        }
-        // The second part's move is decided here too, so that its probabilities can be
-        // computed ahead; the sums follow between the parts' output products.
-        float neg_2[2] = {neg_m[0], neg_m[1]}, alpha_2[2] = {1.f, 1.f};
-        bool moved_2 = false;
-        if constexpr (C::PARTS == 2) {
-            moved_2 = __ballot(mx[0][1] > lim[0] || mx[1][1] > lim[1]) != 0;
-            if (moved_2) {
+            __builtin_amdgcn_sched_barrier(0);
+            wait_vmem_all();   // V(jj) landed
+            __syncthreads();   // V(jj) visible; every wave is done with K(jj)
+            if (jj + 1 < nkeep) copy_k(kept[jj + 1]);
+
+            // Softmax and output product at raised priority: where the other wave
+            // on the SIMD is in its score MFMAs, this wave's VALU work issues first
+            // and the matrix pipe stays fed by both.
+            if (first_round)
+                __builtin_amdgcn_s_setprio(3);
+            else
+                __builtin_amdgcn_s_setprio(1);
+            if (cur & 1) {
+#pragma unroll
+                for (int mt = 0; mt < C::MT; ++mt)
+#pragma unroll
+                    for (int rr = 0; rr < 4; ++rr) {
+                        const int key = 32 * (mt >> 1) + 8 * g + 4 * (mt & 1) + rr;
+                        if (key >= last_cnt) s[mt][0][rr] = s[mt][1][rr] = -INFINITY;
+                    }
+            }
+            constexpr int MP = C::MT / C::PARTS;  // 16-key tiles per part of the block
+            float mx[2][C::PARTS];
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int y = 0; y < C::PARTS; ++y) {
+                    mx[a][y] = -INFINITY;
+#pragma unroll
+                    for (int mt = MP * y; mt < MP * (y + 1); ++mt)
+#pragma unroll
+                        for (int rr = 0; rr < 4; rr += 2)
+                            mx[a][y] = fmaxf(fmaxf(mx[a][y], s[mt][a][rr]), s[mt][a][rr + 1]);
+                    mx[a][y] = quad_max(mx[a][y]) * c2;
+                }
+            const bool moved = __ballot(mx[0][0] > lim[0] || mx[1][0] > lim[1]) != 0;
+            if (moved) {
 #pragma unroll
                 for (int a = 0; a < 2; ++a) {
-                    const float m_new = moved_max<C::DOWN>(m_run[a], mx[a][1], lim[a]);
-                    alpha_2[a] =
+                    const float m_new = moved_max<C::DOWN>(m_run[a], mx[a][0], lim[a]);
+                    const float alpha =
                         (m_new == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m_run[a] - m_new);
                     m_run[a] = m_new;
-                    neg_2[a] = (m_new == -INFINITY) ? 0.f : -m_new;
+                    l_run[a] *= alpha;
+                    // (a limit that may let m fall has to be the same in a query's four lanes)
+                    lim[a] = m_run[a] + (C::DOWN ? rescale_limit(quad_sum(l_run[a]) + 1.f)
+                                                 : rescale_threshold(l_run[a]));
+                    neg_m[a] = (m_run[a] == -INFINITY) ? 0.f : -m_run[a];
+#pragma unroll
+                    for (int dt = 0; dt < C::DT; ++dt) oacc[dt][a] *= alpha;
                 }
             }
-        }
-
-        // 32-key steps, each in two halves of the d tiles; the V^T operands of
-        // the next half are read one half ahead, and each half computes the next
-        // step's probabilities of one query group while its MFMAs run. (Groups
-        // that force two MFMAs per seven VALU instructions, or one per three or
-        // four, measured 0.4 to 1.1% slower than the compiler's own order.)
-        // (the two partial sums of a group start from its first two
-        // probabilities, not from 0 + p, which the compiler cannot drop)
-        float lsum[2][C::PARTS][2];
-        constexpr int TP = C::PT / C::PARTS;  // 32-key steps per part
-        constexpr int DH = C::DT / 2;
-        constexpr int VSTEPS = 2 * C::PT;
-        bf16x8 vb[2][DH];
-        auto vread = [&](int i, bf16x8 (&dst)[DH]) {
-#pragma unroll
-            for (int x = 0; x < DH; ++x) {
-                const int vrow = 16 * (DH * (i & 1) + x) + qi;
-                dst[x] = *reinterpret_cast<const bf16x8*>(
-                    lv + vrow * BLK + (((4 * (i >> 1) + g) ^ swz<BLK>(vrow)) * 8));
-            }
-        };
-        auto pstep = [&](int t, int a) -> bf16x8 {
-            floatx8 p;
-#pragma unroll
-            for (int v = 0; v < 8; ++v) {
-                p[v] = __builtin_amdgcn_exp2f(fmaf(s[2 * t + (v >> 2)][a][v & 3], c2, t < TP ? neg_m[a] : neg_2[a]));
-                if (t % TP == 0 && v < 2)
-                    lsum[a][t / TP][v] = p[v];
-                else
-                    lsum[a][t / TP][v & 1] += p[v];
-            }
-            return __builtin_convertvector(p, bf16x8);
-        };
-        vread(0, vb[0]);
-        bf16x8 pb[2], pbn[2];
-        pbn[0] = pstep(0, 0);
-        pbn[1] = pstep(0, 1);
-#pragma unroll
-        for (int i = 0; i < VSTEPS; ++i) {
-            const int t = i >> 1, hf = i & 1;
-            if (i + 1 < VSTEPS) vread(i + 1, vb[(i + 1) & 1]);
-            __builtin_amdgcn_sched_barrier(0);
-            if (hf == 0) {
-                pb[0] = pbn[0];
-                pb[1] = pbn[1];
-            }
-            if (C::PARTS == 2 && i == VSTEPS / 2) {
-#pragma unroll
-                for (int a = 0; a < 2; ++a) l_run[a] += lsum[a][0][0] + lsum[a][0][1];
+            // The second part's move is decided here too, so that its probabilities can be
+            // computed ahead; the sums follow between the parts' output products.
+            float neg_2[2] = {neg_m[0], neg_m[1]}, alpha_2[2] = {1.f, 1.f};
+            bool moved_2 = false;
+            if constexpr (C::PARTS == 2) {
+                moved_2 = __ballot(mx[0][1] > lim[0] || mx[1][1] > lim[1]) != 0;
                 if (moved_2) {
 #pragma unroll
                     for (int a = 0; a < 2; ++a) {
-                        l_run[a] *= alpha_2[a];
-                        lim[a] = m_run[a] + rescale_limit(quad_sum(l_run[a]) + 1.f);
-                        neg_m[a] = neg_2[a];
-#pragma unroll
-                        for (int dt = 0; dt < C::DT; ++dt) oacc[dt][a] *= alpha_2[a];
+                        const float m_new = moved_max<C::DOWN>(m_run[a], mx[a][1], lim[a]);
+                        alpha_2[a] =
+                            (m_new == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m_run[a] - m_new);
+                        m_run[a] = m_new;
+                        neg_2[a] = (m_new == -INFINITY) ? 0.f : -m_new;
                     }
                 }
             }
-            if (t + 1 < C::PT) pbn[hf] = pstep(t + 1, hf);
+
+            // 32-key steps, each in two halves of the d tiles; the V^T operands of
+            // the next half are read one half ahead, and each half computes the next
+            // step's probabilities of one query group while its MFMAs run. (Groups
+            // that force two MFMAs per seven VALU instructions, or one per three or
+            // four, measured 0.4 to 1.1% slower than the compiler's own order.)
+            // (the two partial sums of a group start from its first two
+            // probabilities, not from 0 + p, which the compiler cannot drop)
+            float lsum[2][C::PARTS][2];
+            constexpr int TP = C::PT / C::PARTS;  // 32-key steps per part
+            constexpr int DH = C::DT / 2;
+            constexpr int VSTEPS = 2 * C::PT;
+            bf16x8 vb[2][DH];
+            auto vread = [&](int i, bf16x8 (&dst)[DH]) {
 #pragma unroll
-            for (int x = 0; x < DH; ++x)
+                for (int x = 0; x < DH; ++x) {
+                    const int vrow = 16 * (DH * (i & 1) + x) + qi;
+                    dst[x] = *reinterpret_cast<const bf16x8*>(
+                        lv + vrow * BLK + (((4 * (i >> 1) + g) ^ swz<BLK>(vrow)) * 8));
+                }
+            };
+            auto pstep = [&](int t, int a) -> bf16x8 {
+                floatx8 p;
 #pragma unroll
-                for (int a = 0; a < 2; ++a)
-                    oacc[DH * hf + x][a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                        vb[hf][x], pb[a], oacc[DH * hf + x][a], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
+                for (int v = 0; v < 8; ++v) {
+                    p[v] = __builtin_amdgcn_exp2f(fmaf(s[2 * t + (v >> 2)][a][v & 3], c2, t < TP ? neg_m[a] : neg_2[a]));
+                    if (t % TP == 0 && v < 2)
+                        lsum[a][t / TP][v] = p[v];
+                    else
+                        lsum[a][t / TP][v & 1] += p[v];
+                }
+                return __builtin_convertvector(p, bf16x8);
+            };
+            vread(0, vb[0]);
+            bf16x8 pb[2], pbn[2];
+            pbn[0] = pstep(0, 0);
+            pbn[1] = pstep(0, 1);
+#pragma unroll
+            for (int i = 0; i < VSTEPS; ++i) {
+                const int t = i >> 1, hf = i & 1;
+                if (i + 1 < VSTEPS) vread(i + 1, vb[(i + 1) & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+                if (hf == 0) {
+                    pb[0] = pbn[0];
+                    pb[1] = pbn[1];
+                }
+                if (C::PARTS == 2 && i == VSTEPS / 2) {
+#pragma unroll
+                    for (int a = 0; a < 2; ++a) l_run[a] += lsum[a][0][0] + lsum[a][0][1];
+                    if (moved_2) {
+#pragma unroll
+                        for (int a = 0; a < 2; ++a) {
+                            l_run[a] *= alpha_2[a];
+                            lim[a] = m_run[a] + rescale_limit(quad_sum(l_run[a]) + 1.f);
+                            neg_m[a] = neg_2[a];
+#pragma unroll
+                            for (int dt = 0; dt < C::DT; ++dt) oacc[dt][a] *= alpha_2[a];
+                        }
+                    }
+                }
+                if (t + 1 < C::PT) pbn[hf] = pstep(t + 1, hf);
+#pragma unroll
+                for (int x = 0; x < DH; ++x)
+#pragma unroll
+                    for (int a = 0; a < 2; ++a)
+                        oacc[DH * hf + x][a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            vb[hf][x], pb[a], oacc[DH * hf + x][a], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (first_round)
+                __builtin_amdgcn_s_setprio(2);
+            else
+                __builtin_amdgcn_s_setprio(0);
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+                l_run[a] += lsum[a][C::PARTS - 1][0] + lsum[a][C::PARTS - 1][1];
+
+            wait_vmem_all();   // K(jj+1) landed
+            __syncthreads();   // K(jj+1) visible; every wave is done with V(jj)
+            if (jj + 1 < nkeep) copy_v(kept[jj + 1]);
         }
-        if (first_round)
-            __builtin_amdgcn_s_setprio(2);
-        else
-            __builtin_amdgcn_s_setprio(0);
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-            l_run[a] += lsum[a][C::PARTS - 1][0] + lsum[a][C::PARTS - 1][1];
-
-        wait_vmem_all();   // K(jj+1) landed
-        __syncthreads();   // K(jj+1) visible; every wave is done with V(jj)
-        if (jj + 1 < nkeep) copy_v(kept[jj + 1]);
-    }
 
 #pragma unroll
-    for (int a = 0; a < 2; ++a) {
-        const float l_tot = quad_sum(l_run[a]);
-        const bool live = qvalid[a] && l_tot > 0.f;
-        const float inv = live ? 1.0f / l_tot : 0.f;
-        const int q = 32 * wave + 16 * a + qi;  // query of the block
-        const int64_t orow = int64_t(h) * nq * BLK + int64_t(r) * BLK + q;
-        float lse_out = live ? (m_run[a] + __log2f(l_tot)) * kLn2 : -INFINITY;
-        if (tp.piece >= 0) {  // a piece of a split tail row: float32 partial into the workspace
-            const int64_t prow = int64_t(blockIdx.x - tail_first) * BLK + q;
+        for (int a = 0; a < 2; ++a) {
+            const float l_tot = quad_sum(l_run[a]);
+            const bool live = qvalid[a] && l_tot > 0.f;
+            const float inv = live ? 1.0f / l_tot : 0.f;
+            const int q = 32 * wave + 16 * a + qi;  // query of the block
+            const int64_t orow = int64_t(h) * nq * BLK + int64_t(r) * BLK + q;
+            float lse_out = live ? (m_run[a] + __log2f(l_tot)) * kLn2 : -INFINITY;
+            if (tp.piece >= 0) {  // a piece of a split tail row: float32 partial into the workspace
+                const int64_t prow = int64_t(blockIdx.x - tail_first) * BLK + q;
+#pragma unroll
+                for (int dt = 0; dt < C::DT; ++dt) {
+                    float4 o;
+                    o.x = live ? oacc[dt][a][0] * inv : 0.f;
+                    o.y = live ? oacc[dt][a][1] * inv : 0.f;
+                    o.z = live ? oacc[dt][a][2] * inv : 0.f;
+                    o.w = live ? oacc[dt][a][3] * inv : 0.f;
+                    *reinterpret_cast<float4*>(part_o + prow * D + 16 * dt + 4 * g) = o;
+                }
+                if (g == 0) part_lse[prow] = lse_out;
+                continue;
+            }
+            float ka = 0.f, kb = 1.f;
+            bool store = true;
+            if (!OUT_BF16 && acc) {
+                store = live;
+                if (live) {
+                    const float la2 = lse[orow] * kLog2e;
+                    const float lb2 = m_run[a] + __log2f(l_tot);
+                    const float mm = fmaxf(la2, lb2);
+                    const float wa = (la2 == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(la2 - mm);
+                    const float wb = __builtin_amdgcn_exp2f(lb2 - mm);
+                    const float t = wa + wb;
+                    ka = wa / t;
+                    kb = wb / t;
+                    lse_out = (mm + __log2f(t)) * kLn2;
+                }
+            }
+            if (!store) continue;
 #pragma unroll
             for (int dt = 0; dt < C::DT; ++dt) {
-                float4 o;
-                o.x = live ? oacc[dt][a][0] * inv : 0.f;
-                o.y = live ? oacc[dt][a][1] * inv : 0.f;
-                o.z = live ? oacc[dt][a][2] * inv : 0.f;
-                o.w = live ? oacc[dt][a][3] * inv : 0.f;
-                *reinterpret_cast<float4*>(part_o + prow * D + 16 * dt + 4 * g) = o;
-            }
-            if (g == 0) part_lse[prow] = lse_out;
-            continue;
-        }
-        float ka = 0.f, kb = 1.f;
-        bool store = true;
-        if (!OUT_BF16 && acc) {
-            store = live;
-            if (live) {
-                const float la2 = lse[orow] * kLog2e;
-                const float lb2 = m_run[a] + __log2f(l_tot);
-                const float mm = fmaxf(la2, lb2);
-                const float wa = (la2 == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(la2 - mm);
-                const float wb = __builtin_amdgcn_exp2f(lb2 - mm);
-                const float t = wa + wb;
-                ka = wa / t;
-                kb = wb / t;
-                lse_out = (mm + __log2f(t)) * kLn2;
-            }
-        }
-        if (!store) continue;
+                const int d0 = 16 * dt + 4 * g;
+                float o4[4];
 #pragma unroll
-        for (int dt = 0; dt < C::DT; ++dt) {
-            const int d0 = 16 * dt + 4 * g;
-            float o4[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) o4[u] = live ? oacc[dt][a][u] * inv : 0.f;
-            if constexpr (OUT_BF16) {
-                uint16_t* op = static_cast<uint16_t*>(O) + orow * D + d0;
-                uint2 w;
-                w.x = f32_to_bf16_bits(o4[0]) | (f32_to_bf16_bits(o4[1]) << 16);
-                w.y = f32_to_bf16_bits(o4[2]) | (f32_to_bf16_bits(o4[3]) << 16);
-                *reinterpret_cast<uint2*>(op) = w;
-            } else {
-                float* op = static_cast<float*>(O) + orow * D + d0;
-                if (acc) {
-                    const float4 prev = *reinterpret_cast<const float4*>(op);
-                    o4[0] = ka * prev.x + kb * o4[0];
-                    o4[1] = ka * prev.y + kb * o4[1];
-                    o4[2] = ka * prev.z + kb * o4[2];
-                    o4[3] = ka * prev.w + kb * o4[3];
+                for (int u = 0; u < 4; ++u) o4[u] = live ? oacc[dt][a][u] * inv : 0.f;
+                if constexpr (OUT_BF16) {
+                    uint16_t* op = static_cast<uint16_t*>(O) + orow * D + d0;
+                    uint2 w;
+                    w.x = f32_to_bf16_bits(o4[0]) | (f32_to_bf16_bits(o4[1]) << 16);
+                    w.y = f32_to_bf16_bits(o4[2]) | (f32_to_bf16_bits(o4[3]) << 16);
+                    *reinterpret_cast<uint2*>(op) = w;
+                } else {
+                    float* op = static_cast<float*>(O) + orow * D + d0;
+                    if (acc) {
+                        const float4 prev = *reinterpret_cast<const float4*>(op);
+                        o4[0] = ka * prev.x + kb * o4[0];
+                        o4[1] = ka * prev.y + kb * o4[1];
+                        o4[2] = ka * prev.z + kb * o4[2];
+                        o4[3] = ka * prev.w + kb * o4[3];
+                    }
+                    *reinterpret_cast<float4*>(op) = make_float4(o4[0], o4[1], o4[2], o4[3]);
                 }
-                *reinterpret_cast<float4*>(op) = make_float4(o4[0], o4[1], o4[2], o4[3]);
             }
+            if (lse && g == 0) lse[orow] = lse_out;
         }
-        if (lse && g == 0) lse[orow] = lse_out;
     }
 }
 
@@ -1273,22 +1310,31 @@ hipError_t launch_rows(const Geom& g, const void* Q, const int32_t* sel, int kee
     const float c2 = scale * kLog2e;
     const size_t dyn = size_t(keep) * sizeof(int32_t);
     constexpr int THREADS = CfgRows<D, BLK>::THREADS;
+    if constexpr (BLK == 128) {  // (64-token rows come here with all blocks only)
+        if (part.shards.n > 1) {   // (never with a workspace, an order or bf16 output)
+            attn_rows_kernel<D, BLK, false, false, true><<<G, THREADS, dyn, s>>>(
+                (const uint16_t*)Q, sel, slot_of, (const uint16_t*)Kp, (const uint16_t*)Vp, O, lse,
+                g.L, g.n, g.i0, g.nq, keep, cap, c2, 0, 0, part.h_lo, n_heads, part.acc, 1, nullptr,
+                G, 1, nullptr, nullptr, nullptr, part.shards);
+            return hipGetLastError();
+        }
+    }
     TailPlan tp;
     void* partials = nullptr;
-    if (hipError_t e = balanced_plan(attn_rows_kernel<D, BLK, true, false>, THREADS, dyn, g, part, sel,
+    if (hipError_t e = balanced_plan(attn_rows_kernel<D, BLK, true, false, false>, THREADS, dyn, g, part, sel,
                                      keep, G, int64_t(BLK) * (D + 1) * 4, s, &tp, &partials);
         e != hipSuccess)
         return e;
     const TailSpace ts = tp.k > 1 ? tail_space(partials, tp, G, D, BLK) : TailSpace{nullptr, nullptr};
     const int grid = tp.first + (G - tp.first) * tp.k;
-    auto* kern = part.order ? (out_bf16 ? attn_rows_kernel<D, BLK, true, true>
-                                        : attn_rows_kernel<D, BLK, false, true>)
-                            : (out_bf16 ? attn_rows_kernel<D, BLK, true, false>
-                                        : attn_rows_kernel<D, BLK, false, false>);
+    auto* kern = part.order ? (out_bf16 ? attn_rows_kernel<D, BLK, true, true, false>
+                                        : attn_rows_kernel<D, BLK, false, true, false>)
+                            : (out_bf16 ? attn_rows_kernel<D, BLK, true, false, false>
+                                        : attn_rows_kernel<D, BLK, false, false, false>);
     kern<<<grid, THREADS, dyn, s>>>(
         (const uint16_t*)Q, sel, slot_of, (const uint16_t*)Kp, (const uint16_t*)Vp, O, lse, g.L, g.n,
         g.i0, g.nq, keep, cap, c2, part.kv_lo, part.kv_hi, part.h_lo, n_heads, part.acc, 1,
-        part.order, tp.first, tp.k, ts.part_o, ts.part_lse, tp.row_sort);
+        part.order, tp.first, tp.k, ts.part_o, ts.part_lse, tp.row_sort, NoShards{});
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || tp.k < 2) return e;
     return out_bf16 ? launch_tail_merge<D, BLK, true>(g, part, tp, G, ts.part_o, ts.part_lse, O, lse, s)
@@ -1306,26 +1352,33 @@ hipError_t launch_shape(const Geom& g, const void* Q, const int32_t* sel, int ke
     const float c2 = scale * kLog2e;
     const int remap = 1;
     const size_t dyn = size_t(keep) * sizeof(int32_t);
+    if (part.shards.n > 1) {  // (never with a workspace, an order or bf16 output)
+        attn_bf16_kernel<D, BLK, false, true><<<G, C::THREADS, dyn, s>>>(
+            (const uint16_t*)Q, sel, slot_of, (const uint16_t*)Kp, (const uint16_t*)Vp, O, lse, g.L,
+            g.n, g.i0, g.nq, keep, cap, c2, 0, 0, part.h_lo, n_heads, part.acc, remap, nullptr, G, 1,
+            nullptr, nullptr, nullptr, part.shards);
+        return hipGetLastError();
+    }
     TailPlan tp;
     void* partials = nullptr;
-    if (hipError_t e = balanced_plan(attn_bf16_kernel<D, BLK, true>, C::THREADS, dyn, g, part,
+    if (hipError_t e = balanced_plan(attn_bf16_kernel<D, BLK, true, false>, C::THREADS, dyn, g, part,
                                      sel, keep, G, int64_t(BLK) * (D + 1) * 4, s, &tp, &partials);
         e != hipSuccess)
         return e;
     const TailSpace ts = tp.k > 1 ? tail_space(partials, tp, G, D, BLK) : TailSpace{nullptr, nullptr};
     const int grid = tp.first + (G - tp.first) * tp.k;
     if (out_bf16)
-        attn_bf16_kernel<D, BLK, true><<<grid, C::THREADS, dyn, s>>>(
+        attn_bf16_kernel<D, BLK, true, false><<<grid, C::THREADS, dyn, s>>>(
             (const uint16_t*)Q, sel, slot_of, (const uint16_t*)Kp, (const uint16_t*)Vp, O, lse,
             g.L, g.n, g.i0, g.nq, keep, cap, c2, part.kv_lo, part.kv_hi, part.h_lo, n_heads,
             part.acc, remap, part.order, tp.first, tp.k, ts.part_o, ts.part_lse,
-            tp.row_sort);
+            tp.row_sort, NoShards{});
     else
-        attn_bf16_kernel<D, BLK, false><<<grid, C::THREADS, dyn, s>>>(
+        attn_bf16_kernel<D, BLK, false, false><<<grid, C::THREADS, dyn, s>>>(
             (const uint16_t*)Q, sel, slot_of, (const uint16_t*)Kp, (const uint16_t*)Vp, O, lse,
             g.L, g.n, g.i0, g.nq, keep, cap, c2, part.kv_lo, part.kv_hi, part.h_lo, n_heads,
             part.acc, remap, part.order, tp.first, tp.k, ts.part_o, ts.part_lse,
-            tp.row_sort);
+            tp.row_sort, NoShards{});
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || tp.k < 2) return e;
     return out_bf16 ? launch_tail_merge<D, BLK, true>(g, part, tp, G, ts.part_o, ts.part_lse, O, lse, s)
@@ -1394,7 +1447,8 @@ bool rows64(const Geom& g, int keep, int G) {
     return G <= 1024 || (G >= 1664 && G <= 2000) || G > 2560;
 }
 bool whole_rows(const Geom& g, const AttnPart& p) {
-    return !p.acc && p.kv_lo == 0 && p.kv_hi == g.n && p.h_lo == 0 && p.h_hi == g.H;
+    return !p.acc && p.kv_lo == 0 && p.kv_hi == g.n && p.h_lo == 0 && p.h_hi == g.H &&
+           p.shards.n <= 1;
 }
 
 }  // namespace
@@ -1434,21 +1488,21 @@ int64_t attn_tail_workspace_bytes(const Geom& g, int keep) {
     if (g.block == 128 && (g.d == 64 || g.d == 128)) {
         const bool few = split_key128(g.H * g.nq, keep, true);
         if (g.d == 64)
-            slots = few ? resident_slots(attn_bf16_kernel<64, 128, true>, Cfg<64, 128>::THREADS, dyn)
-                        : resident_slots(attn_rows_kernel<64, 128, true, false>,
+            slots = few ? resident_slots(attn_bf16_kernel<64, 128, true, false>, Cfg<64, 128>::THREADS, dyn)
+                        : resident_slots(attn_rows_kernel<64, 128, true, false, false>,
                                          CfgRows<64, 128>::THREADS, dyn);
         else
-            slots = few ? resident_slots(attn_bf16_kernel<128, 128, true>, Cfg<128, 128>::THREADS, dyn)
-                        : resident_slots(attn_rows_kernel<128, 128, true, false>,
+            slots = few ? resident_slots(attn_bf16_kernel<128, 128, true, false>, Cfg<128, 128>::THREADS, dyn)
+                        : resident_slots(attn_rows_kernel<128, 128, true, false, false>,
                                          CfgRows<128, 128>::THREADS, dyn);
     } else if (g.block == 64 && (g.d == 64 || g.d == 128)) {
         if (g.d == 64)
-            slots = resident_slots(attn_bf16_kernel<64, 64, true>, Cfg<64, 64>::THREADS, dyn);
+            slots = resident_slots(attn_bf16_kernel<64, 64, true, false>, Cfg<64, 64>::THREADS, dyn);
         else
             slots = rows64(g, keep, g.H * g.nq)
-                        ? resident_slots(attn_rows_kernel<128, 64, true, false>,
+                        ? resident_slots(attn_rows_kernel<128, 64, true, false, false>,
                                          CfgRows<128, 64>::THREADS, dyn)
-                        : resident_slots(attn_bf16_kernel<128, 64, true>, Cfg<128, 64>::THREADS, dyn);
+                        : resident_slots(attn_bf16_kernel<128, 64, true, false>, Cfg<128, 64>::THREADS, dyn);
     }
     if (slots <= 0) return 0;
     // the row order, then the tail pieces, which never outnumber the resident slots

@@ -16,16 +16,17 @@
 //
 // run_chunks executes a plan on one stream. Everything the plan reads is in
 // place when the call's work starts (the call is stream-ordered), so the chunks
-// need not be launches of their own: the chunks of one shard share a launch over
-// all their heads (chunk_steps). A head still folds its shards one after another in
-// plan order through the log-sum-exp inside the attention kernel, each with a softmax
-// of its own, so the result has the rounding of a chunk-by-chunk run; query blocks
-// with no kept block in a shard exit without touching memory. One launch per chunk
-// leaves the GPU to the longest row of each of a few heads: 40 heads x 147 rows, 591
-// blocks of 128, 89 kept, four owners, 31 chunks took 6.85 ms, the four launches
-// 4.75 ms. (All shards in one launch take 3.93 ms, but a row then has one softmax for
-// all of them and fewer exact top probabilities: error of O against 64 bits 6.4e-4
-// instead of 6.3e-4.) Heads that no chunk covers end as the empty result.
+// need not be launches of their own: the chunks of one shard are one step over all
+// their heads (chunk_steps), and in bf16 the steps over the same heads are one launch,
+// each row taking its shards one after another. A head still folds its shards in plan
+// order through the log-sum-exp inside the attention kernel, each with a softmax of its
+// own, so the result has the rounding of a chunk-by-chunk run; shards with no kept
+// block of a row cost it the look at its list. One launch per chunk leaves the GPU to
+// the longest row of each of a few heads, and one per shard to the longest of each
+// shard: 40 heads x 147 rows, 591 blocks of 128, 89 kept, four owners, 31 chunks took
+// 6.84 ms, four launches 4.75 ms, one 4.25 ms. (One softmax for all shards would take
+// 3.80 ms, but then fewer top probabilities are exact: error of O against 64 bits
+// 6.4e-4 instead of 6.3e-4.) Heads that no chunk covers end as the empty result.
 #include <new>
 
 #include "sparsp_internal.h"
@@ -66,10 +67,25 @@ hipError_t run_chunks(const Geom& g, const void* Q, const int32_t* sel, int keep
                       hipStream_t s) {
     const Run run{g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale, O, lse, s};
     try {
-        for (const ChunkStep& step : chunk_steps(g.H, plan, n_chunks)) {
-            const hipError_t e =
-                step.clear ? run.clear(step.part.h_lo, step.part.h_hi) : run.attend(step.part);
-            if (e != hipSuccess) return e;
+        const std::vector<ChunkStep> steps = chunk_steps(g.H, plan, n_chunks);
+        for (size_t i = 0; i < steps.size();) {
+            AttnPart part = steps[i].part;
+            if (steps[i].clear) {
+                if (hipError_t e = run.clear(part.h_lo, part.h_hi); e != hipSuccess) return e;
+                ++i;
+                continue;
+            }
+            // The steps that follow over the same heads, in one launch. (A part of all
+            // blocks stays alone: it may be a kernel of its own.)
+            const bool joins = g.bf16 && part.kv_hi - part.kv_lo < g.n;
+            Shards& sh = part.shards;
+            do {
+                sh.lo[sh.n] = steps[i].part.kv_lo;
+                sh.hi[sh.n++] = steps[i++].part.kv_hi;
+            } while (joins && sh.n < kMaxShards && i < steps.size() && !steps[i].clear &&
+                     steps[i].part.acc && steps[i].part.h_lo == part.h_lo &&
+                     steps[i].part.h_hi == part.h_hi);
+            if (hipError_t e = run.attend(part); e != hipSuccess) return e;
         }
     } catch (const std::bad_alloc&) {  // no exception may leave the C entry
         return hipErrorOutOfMemory;

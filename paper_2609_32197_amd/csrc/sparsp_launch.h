@@ -52,6 +52,11 @@ hipError_t launch_demand_gather(const Geom& g, const uint64_t* mask, const void*
 // (O, lse) already hold a running result and the part is folded into it
 // through the log-sum-exp instead of overwriting it; rows without a kept key
 // in the part are left untouched.
+constexpr int kMaxShards = 16;
+struct Shards {  // block ranges [lo, hi) that a launch attends one after another
+    int n = 0;
+    int lo[kMaxShards] = {}, hi[kMaxShards] = {};
+};
 struct AttnPart {
     int kv_lo, kv_hi, h_lo, h_hi, acc;
     const int32_t* order = nullptr;  // workgroup w takes row order[w] (longest first), if set
@@ -60,6 +65,10 @@ struct AttnPart {
     // whose float32 partials go here and are merged by a second kernel.
     void* ws = nullptr;
     int64_t ws_bytes = 0;
+    // bf16 launches only: with shards.n > 1 these ranges take the place of
+    // [kv_lo, kv_hi), each with a softmax of its own and folded in turn, as launches of
+    // their own would be.
+    Shards shards;
 };
 
 // Packed K/V copies of n_vheads virtual heads (virtual head v reads head v % g.H).
@@ -117,12 +126,12 @@ hipError_t launch_fill_identity(float* O, float* lse, int64_t rows, int d, hipSt
 int plan_chunks(const Geom& g, const uint64_t* demand, int ranks, int rank, int heads_per_chunk,
                 int tail_heads_per_chunk, sparsp_chunk* out, int max_chunks);
 
-// Host: the launches of a plan. Every head attends its chunks' block ranges in plan
+// Host: the steps of a plan. Every head attends its chunks' block ranges in plan
 // order, each but the first folded into the ones before (acc = 1); chunks of one
-// block range that no such order keeps apart share a launch where their heads adjoin.
-// Never more attention launches than the plan has chunks; a schedule of plan_chunks
+// block range that no such order keeps apart share a step where their heads adjoin.
+// Never more attention steps than the plan has chunks; a schedule of plan_chunks
 // takes one per shard. A step with `clear` gives its heads the empty result instead:
-// before a launch that folds into some of its heads only, and at the end for heads
+// before a step that folds into some of its heads only, and at the end for heads
 // that no chunk covers.
 struct ChunkStep {
     bool clear;

@@ -5,8 +5,7 @@ The reference is the calls the plan stands for: sparsp_block_sparse_attn_part
 per chunk in plan order, from the empty result. The kernel depends on a launch's
 number of rows, so chunks that share a launch may round elsewhere: held to the bars
 of the parity suite (1e-5; 2e-2 max-abs and 1e-3 mean-abs; lse 1e-5 and 1e-4). A
-schedule's launches are one per shard over all heads, and equal those calls bit for
-bit.
+schedule takes each shard over all heads, and equals those calls bit for bit.
 """
 
 import math
@@ -55,9 +54,15 @@ def test_plan_equals_its_parts(gpu, geo, name):
     assert np.abs(ln[fin] - rn[fin]).max(initial=0) <= (1e-4 if g.dtype == sp.BF16 else 1e-5)
 
 
-@pytest.mark.parametrize("geo", GEOMS + [(12, 9000, 128, 128, 10, 60, "bf16")],
-                         ids=lambda g: "d{2}b{3}_{6}".format(*g) + ("" if g[0] == 5 else "_many"))
-@pytest.mark.parametrize("ranks", [1, 4])
+MANY = [(12, 9000, 128, 128, 10, 60, "bf16"), (3, 3000, 64, 128, 0, 24, "bf16"),
+        (12, 3000, 64, 128, 0, 24, "bf16"), (12, 5000, 128, 64, 0, 60, "bf16")]
+
+
+# (a launch takes up to 16 shards one after another)
+@pytest.mark.parametrize("geo, ranks", [(g, r) for g in GEOMS + MANY for r in (1, 4)]
+                         + [(g, r) for g in MANY for r in (16, 17, 23)],
+                         ids=lambda v: v if isinstance(v, int) else
+                         "h{0}d{2}b{3}_{6}".format(*v))
 def test_schedule_folds_one_shard_after_another(gpu, geo, ranks):
     """Each shard has a softmax of its own, as when shards arrive one by one: attending
     them together would round more (bf16: fewer top probabilities are exact)."""
