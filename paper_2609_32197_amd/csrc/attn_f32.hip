@@ -105,6 +105,7 @@ __host__ __device__ constexpr int merge_floats(int DC, int NQ) {
 }
 
 constexpr int kCus = 256;  // of an MI355X
+constexpr int kPastSlot = 1 << 30;  // a byte offset past every slot (256 x 128 x 4 at most)
 
 // DC: 16-wide chunks of d (d <= 16 DC); NQ: 16-query groups per wave.
 template <int DC, int NQ>
@@ -177,8 +178,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void a
     if (acc && nkeep == 0) return;  // nothing to fold in
     const int last_cnt = L - (L / block) * block;  // valid keys of a partial last block
 
-    // Q^T operands. Elements past d are zero, so whatever finite value the K
-    // operand holds there drops out.
+    // Q^T operands. Elements past d are zero, as they are in the K operand.
     floatx4 qf[NQ][DC];
     bool qvalid[NQ];
 #pragma unroll
@@ -197,17 +197,20 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void a
 
     floatx4 o[NQ][DC];
     float m[NQ], l[NQ], lim[NQ];         // lim: where m moves, kRescale above it
+    float off[NQ];                       // m, or 0 while the query has no score above -inf
     const float slack = kRescale / c2;  // in unscaled scores
 #pragma unroll
     for (int a = 0; a < NQ; ++a) {
         m[a] = lim[a] = -INFINITY;
-        l[a] = 0.f;
+        l[a] = off[a] = 0.f;
 #pragma unroll
         for (int c = 0; c < DC; ++c) o[a][c] = floatx4{};
     }
 
     // Copy offsets: lane 4 i + p of instruction c brings row i (a key of K, a
-    // dim 16 c + i of V^T), chunk p ^ (i / 4) of its four.
+    // dim 16 c + i of V^T), chunk p ^ (i / 4) of its four. A chunk past d would be the
+    // next key's: it is asked for past the end of the slot, which reads as zero (an
+    // infinite value times the query's zero would be NaN).
     const float* lk = reinterpret_cast<const float*>(smem) + wave * 2 * DC * 256;
     const float* lv = lk + DC * 256;
     const uint32_t lk_at = uint32_t(reinterpret_cast<uintptr_t>(lk));
@@ -217,7 +220,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void a
         const int i = lane >> 2, p = (lane & 3) ^ ((lane >> 4) & 3);
 #pragma unroll
         for (int c = 0; c < DC; ++c) {
-            koff[c] = (i * d + 16 * c + 4 * p) * 4;
+            koff[c] = 16 * c + 4 * p < d ? (i * d + 16 * c + 4 * p) * 4 : kPastSlot;
             voff[c] = ((16 * c + i) * block + 4 * p) * 4;
         }
     }
@@ -298,8 +301,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void a
             const float mx = quad_max(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])));
             if (__ballot(mx > lim[a]) != 0) {
                 const float m_new = fmaxf(m[a], mx);
-                const float alpha = __builtin_amdgcn_exp2f((m[a] - m_new) * c2);
+                const float to = m_new == -INFINITY ? 0.f : m_new;
+                const float alpha = __builtin_amdgcn_exp2f((m[a] - to) * c2);
                 m[a] = m_new;
+                off[a] = to;
                 lim[a] = m_new + slack;
                 l[a] *= alpha;
 #pragma unroll
@@ -307,7 +312,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void a
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                s[a][0][u] = __builtin_amdgcn_exp2f((x[u] - m[a]) * c2);
+                s[a][0][u] = __builtin_amdgcn_exp2f((x[u] - off[a]) * c2);
                 l[a] += s[a][0][u];
             }
         }

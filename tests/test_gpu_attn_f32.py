@@ -94,3 +94,41 @@ def test_float32_attention_at_large_scales(gpu, scale):
     ln, fin = lse.cpu().numpy(), np.isfinite(lse_ref)
     assert (np.isneginf(ln) == ~fin).all()
     assert (np.abs(ln[fin] - lse_ref[fin]) <= 1e-5 + 4 * 2.0 ** -24 * np.abs(lse_ref[fin])).all()
+
+
+@pytest.mark.parametrize("d", [32, 20])
+def test_float32_attention_of_infinite_scores(gpu, d):
+    """Keys of -inf under queries that are positive score -inf and weigh nothing, also
+    where they fill a wave's first tiles, or a row's whole list; the keys beside them in
+    memory count as ever (d = 20 leaves part of a 16-wide step of the product to
+    padding). Bars as above; q.k of 32 uniform products is below 32."""
+    H, L, b, i0, i1, keep = 2, 1100, 64, 0, 18, 6
+    rng = np.random.default_rng(23)
+    q = rng.uniform(0.1, 1.0, (H, L, d)).astype(np.float32)
+    k, v = (rng.standard_normal((H, L, d)).astype(np.float32) for _ in range(2))
+    g = P.geometry(H, L, d, b, i0, i1, "f32")
+    om, osel, sel, _ = _pipeline(q, k, v, g, "f32", keep)
+    gone = rng.random((H, L)) < 0.3                # single keys,
+    for h in range(H):
+        gone[h, osel[h, 2, 0] * b:(osel[h, 2, 0] + 1) * b] = True  # a first block,
+        for j in osel[h, 7]:                       # and all that one row keeps
+            gone[h, j * b:(j + 1) * b] = True
+    k[gone] = -np.inf
+    mask = P.torch().from_numpy(P.words_as_int64(om)).cuda()
+    out = sp.sparsp_demand_union_gather(g, mask, P.to_device(k, "f32"), P.to_device(v, "f32"))
+    O, lse = sp.sparsp_block_sparse_attn(g, P.to_device(q, "f32"), sel, out["slot_of"],
+                                         out["K_packed"], out["V_packed"], ctypes_scale(d))
+    ln = lse.cpu().numpy()
+    assert not np.isfinite(ln[:, 7 * b:8 * b]).any()
+    x = np.einsum("hqd,hkd->hqk", q.astype(np.float64), k.astype(np.float64)) * ctypes_scale(d)
+    kept = np.repeat(np.repeat(om, b, 1), b, 2)[:, :L, :L]
+    x[~kept] = -np.inf
+    m = x.max(2, keepdims=True)
+    p = np.exp(x - np.where(np.isfinite(m), m, 0.0))
+    l = p.sum(2, keepdims=True)
+    O_ref = np.divide(p @ v.astype(np.float64), l, out=np.zeros((H, L, d)), where=l > 0)
+    assert np.abs(O.cpu().numpy()[:, :L] - O_ref).max() <= 1e-5
+    fin = l[..., 0] > 0
+    lse_ref = (m + np.log(np.where(l > 0, l, 1.0)))[..., 0]
+    assert (np.isneginf(ln[:, :L]) == ~fin).all()
+    assert np.abs(ln[:, :L][fin] - lse_ref[fin]).max() <= 1e-5
