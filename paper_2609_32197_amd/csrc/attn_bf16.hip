@@ -972,9 +972,11 @@ void attn_rows_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
                         (m_new == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m_run[a] - m_new);
                     m_run[a] = m_new;
                     l_run[a] *= alpha;
-                    // (a limit that may let m fall has to be the same in a query's four lanes)
+                    // (a limit that may let m fall has to be the same in a query's four lanes;
+                    // the other is that of the 32x32x16 layout, whose lane pair shares the
+                    // keys of the lanes l and l^32 here: the max moves where it moves there)
                     lim[a] = m_run[a] + (C::DOWN ? rescale_limit(quad_sum(l_run[a]) + 1.f)
-                                                 : rescale_threshold(l_run[a]));
+                                                 : rescale_threshold(pair_sum(l_run[a])));
                     neg_m[a] = (m_run[a] == -INFINITY) ? 0.f : -m_run[a];
 #pragma unroll
                     for (int dt = 0; dt < C::DT; ++dt) oacc[dt][a] *= alpha;
