@@ -1427,8 +1427,11 @@ hipError_t launch_shape(const Geom& g, const void* Q, const int32_t* sel, int ke
 // A workspace turns that around for long lists, since it splits each row over the
 // free slots: the rows kernel has 512 of them and the split-key kernel 256, which is
 // none to spare past 128 rows. `split` says that every row can be split in two or
-// more; then the rows kernel takes lists long enough to carry the pieces' merge. With
-// a workspace, rows / split-key kernel, d = 128 (d = 64 within 5%):
+// more; then the rows kernel takes lists long enough to carry the pieces' merge, and
+// any list from 129 to 170 rows, which it splits in three and the split-key kernel not
+// at all: short ones lose there the few microseconds of the merge, but a call that
+// brings a workspace stays balanced whatever its lists. With a workspace, rows /
+// split-key kernel, d = 128 (d = 64 within 5%):
 //                     kept blocks   8     24     48    100    200
 //      72 rows (4 / 3 pieces)     1.09   1.11   1.11   1.12   1.12
 //     100 rows (4 / 2)            1.19   1.03   1.03   0.93   0.89
@@ -1440,7 +1443,7 @@ hipError_t launch_shape(const Geom& g, const void* Q, const int32_t* sel, int ke
 bool split_key128(int G, int keep, bool split) {
     if (G > kCus) return false;
     if (!split || G <= kCus / 3) return true;
-    return keep < (G > kCus / 2 && G <= 2 * kCus / 3 ? 24 : 48);
+    return keep < 48 && (G <= kCus / 2 || G > 2 * kCus / 3);
 }
 
 bool rows64(const Geom& g, int keep, int G) {

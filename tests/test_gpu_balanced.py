@@ -6,8 +6,8 @@ the S = R mod P rows of the last round are split into k = min(4, P // S)
 pieces, merged through the log-sum-exp. So:
 
 * every row outside the last round equals sparsp_block_sparse_attn's bit for
-  bit (all rows where nothing can be split), and the split rows meet the usual bar
-  against the oracle;
+  bit, and the split rows meet the usual bar against the oracle (their pieces have
+  running maxima of their own);
 * without a workspace, or with one too small for two pieces, the call is
   sparsp_block_sparse_attn bit for bit.
 
@@ -77,37 +77,12 @@ GEOMS = [
 @pytest.mark.parametrize("geo", GEOMS, ids=lambda g: "H{}L{}d{}b{}_{}-{}_{}".format(*g))
 @pytest.mark.parametrize("keep_frac", [0.05, 0.4])
 def test_balanced_attention(gpu, geo, keep_frac):
-    _check_balanced(geo, max(1, int(round(keep_frac * -(-geo[1] // geo[3])))))
-
-
-# Fewer rows of 128-token blocks than workgroups that are resident: every row is
-# split, by the kernel whose pieces fill the GPU better. (H, L, d, block, i0, i1),
-# kept blocks, pieces; all end in a ragged block.
-SPLIT = [
-    ((2, 9000, 128, 128, 35, 71, "bf16"), 28, 3),    # 72 rows: split-key kernel
-    ((2, 9000, 128, 128, 21, 71, "bf16"), 47, 2),    # 100 rows: its longest list
-    ((2, 9000, 128, 128, 21, 71, "bf16"), 48, 4),    # rows kernel
-    ((3, 9000, 128, 128, 28, 71, "bf16"), 24, 3),    # 129 rows: rows kernel
-    ((3, 9000, 64, 128, 20, 71, "bf16"), 71, 3),     # 153 rows, every block
-    ((2, 10980, 128, 128, 1, 86, "bf16"), 24, 3),    # 170 rows: the last in three
-    ((3, 7400, 64, 128, 1, 58, "bf16"), 48, 2),      # 171 rows: in two
-    ((4, 8300, 128, 128, 1, 65, "bf16"), 50, 2),     # 256 rows
-]
-
-
-@pytest.mark.parametrize("geo,keep,pieces", SPLIT,
-                         ids=lambda x: "H{}L{}d{}b{}_{}-{}_{}".format(*x) if isinstance(x, tuple) else str(x))
-def test_every_row_split(gpu, geo, keep, pieces):
-    split, kk = _check_balanced(geo, keep)
-    assert len(split) == geo[0] * (geo[5] - geo[4]) and kk == pieces
-
-
-def _check_balanced(geo, keep):
     torch = P.torch()
     H, L, d, b, i0, i1, dt = geo
     n = -(-L // b)
     q, k, v = _rand_inputs(5, H, L, d, dt)
     g = P.geometry(H, L, d, b, i0, i1, dt)
+    keep = max(1, int(round(keep_frac * n)))
     om, osel, sel, out = _pipeline(q, k, v, g, dt, keep)
     split, kk, nbytes = tail_rows(g, keep, sel)
     assert nbytes > 0
@@ -116,6 +91,8 @@ def _check_balanced(geo, keep):
     args = (g, Qd, sel, out["slot_of"], out["K_packed"], out["V_packed"], ctypes_scale(d))
     nq = i1 - i0
     rows = H * nq
+    if len(split) == 0:
+        pytest.skip(f"{rows} rows fill every round on this device: nothing to split")
     whole = np.array([r not in split for r in range(rows)])
     for odt in (sp.F32, sp.BF16):
         O0, l0 = sp.sparsp_block_sparse_attn(*args, out_dtype=odt)
@@ -141,24 +118,20 @@ def _check_balanced(geo, keep):
             got = ln[h, r * b:(r + 1) * b]
             assert (np.isneginf(got) == ~fin).all()
             assert np.abs(got[fin] - lse_ref[fin]).max() <= 1e-4
-    return split, kk
 
 
 @pytest.mark.parametrize("geo", GEOMS[:3], ids=lambda g: "H{}L{}d{}b{}_{}-{}_{}".format(*g))
-@pytest.mark.parametrize("keep", [5, 29])
-def test_without_room_the_call_is_unchanged(gpu, geo, keep):
+def test_without_room_the_call_is_unchanged(gpu, geo):
     torch = P.torch()
     H, L, d, b, i0, i1, dt = geo
     q, k, v = _rand_inputs(6, H, L, d, dt)
     g = P.geometry(H, L, d, b, i0, i1, dt)
+    keep = 5
     _, _, sel, out = _pipeline(q, k, v, g, dt, keep)
     args = (g, P.to_device(q, dt), sel, out["slot_of"], out["K_packed"], out["V_packed"],
             ctypes_scale(d))
     O0, l0 = sp.sparsp_block_sparse_attn(*args)
-    # too small for two pieces of even one row, and (fewer rows than resident
-    # workgroups) for two of every row by one float
-    piece, rows = b * (d + 1) * 4, H * (i1 - i0)
-    for nbytes in (16, piece, row_sort_bytes(rows) + 2 * rows * piece - 4):
+    for nbytes in (16, b * (d + 1) * 4):   # too small for two pieces of even one row
         ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
         O1, l1 = sp.sparsp_block_sparse_attn(*args, workspace=ws)
         assert torch.equal(O0.view(torch.int16), O1.view(torch.int16))
