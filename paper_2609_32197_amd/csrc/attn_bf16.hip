@@ -665,14 +665,14 @@ void attn_bf16_kernel(const uint16_t* __restrict__ Q, const int32_t* __restrict_
 }
 
 // Kernel for 128-token blocks (and, with two waves, 64-token ones at d = 128): two
-// independent workgroups per CU. Four waves per workgroup, wave w owning queries 32 w .. +31 and every key of each kept
-// block, so each wave runs one online softmax and no merge is needed; single
-// K and V tile buffers (64 KB of LDS at d = 128). The two waves that share a
-// SIMD belong to different workgroups and are not held in step by a common
-// barrier, so one can run its MFMAs while the other runs its softmax. The K
-// copy of block j+1 is issued once every wave has finished the scores of
-// block j, the V copy once the output product of block j is done; each copy
-// thus has half a block of compute to land.
+// independent workgroups per CU. Four waves per workgroup, wave w owning queries
+// 32 w .. +31 and every key of each kept block, so each wave runs one online softmax
+// and no merge is needed; single K and V tile buffers (64 KB of LDS at d = 128). The
+// two waves that share a SIMD belong to different workgroups and are not held in step
+// by a common barrier, so one can run its MFMAs while the other runs its softmax. The
+// K copy of block j+1 is issued once every wave has finished the scores of block j,
+// the V copy once the output product of block j is done; each copy thus has half a
+// block of compute to land.
 //
 // Products use v_mfma_f32_16x16x32_bf16. The part runs at its power limit here,
 // and this form does more work per joule than 32x32x16: with operands in
@@ -1429,9 +1429,10 @@ hipError_t launch_shape(const Geom& g, const void* Q, const int32_t* sel, int ke
 // none to spare past 128 rows. `split` says that every row can be split in two or
 // more; then the rows kernel takes lists long enough to carry the pieces' merge, and
 // any list from 129 to 170 rows, which it splits in three and the split-key kernel not
-// at all: short ones lose there the few microseconds of the merge, but a call that
-// brings a workspace stays balanced whatever its lists. With a workspace, rows /
-// split-key kernel, d = 128 (d = 64 within 5%):
+// at all: a call that brings a workspace is balanced there whatever its lists. Short
+// ones lose by it (153 rows of 2 / 6 / 12 blocks 25 / 32 / 37 us against 16 / 23 / 33,
+// d = 64 19 / 21 / 25 against 15 / 16 / 23). With a workspace, rows / split-key kernel,
+// d = 128 (d = 64 within 5%):
 //                     kept blocks   8     24     48    100    200
 //      72 rows (4 / 3 pieces)     1.09   1.11   1.11   1.12   1.12
 //     100 rows (4 / 2)            1.19   1.03   1.03   0.93   0.89
