@@ -1421,13 +1421,18 @@ hipError_t launch_shape(const Geom& g, const void* Q, const int32_t* sel, int ke
 // The kernel for 128-token blocks. With at most one row per CU the split-key kernel's
 // eight waves on a row fill its SIMDs, where the rows kernel's four leave each with
 // one wave. Attention alone, rows / split-key (us), d = 128: 50 rows of 30 kept blocks
-// 65 / 59, 190 of 30 67 / 61, of 90 183 / 159, 250 of 6 22 / 23, of 200 428 / 390;
-// d = 64, 250 of 30 49 / 41. Past one row per CU some CU has two, and the rows kernel is
-// ahead.
+// 65 / 59, 190 of 30 67 / 61, of 90 183 / 159, 250 of 200 428 / 390; d = 64, 250 of 30
+// 49 / 41. Past one row per CU some CU has two, and the rows kernel is ahead. The
+// split-key kernel takes longer to begin and to end a row (split-key over rows kernel,
+// 40 and 240 rows):
+//     kept blocks      1            2            3            4            5           8
+//   d = 128       1.20 / 1.17  1.10 / 1.13  1.05 / 1.07  1.01 / 1.04  0.98 / 1.05 0.92 / 0.99
+//   d = 64        1.11 / 1.12  1.04 / 1.07  1.01 / 1.04  0.97 / 1.00  0.95 / 0.98 0.90 / 0.93
+// so the shortest lists stay on the rows kernel.
 // A workspace turns that around for long lists, since it splits each row over the
 // free slots: the rows kernel has 512 of them and the split-key kernel 256, which is
 // none to spare past 128 rows. `split` says that every row can be split in two or
-// more; then the rows kernel takes lists long enough to carry the pieces' merge, and
+// more. Then the rows kernel takes lists long enough to carry the pieces' merge, and
 // any list from 129 to 170 rows, which it splits in three and the split-key kernel not
 // at all: a call that brings a workspace is balanced there whatever its lists. Short
 // ones lose by it (153 rows of 2 / 6 / 12 blocks 25 / 32 / 37 us against 16 / 23 / 33,
@@ -1439,12 +1444,16 @@ hipError_t launch_shape(const Geom& g, const void* Q, const int32_t* sel, int ke
 //     130 rows (3 / 1)            1.24   0.91   0.77   0.68   0.64
 //     168 rows (3 / 1)            1.32   1.05   0.88   0.73   0.63
 //     200 rows (2 / 1)            1.30   1.10   1.01   0.87   0.84
-// No row is left whole there, so a workspace still leaves every unsplit row's bits as
-// they are without one.
-bool split_key128(int G, int keep, bool split) {
+// and for the fewest rows, 5 and 40: 0.94 and 0.93 at 1 to 4 blocks, 0.98 and 0.95 at 8,
+// 1.01 and 0.98 at 12, 1.04 and 1.01 at 20. Past 170 rows lists of less than 48 blocks
+// are left whole, by the kernel that a call without a workspace takes, so that a
+// workspace leaves every unsplit row's bits as they are without one.
+bool whole128(int G, int keep) { return G > 2 * kCus / 3 && G <= kCus && keep < 48; }
+bool split_key128(int G, int keep, int d, bool split) {
     if (G > kCus) return false;
-    if (!split || G <= kCus / 3) return true;
-    return keep < 48 && (G <= kCus / 2 || G > 2 * kCus / 3);
+    if (!split || whole128(G, keep)) return keep > (d == 128 ? 4 : 2);
+    if (G <= kCus / 3) return keep >= 12;
+    return G <= kCus / 2 && keep < 48;
 }
 
 bool rows64(const Geom& g, int keep, int G) {
@@ -1466,15 +1475,18 @@ hipError_t launch_attn_bf16(const Geom& g, const void* Q, const int32_t* sel, in
     (void)hipGetLastError();
     if (g.block == 128 && (g.d == 64 || g.d == 128)) {
         const int G = (part.h_hi - part.h_lo) * g.nq;
-        const bool few = split_key128(G, keep, can_split(part, G, int64_t(g.block) * (g.d + 1) * 4));
+        const bool few =
+            split_key128(G, keep, g.d, can_split(part, G, int64_t(g.block) * (g.d + 1) * 4));
+        AttnPart p = part;  // rows that are left whole take the row order alone
+        if (whole128(G, keep)) p.ws_bytes = min(part.ws_bytes, row_sort_bytes(G));
         if (g.d == 64)
             return few ? launch_shape<64, 128>(g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale,
-                                               part, O, out_bf16, lse, s)
+                                               p, O, out_bf16, lse, s)
                        : launch_rows<64, 128>(g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale,
-                                              part, O, out_bf16, lse, s);
-        return few ? launch_shape<128, 128>(g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale, part,
+                                              p, O, out_bf16, lse, s);
+        return few ? launch_shape<128, 128>(g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale, p,
                                             O, out_bf16, lse, s)
-                   : launch_rows<128, 128>(g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale, part,
+                   : launch_rows<128, 128>(g, Q, sel, keep, slot_of, Kp, Vp, capacity, scale, p,
                                            O, out_bf16, lse, s);
     }
     if (g.block != 64 || (g.d != 64 && g.d != 128)) return hipErrorInvalidValue;
@@ -1492,7 +1504,8 @@ int64_t attn_tail_workspace_bytes(const Geom& g, int keep) {
     const size_t dyn = size_t(keep) * sizeof(int32_t);
     int slots = 0;
     if (g.block == 128 && (g.d == 64 || g.d == 128)) {
-        const bool few = split_key128(g.H * g.nq, keep, true);
+        const bool few =
+            whole128(g.H * g.nq, keep) || split_key128(g.H * g.nq, keep, g.d, true);
         if (g.d == 64)
             slots = few ? resident_slots(attn_bf16_kernel<64, 128, true, false>, Cfg<64, 128>::THREADS, dyn)
                         : resident_slots(attn_rows_kernel<64, 128, true, false, false>,

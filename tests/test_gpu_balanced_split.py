@@ -4,7 +4,7 @@ none. Launches on each side of the lines between those.
 
 Rows, pieces and the plain call's bits where nothing is split follow
 ``test_gpu_balanced.py``, whose helpers read the split back from the workspace's
-size; split rows meet the parity bar against the oracle.
+size; the rows of both calls meet the parity bar against the oracle.
 """
 
 import numpy as np
@@ -20,16 +20,23 @@ pytestmark = pytest.mark.gpu
 
 # (H, L, d, block, i0, i1, dtype), kept blocks, pieces; all end in a ragged block
 SPLIT = [
-    ((2, 9000, 128, 128, 35, 71, "bf16"), 28, 3),    # 72 rows: split-key kernel
+    ((1, 9000, 128, 128, 66, 71, "bf16"), 4, 4),     # 5 rows: rows kernel
+    ((2, 9000, 64, 128, 35, 71, "bf16"), 11, 4),     # 72 rows: rows kernel, its longest list
+    ((2, 9000, 128, 128, 35, 71, "bf16"), 12, 3),    # split-key kernel
+    ((2, 9000, 128, 128, 35, 71, "bf16"), 28, 3),
     ((2, 9000, 128, 128, 21, 71, "bf16"), 47, 2),    # 100 rows: its longest list
     ((2, 9000, 128, 128, 21, 71, "bf16"), 48, 4),    # rows kernel
     ((2, 9000, 128, 128, 7, 71, "bf16"), 5, 2),      # 128 rows: split-key kernel
     ((3, 9000, 128, 128, 28, 71, "bf16"), 1, 3),     # 129 rows: rows kernel, lists of one
     ((3, 9000, 64, 128, 20, 71, "bf16"), 71, 3),     # 153 rows, every block
     ((2, 10980, 128, 128, 1, 86, "bf16"), 24, 3),    # 170 rows: the last in three
-    ((3, 7400, 64, 128, 1, 58, "bf16"), 47, 1),      # 171 rows: split-key kernel, whole
+    ((3, 7400, 64, 128, 1, 58, "bf16"), 2, 1),       # 171 rows, left whole: rows kernel
+    ((3, 7400, 64, 128, 1, 58, "bf16"), 3, 1),       # split-key kernel
+    ((3, 7400, 64, 128, 1, 58, "bf16"), 47, 1),
     ((3, 7400, 64, 128, 1, 58, "bf16"), 48, 2),      # rows kernel, in two
-    ((4, 8300, 128, 128, 1, 65, "bf16"), 50, 2),     # 256 rows
+    ((4, 8300, 128, 128, 1, 65, "bf16"), 4, 1),      # 256 rows, whole: rows kernel
+    ((4, 8300, 128, 128, 1, 65, "bf16"), 5, 1),      # split-key kernel
+    ((4, 8300, 128, 128, 1, 65, "bf16"), 50, 2),     # rows kernel, in two
 ]
 
 
@@ -53,18 +60,18 @@ def test_every_row_split(gpu, geo, keep, pieces):
     if pieces == 1:
         assert torch.equal(O0.view(torch.int16), O1.view(torch.int16))
         assert torch.equal(l0.view(torch.int32), l1.view(torch.int32))
-        return
     Qf, Kf, Vf = (orc.decode_input(x, dt) for x in (q, k, v))
-    On, ln = O1.float().cpu().numpy(), l1.cpu().numpy()
+    got = [(O.float().cpu().numpy(), l.cpu().numpy()) for O, l in ((O0, l0), (O1, l1))]
     for row in sorted({*range(0, rows, max(1, rows // 20)), rows - 1}):
         h, r = divmod(row, nq)
         o_ref, lse_ref = orc.attend_block(Qf[h], Kf[h], Vf[h], om[h, r], i0 + r, L, b,
                                           ctypes_scale(d))
-        P.check_attention(On[h, r * b:(r + 1) * b], o_ref, True, f"{geo} keep={keep} row={row}")
         fin = np.isfinite(lse_ref)
-        got = ln[h, r * b:(r + 1) * b]
-        assert (np.isneginf(got) == ~fin).all()
-        assert np.abs(got[fin] - lse_ref[fin]).max() <= 1e-4
+        for On, ln in got:
+            P.check_attention(On[h, r * b:(r + 1) * b], o_ref, True, f"{geo} keep={keep} row={row}")
+            lr = ln[h, r * b:(r + 1) * b]
+            assert (np.isneginf(lr) == ~fin).all()
+            assert np.abs(lr[fin] - lse_ref[fin]).max() <= 1e-4
 
 
 @pytest.mark.parametrize("geo", GEOMS[:3], ids=lambda g: "H{}L{}d{}b{}_{}-{}_{}".format(*g))
